@@ -441,12 +441,15 @@ int ip_problem_create(ip_ctx *ctx, const ip_fparams *f, const ip_space *sp, cons
     delete p;
     return rc;
   }
-  // support-vector records: s_0..s_{d-1}, alpha, padding (64 bytes)
+  // support-vector records (s_0..s_{d-1}, alpha, padding: 64 bytes), then
+  // the same as columns of ld doubles
   const int64_t S = f->n_sv;
-  std::vector<double> rec((size_t)S * 8, 0.0);
+  const int64_t ld = (S + IP_COL_PAD - 1) / IP_COL_PAD * IP_COL_PAD;
+  std::vector<double> rec((size_t)S * 8 + (size_t)ld * (d + 1), 0.0);
+  double *col = rec.data() + S * 8;
   for (int64_t i = 0; i < S; ++i) {
-    for (int j = 0; j < d; ++j) rec[i * 8 + j] = f->sv[i * d + j];
-    rec[i * 8 + d] = f->alpha[i];
+    for (int j = 0; j < d; ++j) col[j * ld + i] = rec[i * 8 + j] = f->sv[i * d + j];
+    col[d * ld + i] = rec[i * 8 + d] = f->alpha[i];
   }
   hipError_t e = hipMalloc((void **)&p->rec_dev, rec.size() * 8);
   if (e == hipSuccess) e = hipMalloc((void **)&p->seeds_dev, (size_t)n_seeds * d * 8);
@@ -461,7 +464,9 @@ int ip_problem_create(ip_ctx *ctx, const ip_fparams *f, const ip_space *sp, cons
   }
   p->n_seeds = n_seeds;
   p->f.rec = p->rec_dev;
+  p->f.col = p->rec_dev + S * 8;
   p->f.S = S;
+  p->f.ld = ld;
   p->f.p = f->kernel == IP_KERNEL_POLY ? f->degree : 1;
   p->f.kernel = f->kernel;
   p->f.gamma = f->gamma;

@@ -1,12 +1,9 @@
 // f evaluation at lattice vertices (the edge sign tests of Sec. V-A and the
 // subdivision vertices of Sec. V-B need f at every vertex they touch).
 //
-// Canonical FP64 kernel: one lane per vertex, R vertices per lane (register
-// blocking), support vectors consumed in index order so the accumulation
-// order is the canonical one of ip.h and the result is bit-identical on every
-// device.  Every lane of a wave reads the same 64-byte support-vector record
-// at the same time, so the record is a wave-uniform load served from the
-// scalar cache into SGPRs and used as the scalar operand of v_fma_f64.
+// Canonical FP64 kernels: the terms of a vertex may be formed in any order
+// and place, but are added in index order, so the result is the canonical one
+// of ip.h and bit-identical on every device.
 //
 // FP32 certified kernel: the decision function of a degree-p polynomial
 // kernel is a polynomial of degree p in d variables; it is evaluated in FP32
@@ -32,149 +29,239 @@ static __device__ __align__(256) unsigned char scratch[256 + 4 * (size_t)IP_NOAL
 
 namespace {
 
+// The canonical FP64 sum comes in two kernels with the same MODEs:
 // MODE 0: vertex-table entries listed by slot (key at keys[slot * 4], result
 //         to out[slot * 4]);
 // MODE 1: raw int32 vertices, result to out[i];
 // MODE 2: raw int32 vertices at the indices in list, result to out[index].
 // n_dev (may be NULL): the item count is *n_dev, written by an earlier
 // kernel on the stream, at most n (the grid is sized for n).
-template <int D, int P, int R, int MODE>
-__global__ __launch_bounds__(256) void feval64_kernel(FDev F, LatDev L, const uint32_t *__restrict__ list,
-                                                      uint64_t n, const unsigned long long *n_dev,
-                                                      const uint64_t *__restrict__ keys,
-                                                      const int32_t *__restrict__ vraw,
-                                                      double *__restrict__ out) {
+//
+// Both read the support vectors through vector loads: one record per
+// wave-uniform scalar load ties a wave to the scalar cache's miss rate
+// (about 115 ns per 64-byte record at S = 2000, whatever the unrolling,
+// against the 17 ns of its arithmetic).
+
+// Vertex i of the call: its destination and coordinates.
+template <int D, int MODE>
+__device__ __forceinline__ uint64_t load_vertex(const LatDev &L, const uint32_t *__restrict__ list, uint64_t i,
+                                                const uint64_t *__restrict__ keys,
+                                                const int32_t *__restrict__ vraw, double *x) {
+  const uint64_t src = MODE == 1 ? i : (uint64_t)list[i];
+  int32_t v[D];
+  if (MODE == 0) {
+    vunpack<D>(L, keys[src * 4], v);
+  } else {
+#pragma unroll
+    for (int j = 0; j < D; ++j) v[j] = vraw[src * D + j];
+  }
+  lat_coords<D>(L, v, x);
+  return src;
+}
+
+// Few vertices: a block of eight waves takes 7 V of them.  Seven waves hold
+// V vertices each in registers and form their terms one support vector per
+// lane (the vectors as columns, read coalesced one tile of 64 ahead); the
+// eighth adds the terms of the tile before in index order, one vertex per
+// lane, from LDS.  What is left serial is the chain of S dependent fma
+// (8 cycles each): d = 6, S = 2000 takes 25 us for up to 4096 vertices, where
+// one vertex per lane took 314 us.
+template <int D, int P, int MODE, int V>
+__global__ __launch_bounds__(512) void feval64_split_kernel(FDev F, LatDev L, const uint32_t *__restrict__ list,
+                                                            uint64_t n, const unsigned long long *n_dev,
+                                                            const uint64_t *__restrict__ keys,
+                                                            const int32_t *__restrict__ vraw,
+                                                            double *__restrict__ out) {
+  constexpr int T = IP_COL_PAD, NW = 7, G = NW * V, LD = G | 1;
   constexpr uint64_t S4 = MODE == 0 ? 4 : 1;
+  __shared__ double term[2][T * LD];
+  __shared__ __align__(16) double alpha[2][T];
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
   if (n_dev) n = (uint64_t)*n_dev < n ? (uint64_t)*n_dev : n;
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x * R;
-  for (uint64_t base = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) * R; base < n; base += stride) {
-    double x[R][D];
-    uint64_t dst[R];
+  const int64_t ld = F.ld;
+  const int nt = (int)(ld / T);
+  for (uint64_t blk = (uint64_t)blockIdx.x * G; blk < n; blk += (uint64_t)gridDim.x * G) {
+    // step t of either branch: the terms of tile t are formed while those of
+    // tile t - 1 are added; both meet at one barrier per step
+    if (wv < NW) {
+      const uint64_t v0 = blk + (uint64_t)wv * V;
+      double x[V][D];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      uint64_t i = base + r < n ? base + r : n - 1;
-      int32_t v[D];
-      if (MODE == 0) {
-        uint32_t s = list[i];
-        dst[r] = s;
-        vunpack<D>(L, keys[(uint64_t)s * 4], v);
-      } else {
-        const uint64_t src = MODE == 2 ? (uint64_t)list[i] : i;
-        dst[r] = src;
+      for (int r = 0; r < V; ++r) load_vertex<D, MODE>(L, list, v0 + r < n ? v0 + r : n - 1, keys, vraw, x[r]);
+      double nx[D], nal = F.col[D * ld + lane];
 #pragma unroll
-        for (int j = 0; j < D; ++j) v[j] = vraw[src * D + j];
-      }
-      lat_coords<D>(L, v, x[r]);
-    }
-    double acc[R];
+      for (int j = 0; j < D; ++j) nx[j] = F.col[j * ld + lane];
+      for (int t = 0; t <= nt; ++t) {
+        if (t < nt && v0 < n) {
+          double sv[D];
 #pragma unroll
-    for (int r = 0; r < R; ++r) acc[r] = 0.0;
-    const double gamma = F.gamma, coef0 = F.coef0;
-    for (int64_t s = 0; s < F.S; ++s) {
-      const double *rec = F.rec + s * 8;
-      double sv[D];
+          for (int j = 0; j < D; ++j) sv[j] = nx[j];
+          if (wv == 0) alpha[t & 1][lane] = nal;
+          const int64_t s1 = t + 1 < nt ? (int64_t)(t + 1) * T + lane : lane;
 #pragma unroll
-      for (int j = 0; j < D; ++j) sv[j] = rec[j];
-      const double al = rec[D];
+          for (int j = 0; j < D; ++j) nx[j] = F.col[j * ld + s1];
+          if (wv == 0) nal = F.col[D * ld + s1];
+          double *tw = &term[t & 1][lane * LD + wv * V];
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        double dot = 0.0;
-#pragma unroll
-        for (int j = 0; j < D; ++j) dot = fma(sv[j], x[r][j], dot);
-        double t = fma(gamma, dot, coef0);
-        double tp = t;
-        if (P > 0) {
-#pragma unroll
-          for (int q = 1; q < P; ++q) tp = tp * t;
-        } else {
-          for (int q = 1; q < F.p; ++q) tp = tp * t;
+          for (int r = 0; r < V; ++r) tw[r] = sv_term<D, P>(F, sv, x[r]);
         }
-        acc[r] = fma(al, tp, acc[r]);
+        __syncthreads();
       }
-    }
+    } else {
+      double acc = 0.0;
+      const int c = lane < G ? lane : 0;
+      for (int t = 0; t <= nt; ++t) {
+        if (t > 0) {
+          const double *tr = term[(t - 1) & 1] + c;
+          const double *al = alpha[(t - 1) & 1];
+          const int64_t m = F.S - (int64_t)(t - 1) * T;
+          if (m >= T) {
+            // 16 terms and weights in flight while 16 are added
+            constexpr int H = 16;
+            double a0[H], b0[H], a1[H], b1[H];
 #pragma unroll
-    for (int r = 0; r < R; ++r)
-      if (base + r < n) out[dst[r] * S4] = acc[r] + F.bias;
+            for (int s = 0; s < H; ++s) {
+              a0[s] = al[s];
+              b0[s] = tr[s * LD];
+            }
+#pragma unroll
+            for (int h = 0; h < T; h += 2 * H) {
+#pragma unroll
+              for (int s = 0; s < H; ++s) {
+                a1[s] = al[h + H + s];
+                b1[s] = tr[(h + H + s) * LD];
+              }
+              __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+              for (int s = 0; s < H; ++s) acc = fma(a0[s], b0[s], acc);
+              if (h + 2 * H < T) {
+#pragma unroll
+                for (int s = 0; s < H; ++s) {
+                  a0[s] = al[h + 2 * H + s];
+                  b0[s] = tr[(h + 2 * H + s) * LD];
+                }
+              }
+              __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+              for (int s = 0; s < H; ++s) acc = fma(a1[s], b1[s], acc);
+            }
+          } else {
+            for (int s = 0; s < (int)m; ++s) acc = fma(al[s], tr[s * LD], acc);
+          }
+        }
+        __syncthreads();
+      }
+      const uint64_t i = blk + lane;
+      if (lane < G && i < n) out[(MODE == 1 ? i : (uint64_t)list[i]) * S4] = acc + F.bias;
+    }
   }
 }
 
-// Canonical FP64 RBF evaluation (same MODEs as feval64_kernel): the support
-// vectors pass through LDS in tiles of kRbfTile records, which every lane of
-// the block then reads at the same address (a broadcast), in index order.
-// The loop over vertex groups is uniform across the block, so the barriers
-// around each tile are reached by every thread.
-constexpr int kRbfTile = 256;
-
-template <int D, int R, int MODE>
-__global__ __launch_bounds__(256) void rbf64_kernel(FDev F, LatDev L, const uint32_t *__restrict__ list, uint64_t n,
-                                                    const unsigned long long *n_dev,
-                                                    const uint64_t *__restrict__ keys,
-                                                    const int32_t *__restrict__ vraw, double *__restrict__ out) {
-  __shared__ double tile[kRbfTile * 8];
+// Many vertices: R of them per lane, the records passing through LDS in
+// tiles of 64 (the next one in flight meanwhile), each read at one address by
+// the whole wave and used for R vertices; U records at a time, so that U R
+// chains overlap.  The loop over vertex groups is uniform across the block,
+// so every thread reaches the barrier of each tile.
+template <int D, int P, int R, int U, int MODE>
+__global__ __launch_bounds__(256, (P < 0 || R < 4) ? 4 : 2) void feval64_tile_kernel(
+    FDev F, LatDev L, const uint32_t *__restrict__ list, uint64_t n, const unsigned long long *n_dev,
+    const uint64_t *__restrict__ keys, const int32_t *__restrict__ vraw, double *__restrict__ out) {
+  constexpr int T = 64;
   constexpr uint64_t S4 = MODE == 0 ? 4 : 1;
+  __shared__ __align__(16) double tile[2][T * 8];
   if (n_dev) n = (uint64_t)*n_dev < n ? (uint64_t)*n_dev : n;
-  const uint64_t per_block = (uint64_t)blockDim.x * R;
-  for (uint64_t blk = (uint64_t)blockIdx.x * per_block; blk < n; blk += (uint64_t)gridDim.x * per_block) {
-    const uint64_t base = blk + (uint64_t)threadIdx.x * R;
-    double x[R][D];
+  const int64_t nd = F.S * 8;
+  const int64_t nt = (F.S + T - 1) / T;
+  for (uint64_t blk = (uint64_t)blockIdx.x * 256 * R; blk < n; blk += (uint64_t)gridDim.x * 256 * R) {
+    double x[R][D], acc[R];
     uint64_t dst[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const uint64_t i = base + r < n ? base + r : n - 1;
-      int32_t v[D];
-      if (MODE == 0) {
-        const uint32_t s = list[i];
-        dst[r] = s;
-        vunpack<D>(L, keys[(uint64_t)s * 4], v);
-      } else {
-        const uint64_t src = MODE == 2 ? (uint64_t)list[i] : i;
-        dst[r] = src;
-#pragma unroll
-        for (int j = 0; j < D; ++j) v[j] = vraw[src * D + j];
-      }
-      lat_coords<D>(L, v, x[r]);
+      const uint64_t q = blk + r * 256 + threadIdx.x;
+      dst[r] = load_vertex<D, MODE>(L, list, q < n ? q : n - 1, keys, vraw, x[r]);
+      acc[r] = 0.0;
     }
-    double acc[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) acc[r] = 0.0;
-    for (int64_t t0 = 0; t0 < F.S; t0 += kRbfTile) {
-      const int nt = (int)(F.S - t0 < kRbfTile ? F.S - t0 : kRbfTile);
+    double2 nx;
+    auto fetch = [&](int64_t t) {
+      const int64_t o = t * T * 8 + threadIdx.x * 2;
+      nx = o < nd ? *(const double2 *)(F.rec + o) : make_double2(0.0, 0.0);
+    };
+    fetch(0);
+    __syncthreads();
+    for (int64_t t = 0; t < nt; ++t) {
+      *(double2 *)&tile[t & 1][threadIdx.x * 2] = nx;
       __syncthreads();
-      for (int q = threadIdx.x; q < nt * 8; q += blockDim.x) tile[q] = F.rec[t0 * 8 + q];
-      __syncthreads();
-      for (int s = 0; s < nt; ++s) {
-        const double *sv = tile + s * 8;
+      if (t + 1 < nt) fetch(t + 1);
+      const double *tl = tile[t & 1];
+      const int m = (int)(F.S - t * T < T ? F.S - t * T : T);
+      int s = 0;
+      for (; s + U <= m; s += U) {
+        double tp[U][R], al[U];
 #pragma unroll
-        for (int r = 0; r < R; ++r) acc[r] = rbf_term<D>(sv, sv[D], F.gamma, x[r], acc[r]);
+        for (int u = 0; u < U; ++u) {
+          double sv[8];
+#pragma unroll
+          for (int j = 0; j < (D + 2) / 2; ++j) {
+            const double2 z = *(const double2 *)&tl[(s + u) * 8 + 2 * j];
+            sv[2 * j] = z.x;
+            sv[2 * j + 1] = z.y;
+          }
+          al[u] = sv[D];
+#pragma unroll
+          for (int r = 0; r < R; ++r) tp[u][r] = sv_term<D, P>(F, sv, x[r]);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int r = 0; r < R; ++r) acc[r] = fma(al[u], tp[u][r], acc[r]);
       }
+      for (; s < m; ++s)
+#pragma unroll
+        for (int r = 0; r < R; ++r) acc[r] = fma(tl[s * 8 + D], sv_term<D, P>(F, tl + s * 8, x[r]), acc[r]);
     }
 #pragma unroll
     for (int r = 0; r < R; ++r)
-      if (base + r < n) out[dst[r] * S4] = acc[r] + F.bias;
+      if (blk + r * 256 + threadIdx.x < n) out[dst[r] * S4] = acc[r] + F.bias;
   }
 }
+
+// Which kernel, by the vertex count n (times in us at d = 6, p = 3,
+// S = 2000).  Up to 16384 vertices one lane each fills less than one wave per
+// CU, and the split form is the faster (4096: 25 against 90; 16384: 68
+// against 92).  Above, the least number of vertices per lane that still
+// fills the SIMDs once: 65 536 lanes are one wave on each (65536: 1 per lane
+// 101, 2 per lane 148; 200003: 1, 2 and 4 per lane 264, 209, 232; 1048576:
+// 1006, 772, 730).  The Gaussian term is 34 operations long and needs no
+// sharing of the records (d = 5, S = 300, 1048576 vertices: 351 with one per
+// lane, 438 with two).
+constexpr uint64_t kSplitMax = 16384;
 
 template <int D, int P, int MODE>
 void launch64(hipStream_t st, const FDev &F, const LatDev &L, const uint32_t *list, uint64_t n,
               const unsigned long long *n_dev, const uint64_t *keys, const int32_t *vraw, double *out) {
-  constexpr int R = D <= 4 ? 4 : 2;
-  const uint64_t threads = (n + R - 1) / R;
-  uint64_t blocks = (threads + 255) / 256;
-  if (blocks > 65536) blocks = 65536;
-  if (blocks == 0) return;
-  hipLaunchKernelGGL((feval64_kernel<D, P, R, MODE>), dim3((unsigned)blocks), dim3(256), 0, st, F, L, list, n, n_dev,
-                     keys, vraw, out);
+#define IP_L64(KERNEL, PER, BLOCK)                                                                                   \
+  hipLaunchKernelGGL(KERNEL, dim3((unsigned)std::min<uint64_t>((n + (PER) - 1) / (PER), 65536)), dim3(BLOCK), 0, st, \
+                     F, L, list, n, n_dev, keys, vraw, out)
+  if (n <= kSplitMax) {
+    IP_L64((feval64_split_kernel<D, P, MODE, 4>), 28, 512);
+  } else if (P < 0) {
+    IP_L64((feval64_tile_kernel<D, P, 1, 2, MODE>), 256, 256);
+  } else if (n <= 98304) {
+    IP_L64((feval64_tile_kernel<D, P, 1, 4, MODE>), 256, 256);
+  } else if (n <= 393216) {
+    IP_L64((feval64_tile_kernel<D, P, 2, 4, MODE>), 512, 256);
+  } else {
+    IP_L64((feval64_tile_kernel<D, P, 4, 4, MODE>), 1024, 256);
+  }
+#undef IP_L64
 }
 
 template <int D, int MODE>
 void launch64_p(hipStream_t st, const FDev &F, const LatDev &L, const uint32_t *list, uint64_t n,
                 const unsigned long long *n_dev, const uint64_t *keys, const int32_t *vraw, double *out) {
   if (F.kernel == IP_KERNEL_RBF) {
-    constexpr int R = 2;
-    const uint64_t blocks = std::min<uint64_t>((n + 256 * R - 1) / (256 * R), 65536);
-    if (blocks == 0) return;
-    hipLaunchKernelGGL((rbf64_kernel<D, R, MODE>), dim3((unsigned)blocks), dim3(256), 0, st, F, L, list, n, n_dev,
-                       keys, vraw, out);
+    launch64<D, -1, MODE>(st, F, L, list, n, n_dev, keys, vraw, out);
     return;
   }
   switch (F.p) {

@@ -38,12 +38,16 @@ struct LatDev {
 };
 
 // Manifold parameters on the device.  rec holds one 64-byte record per
-// support vector: s_0..s_{d-1}, alpha, zero padding (8 doubles).
+// support vector: s_0..s_{d-1}, alpha, zero padding (8 doubles).  col holds
+// the same numbers as columns: s_0, .., s_{d-1}, alpha, each of ld doubles
+// (S rounded up to IP_COL_PAD, zeros past S).
+#define IP_COL_PAD 64
 // kernel: IP_KERNEL_POLY (alpha_i (gamma <s_i, x> + coef0)^p) or
 // IP_KERNEL_RBF (alpha_i exp(-(gamma |x - s_i|^2))).
 struct FDev {
   const double *rec;
-  int64_t S;
+  const double *col;
+  int64_t S, ld;
   int32_t p;
   int32_t kernel;
   double gamma, coef0, bias;
@@ -131,6 +135,35 @@ __device__ __forceinline__ double rbf_term(const double *sv, double al, double g
     d2 = fma(df, df, d2);
   }
   return fma(al, exp_own(-(gamma * d2)), acc);
+}
+
+// One term of the canonical sum at x: t^p (P > 0: the degree, 0: F.p) or, P
+// = -1, the Gaussian exp(-(gamma |x - s|^2)); acc = fma(alpha, term, acc)
+// follows in index order.
+template <int D, int P>
+__device__ __forceinline__ double sv_term(const FDev &F, const double *sv, const double *x) {
+  if constexpr (P < 0) {
+    double d2 = 0.0;
+#pragma unroll
+    for (int j = 0; j < D; ++j) {
+      const double df = x[j] - sv[j];
+      d2 = fma(df, df, d2);
+    }
+    return exp_own(-(F.gamma * d2));
+  } else {
+    double dot = 0.0;
+#pragma unroll
+    for (int j = 0; j < D; ++j) dot = fma(sv[j], x[j], dot);
+    const double t = fma(F.gamma, dot, F.coef0);
+    double tp = t;
+    if (P > 0) {
+#pragma unroll
+      for (int q = 1; q < P; ++q) tp = tp * t;
+    } else {
+      for (int q = 1; q < F.p; ++q) tp = tp * t;
+    }
+    return tp;
+  }
 }
 
 // FP32 monomial-basis form of f (see feval.hip).  c[0] is the constant term
