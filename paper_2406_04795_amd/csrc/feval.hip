@@ -547,78 +547,245 @@ int dispatch32_p(ip_ctx *ctx, const ip_problem *p, const LatDev &L, const uint32
   return dispatch32<MODE>(ctx, p->poly, L, list, n, vt, vb, vraw, out, bout, fb, fb_ctr, c64);
 }
 
-// Canonical f and gradient at x (the order of ip.h's ip_seed_search): per
-// support vector in index order, read as a wave-uniform record.
-template <int D>
-__device__ __forceinline__ double f_grad(const FDev &F, const double *x, double *g) {
-  double acc = 0.0;
-#pragma unroll
-  for (int j = 0; j < D; ++j) g[j] = 0.0;
-  if (F.kernel == IP_KERNEL_RBF) {
-    const double m2g = -2.0 * F.gamma;
-    for (int64_t i = 0; i < F.S; ++i) {
-      const double *rec = F.rec + i * 8;
-      double df[D], d2 = 0.0;
-#pragma unroll
-      for (int j = 0; j < D; ++j) {
-        df[j] = x[j] - rec[j];
-        d2 = fma(df[j], df[j], d2);
-      }
-      const double e = exp_own(-(F.gamma * d2));
-      acc = fma(rec[D], e, acc);
-      const double w = (rec[D] * e) * m2g;
-#pragma unroll
-      for (int j = 0; j < D; ++j) g[j] = fma(w, df[j], g[j]);
-    }
-    return acc + F.bias;
+// One support vector's factors for f and its gradient at x (the order of
+// ip.h's ip_seed_search): f = fma(alpha, e, f), g_j = fma(w, s_j, g_j)
+// (RBF: fma(w, x_j - s_j, g_j)); pg is p gamma (RBF: -2 gamma).
+template <int D, bool RBF>
+__device__ __forceinline__ void grad_factors(const FDev &F, const double *sv, const double *x, double pg, double *e,
+                                             double *w) {
+  if (RBF) {
+    *e = sv_term<D, -1>(F, sv, x);
+    *w = (sv[D] * *e) * pg;
+    return;
   }
-  const double pg = (double)F.p * F.gamma;
-  for (int64_t i = 0; i < F.S; ++i) {
-    const double *rec = F.rec + i * 8;
-    double dot = 0.0;
+  double dot = 0.0;
 #pragma unroll
-    for (int j = 0; j < D; ++j) dot = fma(rec[j], x[j], dot);
-    const double t = fma(F.gamma, dot, F.coef0);
-    double tp1 = 1.0;
-    if (F.p > 1) {
-      tp1 = t;
-      for (int r = 2; r < F.p; ++r) tp1 = tp1 * t;
-    }
-    acc = fma(rec[D], tp1 * t, acc);
-    const double w = (rec[D] * tp1) * pg;
-#pragma unroll
-    for (int j = 0; j < D; ++j) g[j] = fma(w, rec[j], g[j]);
+  for (int j = 0; j < D; ++j) dot = fma(sv[j], x[j], dot);
+  const double t = fma(F.gamma, dot, F.coef0);
+  double tp1 = 1.0;
+  if (F.p > 1) {
+    tp1 = t;
+    for (int r = 2; r < F.p; ++r) tp1 = tp1 * t;
   }
-  return acc + F.bias;
+  *e = tp1 * t;
+  *w = (sv[D] * tp1) * pg;
 }
 
 // Seed search (Sec. V-A: minimise |f| from given configurations), one lane
 // per start: `iters` minimum-norm Newton steps, each clamped into the box;
-// a zero gradient ends a lane's steps.  Then f at the final point.
-template <int D>
+// a zero gradient ends a lane's steps.  Then f at the final point.  The
+// records pass through LDS in tiles, as in feval64_tile_kernel (the loops
+// are uniform across the block; a lane whose steps have ended keeps its x).
+template <int D, bool RBF>
 __global__ __launch_bounds__(256) void seed_kernel(FDev F, LatDev L, const double *__restrict__ q0, uint64_t n,
                                                    int iters, double *__restrict__ q, double *__restrict__ fq) {
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
-    double x[D], g[D];
+  constexpr int T = 64, U = RBF ? 2 : 4;
+  __shared__ __align__(16) double tile[2][T * 8];
+  const double pg = RBF ? -2.0 * F.gamma : (double)F.p * F.gamma;
+  const int64_t nd = F.S * 8, nt = (F.S + T - 1) / T;
+  for (uint64_t blk = (uint64_t)blockIdx.x * 256; blk < n; blk += (uint64_t)gridDim.x * 256) {
+    const uint64_t i = blk + threadIdx.x < n ? blk + threadIdx.x : n - 1;
+    double x[D], g[D], f = 0.0;
+    bool done = false;
 #pragma unroll
     for (int j = 0; j < D; ++j) x[j] = q0[i * D + j];
-    for (int it = 0; it < iters; ++it) {
-      const double fv = f_grad<D>(F, x, g);
+    for (int it = 0; it <= iters; ++it) {
+      f = 0.0;
+#pragma unroll
+      for (int j = 0; j < D; ++j) g[j] = 0.0;
+      double2 nx;
+      auto fetch = [&](int64_t t) {
+        const int64_t o = t * T * 8 + threadIdx.x * 2;
+        nx = o < nd ? *(const double2 *)(F.rec + o) : make_double2(0.0, 0.0);
+      };
+      auto add = [&](const double *sv, double e, double w) {
+        f = fma(sv[D], e, f);
+#pragma unroll
+        for (int j = 0; j < D; ++j) g[j] = fma(w, RBF ? x[j] - sv[j] : sv[j], g[j]);
+      };
+      fetch(0);
+      __syncthreads();
+      for (int64_t t = 0; t < nt; ++t) {
+        *(double2 *)&tile[t & 1][threadIdx.x * 2] = nx;
+        __syncthreads();
+        if (t + 1 < nt) fetch(t + 1);
+        const double *tl = tile[t & 1];
+        const int m = (int)(F.S - t * T < T ? F.S - t * T : T);
+        int s = 0;
+        for (; s + U <= m; s += U) {
+          double sv[U][8], e[U], w[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+#pragma unroll
+            for (int j = 0; j < (D + 2) / 2; ++j) {
+              const double2 z = *(const double2 *)&tl[(s + u) * 8 + 2 * j];
+              sv[u][2 * j] = z.x;
+              sv[u][2 * j + 1] = z.y;
+            }
+            grad_factors<D, RBF>(F, sv[u], x, pg, &e[u], &w[u]);
+          }
+#pragma unroll
+          for (int u = 0; u < U; ++u) add(sv[u], e[u], w[u]);
+        }
+        for (; s < m; ++s) {
+          double e, w;
+          grad_factors<D, RBF>(F, tl + s * 8, x, pg, &e, &w);
+          add(tl + s * 8, e, w);
+        }
+      }
+      f = f + F.bias;
       double n2 = 0.0;
 #pragma unroll
       for (int j = 0; j < D; ++j) n2 = fma(g[j], g[j], n2);
-      if (!(n2 > 0.0)) break;
-      const double c = fv / n2;
+      done = done || !(n2 > 0.0);
+      if (it == iters || done) continue;
+      const double c = f / n2;
 #pragma unroll
       for (int j = 0; j < D; ++j) {
         const double v = fma(-c, g[j], x[j]);
         x[j] = v < L.lo[j] ? L.lo[j] : (v > L.hi[j] ? L.hi[j] : v);
       }
     }
-    const double fv = f_grad<D>(F, x, g);
+    if (blk + threadIdx.x < n) {
 #pragma unroll
-    for (int j = 0; j < D; ++j) q[i * D + j] = x[j];
-    fq[i] = fv;
+      for (int j = 0; j < D; ++j) q[i * D + j] = x[j];
+      fq[i] = f;
+    }
+  }
+}
+
+// The same search with the sums of a step formed side by side, for few starts:
+// a block takes 16 starts.  Waves 2 to 7 form, per support vector and start,
+// the two factors that the sums share (t^p or the exponential, and the
+// gradient weight), one tile of 48 vectors ahead; waves 0 and 1 add them, one
+// lane per (sum, start), f and the d gradient components side by side, each
+// in index order.  Serial per step: S dependent fma instead of S times the
+// whole term (d = 6, S = 2000, 20 steps, 3001 starts: 7.06 ms with one lane
+// per start).
+constexpr int kSeedG = 16, kSeedT = 48;
+// One lane per start takes the same time up to 65 536 starts (a wave per
+// SIMD); the split form grows from four blocks per CU on.  Both at d = 5,
+// S = 500, 10 steps: 3000 starts 125 us (split) and 527, 12 000: 292 and 527,
+// 16 000: 367 and 527; at d = 3, S = 50: 12 000: 59 and 56, 16 000: 70 and 56.
+constexpr int64_t kSeedSplitMax = 12288;
+
+template <int D, bool RBF>
+__global__ __launch_bounds__(512) void seed_split_kernel(FDev F, LatDev L, const double *__restrict__ q0, uint64_t n,
+                                                         int iters, double *__restrict__ q, double *__restrict__ fq) {
+  constexpr int G = kSeedG, T = kSeedT, NR = T / 24;  // 24 vectors per round of the six forming waves
+  __shared__ double val[2][2][T * G];  // [buffer][sum factor, gradient weight]
+  __shared__ double recs[2][T * 8];
+  __shared__ double xs[G * 8], res[8 * G];
+  __shared__ int done[G];
+  const int tid = threadIdx.x, g = tid & (G - 1);
+  const bool adds = tid < 128;
+  const int c = tid >> 4;                    // adding waves: the sum, 0 for f, 1 + j for component j
+  const int sr = (tid - 128) >> 4;           // forming waves: vector within a round
+  const int nt = (int)((F.S + T - 1) / T);
+  const double pg = RBF ? -2.0 * F.gamma : (double)F.p * F.gamma;
+  for (uint64_t blk = (uint64_t)blockIdx.x * G; blk < n; blk += (uint64_t)gridDim.x * G) {
+    const uint64_t i = blk + g < n ? blk + g : n - 1;
+    if (tid < G) {
+#pragma unroll
+      for (int j = 0; j < D; ++j) xs[g * 8 + j] = q0[i * D + j];
+      done[g] = 0;
+    }
+    __syncthreads();
+    for (int it = 0;; ++it) {
+      double acc = 0.0;
+      if (adds) {
+        const int cc = c <= D ? c : 0;       // lanes past the last sum repeat f
+        const double xc = cc ? xs[g * 8 + cc - 1] : 0.0;
+        const int col = cc ? cc - 1 : D;
+        for (int t = 0; t <= nt; ++t) {
+          if (t > 0) {
+            const double *v = &val[(t - 1) & 1][cc ? 1 : 0][g];
+            const double *r = &recs[(t - 1) & 1][col];
+            const int m = (int)(F.S - (int64_t)(t - 1) * T < T ? F.S - (int64_t)(t - 1) * T : T);
+            int s = 0;
+            for (; s + 12 <= m; s += 12) {
+              double a[12], b[12];
+#pragma unroll
+              for (int u = 0; u < 12; ++u) {
+                a[u] = v[(s + u) * G];
+                b[u] = r[(s + u) * 8];
+                if (RBF) b[u] = cc ? xc - b[u] : b[u];
+              }
+#pragma unroll
+              for (int u = 0; u < 12; ++u) acc = fma(a[u], b[u], acc);
+            }
+            for (; s < m; ++s) acc = fma(v[s * G], RBF && cc ? xc - r[s * 8] : r[s * 8], acc);
+          }
+          __syncthreads();
+        }
+        if (c <= D) res[c * G + g] = c == 0 ? acc + F.bias : acc;
+      } else {
+        double x[D];
+#pragma unroll
+        for (int j = 0; j < D; ++j) x[j] = xs[g * 8 + j];
+        double nx[NR][D + 1];
+        auto fetch = [&](int t) {
+#pragma unroll
+          for (int k = 0; k < NR; ++k) {
+            const int64_t s = (int64_t)t * T + k * 24 + sr;
+            const double *rec = F.rec + (s < F.S ? s : F.S - 1) * 8;
+#pragma unroll
+            for (int j = 0; j <= D; ++j) nx[k][j] = rec[j];
+          }
+        };
+        fetch(0);
+        for (int t = 0; t <= nt; ++t) {
+          if (t < nt) {
+            double sv[NR][D + 1];
+#pragma unroll
+            for (int k = 0; k < NR; ++k)
+#pragma unroll
+              for (int j = 0; j <= D; ++j) sv[k][j] = nx[k][j];
+            if (t + 1 < nt) fetch(t + 1);
+#pragma unroll
+            for (int k = 0; k < NR; ++k) {
+              const int s = k * 24 + sr;
+              double e, w;
+              grad_factors<D, RBF>(F, sv[k], x, pg, &e, &w);
+              val[t & 1][0][s * G + g] = e;
+              val[t & 1][1][s * G + g] = w;
+              if (g == 0) {
+#pragma unroll
+                for (int j = 0; j <= D; ++j) recs[t & 1][s * 8 + j] = sv[k][j];
+              }
+            }
+          }
+          __syncthreads();
+        }
+      }
+      __syncthreads();
+      if (it == iters) break;
+      if (tid < G && !done[g]) {
+        double gr[D], n2 = 0.0;
+#pragma unroll
+        for (int j = 0; j < D; ++j) {
+          gr[j] = res[(1 + j) * G + g];
+          n2 = fma(gr[j], gr[j], n2);
+        }
+        if (!(n2 > 0.0)) {
+          done[g] = 1;
+        } else {
+          const double cf = res[g] / n2;
+#pragma unroll
+          for (int j = 0; j < D; ++j) {
+            const double v = fma(-cf, gr[j], xs[g * 8 + j]);
+            xs[g * 8 + j] = v < L.lo[j] ? L.lo[j] : (v > L.hi[j] ? L.hi[j] : v);
+          }
+        }
+      }
+      __syncthreads();
+    }
+    if (tid < G && blk + g < n) {
+#pragma unroll
+      for (int j = 0; j < D; ++j) q[i * D + j] = xs[g * 8 + j];
+      fq[i] = res[g];
+    }
+    __syncthreads();
   }
 }
 
@@ -626,10 +793,20 @@ __global__ __launch_bounds__(256) void seed_kernel(FDev F, LatDev L, const doubl
 
 int ip_seed_search_impl(ip_ctx *ctx, const ip_problem *p, const double *q0, int64_t n, int32_t iters, double *q,
                         double *fq) {
-  const unsigned blocks = (unsigned)std::min<int64_t>((n + 255) / 256, 16384);
-#define IP_SD(DD)                                                                                            \
-  hipLaunchKernelGGL((seed_kernel<DD>), dim3(blocks), dim3(256), 0, ctx->stream, p->f, p->fine, q0, (uint64_t)n, \
-                     (int)iters, q, fq)
+  const bool split = n <= kSeedSplitMax, rbf = p->f.kernel == IP_KERNEL_RBF;
+  const unsigned blocks = (unsigned)std::min<int64_t>(split ? (n + kSeedG - 1) / kSeedG : (n + 255) / 256, 16384);
+#define IP_SDK(KERNEL, THREADS)                                                                                  \
+  hipLaunchKernelGGL(KERNEL, dim3(blocks), dim3(THREADS), 0, ctx->stream, p->f, p->fine, q0, (uint64_t)n, (int)iters, \
+                     q, fq)
+#define IP_SD(DD)                                \
+  if (split && rbf)                              \
+    IP_SDK((seed_split_kernel<DD, true>), 512);  \
+  else if (split)                                \
+    IP_SDK((seed_split_kernel<DD, false>), 512); \
+  else if (rbf)                                  \
+    IP_SDK((seed_kernel<DD, true>), 256);        \
+  else                                           \
+    IP_SDK((seed_kernel<DD, false>), 256)
   switch (p->d) {
     case 2: IP_SD(2); break;
     case 3: IP_SD(3); break;
@@ -640,6 +817,7 @@ int ip_seed_search_impl(ip_ctx *ctx, const ip_problem *p, const double *q0, int6
     default: return ip_fail(ctx, IP_EINVAL, "dimension out of range");
   }
 #undef IP_SD
+#undef IP_SDK
   IP_TRY_HIP(ctx, hipGetLastError());
   return IP_OK;
 }
