@@ -89,22 +89,23 @@ __global__ __launch_bounds__(512) void feval64_split_kernel(FDev F, LatDev L, co
       double x[V][D];
 #pragma unroll
       for (int r = 0; r < V; ++r) load_vertex<D, MODE>(L, list, v0 + r < n ? v0 + r : n - 1, keys, vraw, x[r]);
-      double nx[D], nal = F.col[D * ld + lane];
+      // the next tile's records are asked for once this one's are used up, and
+      // waited for after the barrier
+      double sv[D], al;
+      auto fetch = [&](int64_t s) {
 #pragma unroll
-      for (int j = 0; j < D; ++j) nx[j] = F.col[j * ld + lane];
+        for (int j = 0; j < D; ++j) sv[j] = F.col[j * ld + s];
+        al = F.col[D * ld + s];
+      };
+      fetch(lane);
       for (int t = 0; t <= nt; ++t) {
         if (t < nt && v0 < n) {
-          double sv[D];
-#pragma unroll
-          for (int j = 0; j < D; ++j) sv[j] = nx[j];
-          if (wv == 0) alpha[t & 1][lane] = nal;
-          const int64_t s1 = t + 1 < nt ? (int64_t)(t + 1) * T + lane : lane;
-#pragma unroll
-          for (int j = 0; j < D; ++j) nx[j] = F.col[j * ld + s1];
-          if (wv == 0) nal = F.col[D * ld + s1];
+          if (wv == 0) alpha[t & 1][lane] = al;
           double *tw = &term[t & 1][lane * LD + wv * V];
 #pragma unroll
           for (int r = 0; r < V; ++r) tw[r] = sv_term<D, P>(F, sv, x[r]);
+          __builtin_amdgcn_sched_barrier(0);
+          fetch((t + 1 < nt ? (int64_t)(t + 1) * T : 0) + lane);
         }
         __syncthreads();
       }
@@ -703,16 +704,31 @@ __global__ __launch_bounds__(512) void seed_split_kernel(FDev F, LatDev L, const
             const double *r = &recs[(t - 1) & 1][col];
             const int m = (int)(F.S - (int64_t)(t - 1) * T < T ? F.S - (int64_t)(t - 1) * T : T);
             int s = 0;
-            for (; s + 12 <= m; s += 12) {
-              double a[12], b[12];
+            if (m == T) {
+              // H factors in flight while H are added
+              constexpr int H = 12;
+              double a0[H], b0[H], a1[H], b1[H];
+              auto get = [&](double *a, double *b, int s0) {
 #pragma unroll
-              for (int u = 0; u < 12; ++u) {
-                a[u] = v[(s + u) * G];
-                b[u] = r[(s + u) * 8];
-                if (RBF) b[u] = cc ? xc - b[u] : b[u];
+                for (int u = 0; u < H; ++u) {
+                  a[u] = v[(s0 + u) * G];
+                  b[u] = r[(s0 + u) * 8];
+                }
+              };
+              auto add = [&](const double *a, const double *b) {
+#pragma unroll
+                for (int u = 0; u < H; ++u) acc = fma(a[u], RBF && cc ? xc - b[u] : b[u], acc);
+              };
+              get(a0, b0, 0);
+#pragma unroll
+              for (; s < T; s += 2 * H) {
+                get(a1, b1, s + H);
+                __builtin_amdgcn_sched_barrier(0);
+                add(a0, b0);
+                if (s + 2 * H < T) get(a0, b0, s + 2 * H);
+                __builtin_amdgcn_sched_barrier(0);
+                add(a1, b1);
               }
-#pragma unroll
-              for (int u = 0; u < 12; ++u) acc = fma(a[u], b[u], acc);
             }
             for (; s < m; ++s) acc = fma(v[s * G], RBF && cc ? xc - r[s * 8] : r[s * 8], acc);
           }
@@ -723,25 +739,20 @@ __global__ __launch_bounds__(512) void seed_split_kernel(FDev F, LatDev L, const
         double x[D];
 #pragma unroll
         for (int j = 0; j < D; ++j) x[j] = xs[g * 8 + j];
-        double nx[NR][D + 1];
+        double sv[NR][D + 1];
+        // asked for once the tile before is used up, waited for after the barrier
         auto fetch = [&](int t) {
 #pragma unroll
           for (int k = 0; k < NR; ++k) {
             const int64_t s = (int64_t)t * T + k * 24 + sr;
             const double *rec = F.rec + (s < F.S ? s : F.S - 1) * 8;
 #pragma unroll
-            for (int j = 0; j <= D; ++j) nx[k][j] = rec[j];
+            for (int j = 0; j <= D; ++j) sv[k][j] = rec[j];
           }
         };
         fetch(0);
         for (int t = 0; t <= nt; ++t) {
           if (t < nt) {
-            double sv[NR][D + 1];
-#pragma unroll
-            for (int k = 0; k < NR; ++k)
-#pragma unroll
-              for (int j = 0; j <= D; ++j) sv[k][j] = nx[k][j];
-            if (t + 1 < nt) fetch(t + 1);
 #pragma unroll
             for (int k = 0; k < NR; ++k) {
               const int s = k * 24 + sr;
@@ -754,6 +765,8 @@ __global__ __launch_bounds__(512) void seed_split_kernel(FDev F, LatDev L, const
                 for (int j = 0; j <= D; ++j) recs[t & 1][s * 8 + j] = sv[k][j];
               }
             }
+            __builtin_amdgcn_sched_barrier(0);
+            fetch(t + 1 < nt ? t + 1 : 0);
           }
           __syncthreads();
         }
