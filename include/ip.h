@@ -150,8 +150,10 @@ typedef struct {
   int32_t levels;        /* breadth-first levels of the search */
   int32_t regrows;       /* hash-table growths */
   double ms_total;       /* wall time of ip_trace on the stream */
-  double ms_feval;       /* time in f-evaluation kernels (HIP events) */
-  double ms_expand;      /* time in frontier-expansion kernels */
+  double ms_feval;       /* time in f evaluation: of a search's levels by the
+                            device clock from kernel start to kernel start
+                            (launch gaps included), else by HIP events */
+  double ms_expand;      /* time in frontier expansion, likewise */
   double ms_points;      /* time in the intersection-point kernel */
   double ms_check;       /* time in the collision kernel (ip_check_cells) */
   double ms_subdivide;   /* batch mode: time in the subdivision kernel

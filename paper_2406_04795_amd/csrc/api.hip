@@ -349,22 +349,28 @@ int ip_create(ip_ctx **out, int device, void *stream) {
   ctx->stream = (hipStream_t)stream;
   hipError_t e = hipSetDevice(device);
   if (e == hipSuccess) e = hipMalloc((void **)&ctx->ctr_dev, sizeof(Counters));
-  if (e == hipSuccess) e = hipHostMalloc((void **)&ctx->ctr_host, sizeof(Counters), hipHostMallocDefault);
+  if (e == hipSuccess) e = hipHostMalloc((void **)&ctx->ctr_host, 3 * sizeof(Counters), hipHostMallocDefault);
   if (e == hipSuccess) e = hipEventCreate(&ctx->ev0);
   if (e == hipSuccess) e = hipEventCreate(&ctx->ev1);
+  for (hipEvent_t &ev : ctx->ctr_ev)
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+  int khz = 0;
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device);
+  if (khz > 0) ctx->ticks_per_ms = (double)khz;
   if (e != hipSuccess) {
     (void)hipGetLastError();
+    for (hipEvent_t ev : {ctx->ev0, ctx->ev1, ctx->ctr_ev[0], ctx->ctr_ev[1]})
+      if (ev) (void)hipEventDestroy(ev);
     if (ctx->ctr_dev) (void)hipFree(ctx->ctr_dev);
     if (ctx->ctr_host) (void)hipHostFree(ctx->ctr_host);
     delete ctx;
     return IP_EDEVICE;
   }
-  memset(ctx->ctr_host, 0, sizeof(Counters));
+  memset(ctx->ctr_host, 0, 3 * sizeof(Counters));
   if (ip_noalloc_setup(ctx) != IP_OK) {
     (void)hipFree(ctx->ctr_dev);
     (void)hipHostFree(ctx->ctr_host);
-    (void)hipEventDestroy(ctx->ev0);
-    (void)hipEventDestroy(ctx->ev1);
+    for (hipEvent_t ev : {ctx->ev0, ctx->ev1, ctx->ctr_ev[0], ctx->ctr_ev[1]}) (void)hipEventDestroy(ev);
     delete ctx;
     return IP_EDEVICE;
   }
@@ -387,7 +393,7 @@ void ip_destroy(ip_ctx *ctx) {
   (void)hipSetDevice(ctx->device);
   (void)hipStreamSynchronize(ctx->stream);
   DevBuf *bufs[] = {&ctx->vtf.keys, &ctx->vtf.eval, &ctx->vtf.vals, &ctx->vtf.fb, &ctx->vtc.keys,
-                    &ctx->vtc.eval, &ctx->vtc.vals, &ctx->vtc.fb, &ctx->vt_aux, &ctx->scratch, &ctx->scene};
+                    &ctx->vtc.eval, &ctx->vtc.vals, &ctx->vtc.fb, &ctx->vtf.out,  &ctx->vtc.out, &ctx->vt_aux, &ctx->scratch, &ctx->scene};
   for (DevBuf *b : bufs)
     if (b->p) ip_dfree(ctx, b->p);
   ip_cache_release(ctx);
@@ -397,8 +403,8 @@ void ip_destroy(ip_ctx *ctx) {
   if (ctx->host_stage) (void)hipHostFree(ctx->host_stage);
   for (void *q : ctx->dev_stage)
     if (q) (void)hipFree(q);
-  if (ctx->ev0) (void)hipEventDestroy(ctx->ev0);
-  if (ctx->ev1) (void)hipEventDestroy(ctx->ev1);
+  for (hipEvent_t ev : {ctx->ev0, ctx->ev1, ctx->ctr_ev[0], ctx->ctr_ev[1]})
+    if (ev) (void)hipEventDestroy(ev);
   delete ctx;
 }
 

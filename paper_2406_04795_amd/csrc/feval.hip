@@ -42,6 +42,10 @@ namespace {
 // (about 115 ns per 64-byte record at S = 2000, whatever the unrolling,
 // against the 17 ns of its arithmetic).
 
+__device__ __forceinline__ void put_stamp(unsigned long long *stamp) {
+  if (stamp && blockIdx.x == 0 && threadIdx.x == 0) *stamp = wall_clock64();
+}
+
 // Vertex i of the call: its destination and coordinates.
 template <int D, int MODE>
 __device__ __forceinline__ uint64_t load_vertex(const LatDev &L, const uint32_t *__restrict__ list, uint64_t i,
@@ -71,7 +75,8 @@ __global__ __launch_bounds__(512) void feval64_split_kernel(FDev F, LatDev L, co
                                                             uint64_t n, const unsigned long long *n_dev,
                                                             const uint64_t *__restrict__ keys,
                                                             const int32_t *__restrict__ vraw,
-                                                            double *__restrict__ out) {
+                                                            double *__restrict__ out, unsigned long long *stamp) {
+  put_stamp(stamp);
   constexpr int T = IP_COL_PAD, NW = 7, G = NW * V, LD = G | 1;
   constexpr uint64_t S4 = MODE == 0 ? 4 : 1;
   __shared__ double term[2][T * LD];
@@ -167,7 +172,9 @@ __global__ __launch_bounds__(512) void feval64_split_kernel(FDev F, LatDev L, co
 template <int D, int P, int R, int U, int MODE>
 __global__ __launch_bounds__(256, (P < 0 || R < 4) ? 4 : 2) void feval64_tile_kernel(
     FDev F, LatDev L, const uint32_t *__restrict__ list, uint64_t n, const unsigned long long *n_dev,
-    const uint64_t *__restrict__ keys, const int32_t *__restrict__ vraw, double *__restrict__ out) {
+    const uint64_t *__restrict__ keys, const int32_t *__restrict__ vraw, double *__restrict__ out,
+    unsigned long long *stamp) {
+  put_stamp(stamp);
   constexpr int T = 64;
   constexpr uint64_t S4 = MODE == 0 ? 4 : 1;
   __shared__ __align__(16) double tile[2][T * 8];
@@ -238,12 +245,25 @@ __global__ __launch_bounds__(256, (P < 0 || R < 4) ? 4 : 2) void feval64_tile_ke
 // lane, 438 with two).
 constexpr uint64_t kSplitMax = 16384;
 
+// One call of the canonical sum: see the MODEs above and launch_feval64.
+struct Eval64 {
+  hipStream_t st;
+  const uint32_t *list;
+  uint64_t n;
+  const unsigned long long *n_dev;
+  const uint64_t *keys;
+  const int32_t *vraw;
+  double *out;
+  uint64_t hint;  // items the launch is shaped for
+  unsigned long long *stamp;
+};
+
 template <int D, int P, int MODE>
-void launch64(hipStream_t st, const FDev &F, const LatDev &L, const uint32_t *list, uint64_t n,
-              const unsigned long long *n_dev, const uint64_t *keys, const int32_t *vraw, double *out) {
-#define IP_L64(KERNEL, PER, BLOCK)                                                                                   \
-  hipLaunchKernelGGL(KERNEL, dim3((unsigned)std::min<uint64_t>((n + (PER) - 1) / (PER), 65536)), dim3(BLOCK), 0, st, \
-                     F, L, list, n, n_dev, keys, vraw, out)
+void launch64(const Eval64 &e, const FDev &F, const LatDev &L) {
+  const uint64_t n = e.hint;
+#define IP_L64(KERNEL, PER, BLOCK)                                                                                  \
+  hipLaunchKernelGGL(KERNEL, dim3((unsigned)std::min<uint64_t>((n + (PER) - 1) / (PER), 65536)), dim3(BLOCK), 0, e.st, \
+                     F, L, e.list, e.n, e.n_dev, e.keys, e.vraw, e.out, e.stamp)
   if (n <= kSplitMax) {
     IP_L64((feval64_split_kernel<D, P, MODE, 4>), 28, 512);
   } else if (P < 0) {
@@ -259,34 +279,33 @@ void launch64(hipStream_t st, const FDev &F, const LatDev &L, const uint32_t *li
 }
 
 template <int D, int MODE>
-void launch64_p(hipStream_t st, const FDev &F, const LatDev &L, const uint32_t *list, uint64_t n,
-                const unsigned long long *n_dev, const uint64_t *keys, const int32_t *vraw, double *out) {
+void launch64_p(const Eval64 &e, const FDev &F, const LatDev &L) {
   if (F.kernel == IP_KERNEL_RBF) {
-    launch64<D, -1, MODE>(st, F, L, list, n, n_dev, keys, vraw, out);
+    launch64<D, -1, MODE>(e, F, L);
     return;
   }
   switch (F.p) {
-    case 1: launch64<D, 1, MODE>(st, F, L, list, n, n_dev, keys, vraw, out); break;
-    case 2: launch64<D, 2, MODE>(st, F, L, list, n, n_dev, keys, vraw, out); break;
-    case 3: launch64<D, 3, MODE>(st, F, L, list, n, n_dev, keys, vraw, out); break;
-    case 4: launch64<D, 4, MODE>(st, F, L, list, n, n_dev, keys, vraw, out); break;
-    default: launch64<D, 0, MODE>(st, F, L, list, n, n_dev, keys, vraw, out); break;
+    case 1: launch64<D, 1, MODE>(e, F, L); break;
+    case 2: launch64<D, 2, MODE>(e, F, L); break;
+    case 3: launch64<D, 3, MODE>(e, F, L); break;
+    case 4: launch64<D, 4, MODE>(e, F, L); break;
+    default: launch64<D, 0, MODE>(e, F, L); break;
   }
 }
 
 template <int MODE>
 int dispatch64(ip_ctx *ctx, const FDev &F, const LatDev &L, const uint32_t *list, uint64_t n,
                const uint64_t *keys, const int32_t *vraw, double *out,
-               const unsigned long long *n_dev = nullptr) {
+               const unsigned long long *n_dev = nullptr, uint64_t hint = 0, unsigned long long *stamp = nullptr) {
   if (n == 0) return IP_OK;
-  hipStream_t st = ctx->stream;
+  const Eval64 e{ctx->stream, list, n, n_dev, keys, vraw, out, hint ? std::min(hint, n) : n, stamp};
   switch (L.d) {
-    case 2: launch64_p<2, MODE>(st, F, L, list, n, n_dev, keys, vraw, out); break;
-    case 3: launch64_p<3, MODE>(st, F, L, list, n, n_dev, keys, vraw, out); break;
-    case 4: launch64_p<4, MODE>(st, F, L, list, n, n_dev, keys, vraw, out); break;
-    case 5: launch64_p<5, MODE>(st, F, L, list, n, n_dev, keys, vraw, out); break;
-    case 6: launch64_p<6, MODE>(st, F, L, list, n, n_dev, keys, vraw, out); break;
-    case 7: launch64_p<7, MODE>(st, F, L, list, n, n_dev, keys, vraw, out); break;
+    case 2: launch64_p<2, MODE>(e, F, L); break;
+    case 3: launch64_p<3, MODE>(e, F, L); break;
+    case 4: launch64_p<4, MODE>(e, F, L); break;
+    case 5: launch64_p<5, MODE>(e, F, L); break;
+    case 6: launch64_p<6, MODE>(e, F, L); break;
+    case 7: launch64_p<7, MODE>(e, F, L); break;
     default: return ip_fail(ctx, IP_EINVAL, "dimension out of range");
   }
   IP_TRY_HIP(ctx, hipGetLastError());
@@ -306,10 +325,12 @@ int dispatch64(ip_ctx *ctx, const FDev &F, const LatDev &L, const uint32_t *list
 // resp. index) for the canonical FP64 kernel.
 template <int D, int P, int MODE>
 __global__ __launch_bounds__(256) void feval32_kernel(PolyDev Q, LatDev L, const uint32_t *__restrict__ list,
-                                                      uint64_t n, VEnt *vt, float *vb,
-                                                      const int32_t *__restrict__ vraw, double *out, double *bout,
-                                                      uint32_t *fb, unsigned long long *fb_ctr,
-                                                      unsigned long long *c64_ctr) {
+                                                      uint64_t n, const unsigned long long *n_dev, VEnt *vt,
+                                                      float *vb, const int32_t *__restrict__ vraw, double *out,
+                                                      double *bout, uint32_t *fb, unsigned long long *fb_ctr,
+                                                      unsigned long long *c64_ctr, unsigned long long *stamp) {
+  put_stamp(stamp);
+  if (n_dev) n = (uint64_t)*n_dev < n ? (uint64_t)*n_dev : n;
   constexpr int kStage = 128;
   __shared__ uint32_t st[4][kStage];
   const int wib = threadIdx.x >> 6;
@@ -463,15 +484,16 @@ __global__ void set_vb_kernel(const uint32_t *list, uint64_t n, float *vb, float
 }
 
 template <int D, int MODE>
-void launch32_p(hipStream_t st, const PolyDev &Q, const LatDev &L, const uint32_t *list, uint64_t n, VEnt *vt,
-                float *vb, const int32_t *vraw, double *out, double *bout, uint32_t *fb, unsigned long long *fb_ctr,
-                unsigned long long *c64) {
-  uint64_t blocks = (n + 255) / 256;
+void launch32_p(hipStream_t st, const PolyDev &Q, const LatDev &L, const uint32_t *list, uint64_t n,
+                const unsigned long long *n_dev, uint64_t hint, VEnt *vt, float *vb, const int32_t *vraw, double *out,
+                double *bout, uint32_t *fb, unsigned long long *fb_ctr, unsigned long long *c64,
+                unsigned long long *stamp) {
+  uint64_t blocks = (hint + 255) / 256;
   if (blocks > 65536) blocks = 65536;
   if (blocks == 0) return;
 #define IP_L32(PP)                                                                                               \
-  hipLaunchKernelGGL((feval32_kernel<D, PP, MODE>), dim3((unsigned)blocks), dim3(256), 0, st, Q, L, list, n, vt, vb, \
-                     vraw, out, bout, fb, fb_ctr, c64)
+  hipLaunchKernelGGL((feval32_kernel<D, PP, MODE>), dim3((unsigned)blocks), dim3(256), 0, st, Q, L, list, n, n_dev,    \
+                     vt, vb, vraw, out, bout, fb, fb_ctr, c64, stamp)
   switch (Q.p) {
     case 1: IP_L32(1); break;
     case 2: IP_L32(2); break;
@@ -485,17 +507,18 @@ void launch32_p(hipStream_t st, const PolyDev &Q, const LatDev &L, const uint32_
 template <int MODE>
 int dispatch32(ip_ctx *ctx, const PolyDev &Q, const LatDev &L, const uint32_t *list, uint64_t n, VEnt *vt, float *vb,
                const int32_t *vraw, double *out, double *bout, uint32_t *fb, unsigned long long *fb_ctr,
-               unsigned long long *c64 = nullptr) {
+               unsigned long long *c64, const unsigned long long *n_dev, uint64_t hint, unsigned long long *stamp) {
   if (!c64) c64 = &ctx->ctr_dev->n_cert64;
   if (n == 0) return IP_OK;
+  hint = hint ? std::min(hint, n) : n;
   hipStream_t st = ctx->stream;
   switch (L.d) {
-    case 2: launch32_p<2, MODE>(st, Q, L, list, n, vt, vb, vraw, out, bout, fb, fb_ctr, c64); break;
-    case 3: launch32_p<3, MODE>(st, Q, L, list, n, vt, vb, vraw, out, bout, fb, fb_ctr, c64); break;
-    case 4: launch32_p<4, MODE>(st, Q, L, list, n, vt, vb, vraw, out, bout, fb, fb_ctr, c64); break;
-    case 5: launch32_p<5, MODE>(st, Q, L, list, n, vt, vb, vraw, out, bout, fb, fb_ctr, c64); break;
-    case 6: launch32_p<6, MODE>(st, Q, L, list, n, vt, vb, vraw, out, bout, fb, fb_ctr, c64); break;
-    case 7: launch32_p<7, MODE>(st, Q, L, list, n, vt, vb, vraw, out, bout, fb, fb_ctr, c64); break;
+    case 2: launch32_p<2, MODE>(st, Q, L, list, n, n_dev, hint, vt, vb, vraw, out, bout, fb, fb_ctr, c64, stamp); break;
+    case 3: launch32_p<3, MODE>(st, Q, L, list, n, n_dev, hint, vt, vb, vraw, out, bout, fb, fb_ctr, c64, stamp); break;
+    case 4: launch32_p<4, MODE>(st, Q, L, list, n, n_dev, hint, vt, vb, vraw, out, bout, fb, fb_ctr, c64, stamp); break;
+    case 5: launch32_p<5, MODE>(st, Q, L, list, n, n_dev, hint, vt, vb, vraw, out, bout, fb, fb_ctr, c64, stamp); break;
+    case 6: launch32_p<6, MODE>(st, Q, L, list, n, n_dev, hint, vt, vb, vraw, out, bout, fb, fb_ctr, c64, stamp); break;
+    case 7: launch32_p<7, MODE>(st, Q, L, list, n, n_dev, hint, vt, vb, vraw, out, bout, fb, fb_ctr, c64, stamp); break;
     default: return ip_fail(ctx, IP_EINVAL, "dimension out of range");
   }
   IP_TRY_HIP(ctx, hipGetLastError());
@@ -542,10 +565,11 @@ int dispatch32_rbf(ip_ctx *ctx, const RbfDev &Q, const LatDev &L, const uint32_t
 template <int MODE>
 int dispatch32_p(ip_ctx *ctx, const ip_problem *p, const LatDev &L, const uint32_t *list, uint64_t n, VEnt *vt,
                  float *vb, const int32_t *vraw, double *out, double *bout, uint32_t *fb,
-                 unsigned long long *fb_ctr, unsigned long long *c64 = nullptr) {
+                 unsigned long long *fb_ctr, unsigned long long *c64 = nullptr,
+                 const unsigned long long *n_dev = nullptr, uint64_t hint = 0, unsigned long long *stamp = nullptr) {
   if (p->f.kernel == IP_KERNEL_RBF)
     return dispatch32_rbf<MODE>(ctx, p->rbf, L, list, n, vt, vb, vraw, out, bout, fb, fb_ctr);
-  return dispatch32<MODE>(ctx, p->poly, L, list, n, vt, vb, vraw, out, bout, fb, fb_ctr, c64);
+  return dispatch32<MODE>(ctx, p->poly, L, list, n, vt, vb, vraw, out, bout, fb, fb_ctr, c64, n_dev, hint, stamp);
 }
 
 // One support vector's factors for f and its gradient at x (the order of
@@ -878,14 +902,9 @@ int ip_feval_noalloc_impl(ip_ctx *ctx, const ip_problem *p, const int32_t *v_dev
   return dispatch64<2>(ctx, p->f, p->fine, fbl, (uint64_t)n, nullptr, v_dev, f_dev, hdr);
 }
 
-int launch_feval64(ip_ctx *ctx, const ip_problem *p, const LatDev &L, const uint32_t *list, uint64_t n_list,
-                   VEnt *vt) {
-  return dispatch64<0>(ctx, p->f, L, list, n_list, (const uint64_t *)vt, nullptr, (double *)vt + 1);
-}
-
-int launch_feval64_dev(ip_ctx *ctx, const ip_problem *p, const LatDev &L, const uint32_t *list, uint64_t n_max,
-                       const unsigned long long *n_dev, VEnt *vt) {
-  return dispatch64<0>(ctx, p->f, L, list, n_max, (const uint64_t *)vt, nullptr, (double *)vt + 1, n_dev);
+int launch_feval64(ip_ctx *ctx, const ip_problem *p, const LatDev &L, const uint32_t *list, uint64_t n, VEnt *vt,
+                   const unsigned long long *n_dev, uint64_t hint, unsigned long long *stamp) {
+  return dispatch64<0>(ctx, p->f, L, list, n, (const uint64_t *)vt, nullptr, (double *)vt + 1, n_dev, hint, stamp);
 }
 
 int launch_feval64_raw(ip_ctx *ctx, const ip_problem *p, const LatDev &L, const int32_t *v, uint64_t n,
@@ -893,9 +912,12 @@ int launch_feval64_raw(ip_ctx *ctx, const ip_problem *p, const LatDev &L, const 
   return dispatch64<1>(ctx, p->f, L, nullptr, n, nullptr, v, out);
 }
 
-int launch_feval32(ip_ctx *ctx, const ip_problem *p, const LatDev &L, const uint32_t *list, uint64_t n_list,
-                   VEnt *vt, float *vb, uint32_t *fb, unsigned long long *fb_ctr) {
-  return dispatch32_p<0>(ctx, p, L, list, n_list, vt, vb, nullptr, nullptr, nullptr, fb, fb_ctr);
+// (a vertex table holds a polynomial f in this mode: RBF traces run in FP64)
+int launch_feval32(ip_ctx *ctx, const ip_problem *p, const LatDev &L, const uint32_t *list, uint64_t n, VEnt *vt,
+                   float *vb, uint32_t *fb, unsigned long long *fb_ctr, const unsigned long long *n_dev, uint64_t hint,
+                   unsigned long long *stamp) {
+  return dispatch32<0>(ctx, p->poly, L, list, n, vt, vb, nullptr, nullptr, nullptr, fb, fb_ctr, nullptr, n_dev, hint,
+                       stamp);
 }
 
 int launch_set_vb(ip_ctx *ctx, const uint32_t *list, uint64_t n, float *vb, float v) {

@@ -185,9 +185,12 @@ struct PolyDev {
   double K32n;  // nested FP32 evaluation: |f32 - F| <= K32n * sum |c_m| |x^m| + E0
 };
 
+// Atomics on one address cost about 12 ns each whoever issues them, so sums
+// that many blocks add to are spread over lines.
+#define IP_COF_SLOTS 16
+
 struct Counters {
   unsigned long long n_eval;     // eval-list length (reset per pass)
-  unsigned long long vt_count;   // vertices inserted (total)
   unsigned long long n_out;      // output-list length (== edges in ET)
   unsigned long long n_cof;      // cofaces expanded in the current level
   unsigned long long n_fb;       // FP64 fallback list length
@@ -200,7 +203,22 @@ struct Counters {
   unsigned long long n_shared;   // intersecting template edges sent to the edge set
   unsigned int vt_fail;          // vertex-table insert found the table full
   unsigned int et_fail;          // edge-table insert found the table full
+  // breadth-first search (trace.hip, "Level chain"); the two-entry fields go
+  // by the level's parity, lv by the level modulo 4
+  unsigned long long lv[4];      // first traced edge of a level
+  unsigned long long n_ev[2];    // vertices the level added (its eval list)
+  unsigned long long n_cofl[2][IP_COF_SLOTS * 8];  // cofaces of the level's edges: partial sums, a cache line each
+  unsigned long long vt_cnt[2];  // vertices before the level
+  unsigned long long n_held;     // eval-list length of a level that stopped
+  unsigned long long cof_total, levels, fb_total, c64_total;
+  unsigned long long t_mark, t_eval;      // device clock at the last pass, at the level's evaluation
+  unsigned long long ticks_expand, ticks_eval;
+  unsigned int stop, stop_level;          // IP_STOP_*, and the level it stopped at
 };
+
+// Why the level chain stopped: the frontier is empty; the coface slots or
+// the traced edges need a larger buffer; the vertex table needs growing.
+enum { IP_STOP_DONE = 1, IP_STOP_CSLOT = 2, IP_STOP_OUT = 4, IP_STOP_VT = 8 };
 
 // ---------------------------------------------------------------------------
 // Device helpers
@@ -400,6 +418,26 @@ __device__ __forceinline__ void stage_flush(T *st, int &n, W writer, unsigned lo
   for (int i = lane; i < n; i += 64) writer(base + (unsigned long long)i, st[i]);
   wave_lds_sync();
   n = 0;
+}
+
+// stage_flush for the last time in a kernel, by the whole block (every thread
+// must call it): the waves' entries go out together, with one atomicAdd.
+template <typename T, typename W>
+__device__ __forceinline__ void stage_flush_block(const T *st, int n, W writer, unsigned long long *ctr) {
+  __shared__ uint32_t cnt[16];  // blocks of up to 16 waves
+  __shared__ unsigned long long base;
+  const int wib = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+  if (lane == 0) cnt[wib] = (uint32_t)n;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t t = 0;
+    for (int w = 0; w < nw; ++w) t += cnt[w];
+    base = t ? atomicAdd(ctr, (unsigned long long)t) : 0ull;
+  }
+  __syncthreads();
+  unsigned long long o = base;
+  for (int w = 0; w < wib; ++w) o += cnt[w];
+  for (int i = lane; i < n; i += 64) writer(o + (unsigned long long)i, st[i]);
 }
 
 template <int STAGE, typename T, typename W>
@@ -629,9 +667,10 @@ struct DevCache {
 };
 
 // Buffers of one vertex table: its VEnt entries, the pending-evaluation
-// list, and in FP32 mode the per-slot bounds and the FP64 fallback list.
+// list, in FP32 mode the per-slot bounds and the FP64 fallback list, and the
+// edges traced through it.
 struct VtBufs {
-  DevBuf keys, eval, vals, fb;
+  DevBuf keys, eval, vals, fb, out;
 };
 
 struct ip_ctx {
@@ -639,7 +678,9 @@ struct ip_ctx {
   hipStream_t stream = nullptr;
   std::string err;
   Counters *ctr_dev = nullptr;
-  Counters *ctr_host = nullptr;  // pinned
+  Counters *ctr_host = nullptr;  // pinned: three, the second and third for the level chain
+  hipEvent_t ctr_ev[2] = {nullptr, nullptr};  // their copies have landed
+  double ticks_per_ms = 1e5;     // device clock (wall_clock64)
   // persistent workspace (grow-only): the fine-lattice vertex table (direct
   // trace, FP64 batch subdivision) and the coarse-lattice one (batch mode),
   // kept apart so that neither is handed to the other and reallocated
@@ -757,20 +798,21 @@ int ip_interleave_free(ip_ctx *ctx, const ip_cells *c, double *out_dev);
 int ip_free_points_to_host(ip_ctx *ctx, const ip_cells *c, double *host);
 
 // f evaluation of the vertices listed in `list` (slots of the vertex table);
-// results go into vt_vals[slot].  Defined in feval.hip.
+// results go into vt[slot].f.  Defined in feval.hip.  n_dev (may be NULL):
+// the count is *n_dev, written by an earlier kernel on the stream, at most
+// n; the launch is then shaped for `hint` items (any hint is right, a close
+// one fast).  stamp (may be NULL) receives the device clock as the first
+// kernel starts.
 // FP32 certified evaluation of the listed slots: vt[slot].f and vb[slot]
 // (the bound, or -1 when the vertex needs FP64); unsettled slots are
 // appended to fb (counter fb_ctr).  Then set vb[list[i]] = v.
-int launch_feval32(ip_ctx *ctx, const ip_problem *p, const LatDev &L, const uint32_t *list, uint64_t n_list,
-                   VEnt *vt, float *vb, uint32_t *fb, unsigned long long *fb_ctr);
+int launch_feval32(ip_ctx *ctx, const ip_problem *p, const LatDev &L, const uint32_t *list, uint64_t n, VEnt *vt,
+                   float *vb, uint32_t *fb, unsigned long long *fb_ctr, const unsigned long long *n_dev = nullptr,
+                   uint64_t hint = 0, unsigned long long *stamp = nullptr);
 int launch_set_vb(ip_ctx *ctx, const uint32_t *list, uint64_t n, float *vb, float v);
-// vt: vertex-table entries; the result goes into vt[slot].f.
-int launch_feval64(ip_ctx *ctx, const ip_problem *p, const LatDev &L, const uint32_t *list,
-                   uint64_t n_list, VEnt *vt);
-// The same for list[0 .. *n_dev) with *n_dev (written on the device by an
-// earlier kernel) at most n_max: no host read of the count.
-int launch_feval64_dev(ip_ctx *ctx, const ip_problem *p, const LatDev &L, const uint32_t *list, uint64_t n_max,
-                       const unsigned long long *n_dev, VEnt *vt);
+int launch_feval64(ip_ctx *ctx, const ip_problem *p, const LatDev &L, const uint32_t *list, uint64_t n, VEnt *vt,
+                   const unsigned long long *n_dev = nullptr, uint64_t hint = 0,
+                   unsigned long long *stamp = nullptr);
 // Canonical FP64 f at n raw vertices (int32, row-major n x d) into out[i].
 int launch_feval64_raw(ip_ctx *ctx, const ip_problem *p, const LatDev &L, const int32_t *v, uint64_t n,
                        double *out);

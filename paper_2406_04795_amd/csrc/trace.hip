@@ -14,8 +14,9 @@
 // frontier edges into VT, slots into CSL, new vertices listed), f evaluation
 // of the new vertices, pass 2 (per coface: the other sign-changing edge is
 // marked in its smaller endpoint's entry; first markers append to OUT).
-// The host reads a small counter block after each pass; table growth rehashes
-// VT, re-points OUT's slots and replays pass 1, which is idempotent.
+// The levels run as a chain on the stream: every pass takes its range from
+// the device counters, and the host queues some levels ahead of the counters
+// it reads ("Level chain" below).
 #include <algorithm>
 #include <cmath>
 #include <cstddef>
@@ -29,6 +30,7 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr int kStage = 128;  // per-wave staged append entries
+constexpr int kExpand = 1024;  // threads of an expand_kernel block
 
 struct OutRec {
   uint64_t key;
@@ -52,6 +54,8 @@ __global__ void fill_vent_kernel(VEnt *p, uint64_t n) {
 }
 
 __global__ void zero_counter_kernel(unsigned long long *p) { *p = 0ull; }
+
+__global__ void set_counter_kernel(unsigned long long *p, unsigned long long v) { *p = v; }
 
 template <int D>
 __device__ void locate(const LatDev &L, const double *y, int32_t *v, int32_t *w) {
@@ -112,9 +116,10 @@ __global__ void seed_vertices_kernel(LatDev L, const double *seeds, int64_t ns, 
     uint64_t slot;
     int r = vt_insert(vt, vt_mask, vpack<D>(L, v), &slot);
     if (r == 1) {
-      unsigned long long idx = atomicAdd(&ctr->n_eval, 1ull);
+      // listed as the vertices of the level before level 0
+      unsigned long long idx = atomicAdd(&ctr->n_ev[1], 1ull);
       eval_list[idx] = (uint32_t)slot;
-      atomicAdd(&ctr->vt_count, 1ull);
+      atomicAdd(&ctr->vt_cnt[0], 1ull);
     } else if (r < 0) {
       atomicOr(&ctr->vt_fail, 1u);
     }
@@ -160,32 +165,105 @@ __global__ void seed_edges_kernel(LatDev L, const double *seeds, int64_t ns, VEn
 }
 
 // Frontier expansion (Sec. V-A "find all cofaces" / "find all interesting
-// cofaces' edges" / "hash all edges").  Each wave takes 64 frontier edges,
+// cofaces' edges" / "hash all edges").  Each wave takes c frontier edges,
 // prefix-sums their coface counts and walks the flattened (edge, coface)
 // list 64 at a time, so lanes stay busy whatever the mix of edge classes.
 //   EDGES = false: pass 1, third vertices into VT and CSL.
 //   EDGES = true : pass 2, sign test and marking of the new edge.
+// A frontier is a few thousand edges at most levels and its passes are bound
+// by the latency of their probes, so c is what gives every wave of the grid
+// some edges, at most 64: with 64 always, 9000 edges in d = 5 kept 141 waves
+// busy for 17 rounds each (57 and 40 us).  Blocks are of 16 waves because
+// every block ends with an atomic on the append counter, 12 ns each in turn.
+//
+// Level chain.  Pass 1, evaluation and pass 2 of level l, l + 1, ... are
+// queued without a look at the counters.  lv[l] and lv[l + 1] bound the
+// frontier of level l in OUT; pass 1 of level l writes lv[l + 1] (no edge is
+// appended then).  Whether the level can go on (buffers, table load) every
+// block decides from values that no block changes meanwhile; when it cannot,
+// block 0 sets `stop`, the passes queued behind do nothing, and the host,
+// which reads the counters some levels late, mends the cause and queues
+// level `stop_level` again.  Pass 1 is idempotent.
 template <int D, bool EDGES>
-__global__ __launch_bounds__(kBlock) void expand_kernel(LatDev L, OutRec *out, uint64_t lo, uint64_t hi, VEnt *vt,
-                                                        uint64_t vt_mask, uint32_t *cslot, uint32_t *eval_list,
-                                                        Counters *ctr) {
+__global__ __launch_bounds__(kExpand) void expand_kernel(LatDev L, OutRec *out, uint64_t out_cap, VEnt *vt,
+                                                        uint64_t vt_mask, uint32_t *cslot, uint64_t cslot_cap,
+                                                        uint32_t *eval_list, Counters *ctr, uint32_t level) {
   constexpr int MAXC = (1 << D) - 2;  // most 2-cofaces an edge can have
-  __shared__ OutRec st_out[EDGES ? kBlock / 64 : 1][EDGES ? kStage : 1];
-  __shared__ uint32_t st_ev[EDGES ? 1 : kBlock / 64][EDGES ? 1 : kStage];
+  __shared__ OutRec st_out[EDGES ? kExpand / 64 : 1][EDGES ? kStage : 1];
+  __shared__ uint32_t st_ev[EDGES ? 1 : kExpand / 64][EDGES ? 1 : kStage];
+  __shared__ unsigned long long wcof[kExpand / 64];
   const int lane = threadIdx.x & 63;
   const int wib = threadIdx.x >> 6;
   const uint64_t wave = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const uint64_t n_waves = ((uint64_t)gridDim.x * blockDim.x) >> 6;
-  const uint64_t nchunks = (hi - lo + 63) >> 6;
+  const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+  const uint32_t par = level & 1u, nxt = par ^ 1u;
+  const bool stopped = ctr->stop != 0u;
+  const uint64_t lo = ctr->lv[level & 3u];
+  const uint64_t hi = EDGES ? ctr->lv[(level + 1) & 3u] : ctr->n_out;
+  uint32_t halt = 0;
+  if (!EDGES) {
+    if (hi == lo)
+      halt = IP_STOP_DONE;
+    else if ((hi - lo) * MAXC > cslot_cap)
+      halt = IP_STOP_CSLOT;
+    if (first) {
+      const unsigned long long now = wall_clock64();
+      if (stopped) {
+        // nothing for the evaluations queued behind the level that stopped
+        if (level == ctr->stop_level + 1) {
+          ctr->n_held = ctr->n_ev[nxt];
+          ctr->n_ev[0] = ctr->n_ev[1] = 0;
+        }
+      } else if (halt) {
+        ctr->stop = halt;
+        ctr->stop_level = level;
+      } else {
+        if (level) ctr->ticks_expand += now - ctr->t_mark;
+        ctr->t_mark = now;
+        ctr->lv[(level + 1) & 3u] = hi;
+        ctr->n_fb = 0;
+        ctr->n_cert64 = 0;
+      }
+    }
+  } else {
+    const unsigned long long nv = ctr->vt_cnt[par] + ctr->n_ev[par];
+    unsigned long long nc = 0;
+    for (int k = 0; k < IP_COF_SLOTS; ++k) nc += ctr->n_cofl[par][k * 8];
+    if (ctr->vt_fail || nv * 2 > vt_mask + 1) halt |= IP_STOP_VT;
+    if (hi + nc + 1 > out_cap) halt |= IP_STOP_OUT;
+    if (first && !stopped) {
+      if (halt) {
+        ctr->stop = halt;
+        ctr->stop_level = level;
+      } else {
+        const unsigned long long now = wall_clock64();
+        ctr->ticks_expand += ctr->t_eval - ctr->t_mark;
+        ctr->ticks_eval += now - ctr->t_eval;
+        ctr->t_mark = now;
+        ctr->vt_cnt[nxt] = nv;
+        ctr->n_ev[nxt] = 0;
+        for (int k = 0; k < IP_COF_SLOTS; ++k) ctr->n_cofl[nxt][k * 8] = 0;
+        ctr->cof_total += nc;
+        ctr->levels += 1;
+        ctr->fb_total += ctr->n_fb;
+        ctr->c64_total += ctr->n_cert64;
+      }
+    }
+  }
+  if (stopped || halt) return;  // the same in every block
+  const uint64_t share = (hi - lo + n_waves - 1) / n_waves;
+  const uint64_t c = share > 64 ? 64 : share;
+  const uint64_t nchunks = (hi - lo + c - 1) / c;
   int sn = 0;
-  unsigned long long cof_acc = 0, new_acc = 0;
+  unsigned long long cof_acc = 0;
   auto put_out = [&](unsigned long long pos, const OutRec &r) { out[pos] = r; };
   auto put_ev = [&](unsigned long long pos, uint32_t s) { eval_list[pos] = s; };
   for (uint64_t ch = wave; ch < nchunks; ch += n_waves) {
-    const uint64_t ei = lo + ch * 64 + lane;
+    const uint64_t ei = lo + ch * c + lane;
     uint64_t e = 0, es = 0;
     int cnt = 0;
-    if (ei < hi) {
+    if (lane < (int)c && ei < hi) {
       e = out[ei].key;
       if (EDGES) es = out[ei].slots;
       cnt = n_cofaces2<D>((uint32_t)((e & ~IP_SIGN_BIT) >> (D * L.B)) & ((1u << D) - 1u));
@@ -211,21 +289,21 @@ __global__ __launch_bounds__(kBlock) void expand_kernel(LatDev L, OutRec *out, u
       }
       const uint64_t me = shfl64(e, j);
       const int r = idx - __shfl(excl, j, 64);
-      const uint64_t crow = (ch * 64 + (uint64_t)j) * MAXC + (uint64_t)r;
+      const uint64_t crow = (ch * c + (uint64_t)j) * MAXC + (uint64_t)r;
       if (!EDGES) {
         bool is_new = false;
         uint32_t slot32 = 0;
         if (valid) {
-          int32_t v[D], c[D];
+          int32_t v[D], tv[D];
           uint32_t R;
           eunpack<D>(L, me, v, &R);
-          coface_vertex<D>(v, R, r, c);
+          coface_vertex<D>(v, R, r, tv);
           double x[D];
-          lat_coords<D>(L, c, x);
+          lat_coords<D>(L, tv, x);
           uint32_t cs = 0xffffffffu;
           if (lat_in_box<D>(L, x)) {
             uint64_t slot;
-            int ins = vt_insert(vt, vt_mask, vpack<D>(L, c), &slot);
+            int ins = vt_insert(vt, vt_mask, vpack<D>(L, tv), &slot);
             if (ins >= 0) {
               cs = (uint32_t)slot;
               is_new = ins == 1;
@@ -236,8 +314,7 @@ __global__ __launch_bounds__(kBlock) void expand_kernel(LatDev L, OutRec *out, u
           }
           cslot[crow] = cs;
         }
-        new_acc += (unsigned long long)__popcll(__ballot(is_new));
-        stage_put<kStage>(st_ev[wib], sn, is_new, slot32, put_ev, &ctr->n_eval);
+        stage_put<kStage>(st_ev[wib], sn, is_new, slot32, put_ev, &ctr->n_ev[par]);
       } else {
         const uint64_t mslots = shfl64(es, j);
         bool is_new = false;
@@ -247,10 +324,10 @@ __global__ __launch_bounds__(kBlock) void expand_kernel(LatDev L, OutRec *out, u
           if (cs != 0xffffffffu) {
             const bool sc = !(vt[cs].f < 0.0);
             const bool sa = (me & IP_SIGN_BIT) != 0;
-            int32_t v[D], c[D];
+            int32_t v[D], tv[D];
             uint32_t R;
             eunpack<D>(L, me, v, &R);
-            coface_vertex<D>(v, R, r, c);
+            coface_vertex<D>(v, R, r, tv);
             // exactly one of (a,c), (b,c) changes sign: the one whose other
             // end has the sign c does not have (Sec. V-A, two edges of a
             // triangle cross the manifold)
@@ -270,7 +347,7 @@ __global__ __launch_bounds__(kBlock) void expand_kernel(LatDev L, OutRec *out, u
             }
             int32_t vm[D];
             uint32_t mask;
-            const bool other_min = edge_canon<D>(other, c, vm, &mask);
+            const bool other_min = edge_canon<D>(other, tv, vm, &mask);
             const uint64_t smin = other_min ? oslot : (uint64_t)cs, smax = other_min ? (uint64_t)cs : oslot;
             if (mark_edge(vt, smin, mask)) {
               is_new = true;
@@ -283,13 +360,17 @@ __global__ __launch_bounds__(kBlock) void expand_kernel(LatDev L, OutRec *out, u
       }
     }
   }
-  if (EDGES)
-    stage_flush(st_out[wib], sn, put_out, &ctr->n_out);
-  else
-    stage_flush(st_ev[wib], sn, put_ev, &ctr->n_eval);
-  if (!EDGES && lane == 0) {
-    if (cof_acc) atomicAdd(&ctr->n_cof, cof_acc);
-    if (new_acc) atomicAdd(&ctr->vt_count, new_acc);
+  // one atomic per block and counter
+  if (EDGES) {
+    stage_flush_block(st_out[wib], sn, put_out, &ctr->n_out);
+  } else {
+    if (lane == 0) wcof[wib] = cof_acc;
+    stage_flush_block(st_ev[wib], sn, put_ev, &ctr->n_ev[par]);
+    if (threadIdx.x == 0) {
+      unsigned long long t = 0;
+      for (int w = 0; w < kExpand / 64; ++w) t += wcof[w];
+      if (t) atomicAdd(&ctr->n_cofl[par][(blockIdx.x % IP_COF_SLOTS) * 8], t);
+    }
   }
 }
 
@@ -397,16 +478,6 @@ __global__ void vt_rehash_kernel(const VEnt *old, const float *ovb, uint64_t oca
   }
 }
 
-__global__ void vt_scan_pending_kernel(const VEnt *vt, uint64_t cap, uint32_t *list, Counters *ctr) {
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < cap; i += (uint64_t)gridDim.x * blockDim.x) {
-    if (vt[i].key == IP_EMPTY_KEY) continue;
-    if ((uint64_t)__double_as_longlong(vt[i].f) == IP_UNEVAL_BITS) {
-      unsigned long long idx = atomicAdd(&ctr->n_eval, 1ull);
-      list[idx] = (uint32_t)i;
-    }
-  }
-}
-
 // After VT moved, point the traced edges at the new slots of their ends.
 template <int D>
 __global__ void remap_slots_kernel(LatDev L, OutRec *out, uint64_t n, const VEnt *vt, uint64_t vt_mask,
@@ -494,6 +565,7 @@ struct Run {
   OutRec *out = nullptr;
   uint64_t out_cap = 0;
   uint32_t *cslot = nullptr;
+  uint64_t cslot_cap = 0;
   int64_t regrows = 0;
   bool cert = false;      // FP32 certified evaluation (else canonical FP64)
   float *vb = nullptr;    // per-slot bound of the stored f (cert only)
@@ -518,6 +590,12 @@ int read_ctr(ip_ctx *ctx) {
 
 int zero_field(ip_ctx *ctx, unsigned long long *field) {
   hipLaunchKernelGGL(zero_counter_kernel, dim3(1), dim3(1), 0, ctx->stream, field);
+  IP_TRY_HIP(ctx, hipGetLastError());
+  return IP_OK;
+}
+
+int set_counter(ip_ctx *ctx, unsigned long long *field, unsigned long long v) {
+  hipLaunchKernelGGL(set_counter_kernel, dim3(1), dim3(1), 0, ctx->stream, field, v);
   IP_TRY_HIP(ctx, hipGetLastError());
   return IP_OK;
 }
@@ -577,32 +655,26 @@ int remap_out(Run &s, uint64_t n_out) {
   return IP_OK;
 }
 
-// Grow VT to new_cap: rehash into a fresh table, re-point the first n_out
-// traced edges, rebuild the pending-evaluation list.
+// Grow VT to new_cap: rehash into a fresh table (no vertex is waiting for
+// its evaluation), re-point the first n_out traced edges.
 template <int D>
 int vt_grow(Run &s, uint64_t new_cap, uint64_t n_out) {
   ip_ctx *ctx = s.ctx;
   if (new_cap > (1ull << 32)) return ip_fail(ctx, IP_ENOMEM, "vertex table above 2^32 entries");
-  void *nt = nullptr, *nl = nullptr, *nvb = nullptr;
+  void *nt = nullptr, *nvb = nullptr;
   IP_TRY(alloc(ctx, &nt, new_cap * sizeof(VEnt)));
-  IP_TRY(alloc(ctx, &nl, new_cap * 4));
   if (s.cert) IP_TRY(alloc(ctx, &nvb, new_cap * 4));
   IP_TRY(fill_vt(ctx, (VEnt *)nt, new_cap));
   hipLaunchKernelGGL(vt_rehash_kernel, dim3(grid_for(s.vt_cap)), dim3(kBlock), 0, ctx->stream, s.vt,
                      (const float *)s.vb, s.vt_cap, (VEnt *)nt, (float *)nvb, new_cap - 1, ctx->ctr_dev);
   IP_TRY_HIP(ctx, hipGetLastError());
-  IP_TRY(zero_field(ctx, &ctx->ctr_dev->n_eval));
-  hipLaunchKernelGGL(vt_scan_pending_kernel, dim3(grid_for(new_cap)), dim3(kBlock), 0, ctx->stream,
-                     (const VEnt *)nt, new_cap, (uint32_t *)nl, ctx->ctr_dev);
-  IP_TRY_HIP(ctx, hipGetLastError());
   IP_TRY_HIP(ctx, hipStreamSynchronize(ctx->stream));
   VtBufs &tb = *s.tb;
   release(ctx, tb.keys.p);
-  release(ctx, tb.eval.p);
   tb.keys = {nt, new_cap * sizeof(VEnt)};
-  tb.eval = {nl, new_cap * 4};
+  IP_TRY(ip_ensure(ctx, tb.eval, new_cap * 4));
   s.vt = (VEnt *)nt;
-  s.eval = (uint32_t *)nl;
+  s.eval = (uint32_t *)tb.eval.p;
   s.vt_cap = new_cap;
   if (s.cert) {
     release(ctx, tb.vals.p);
@@ -617,25 +689,43 @@ int vt_grow(Run &s, uint64_t new_cap, uint64_t n_out) {
   return IP_OK;
 }
 
+// Room for `need` traced edges, the first n_used kept.  The list lives in the
+// context like the vertex table; out_trim gives a large one back.
 int out_reserve(Run &s, uint64_t need, uint64_t n_used) {
-  if (need <= s.out_cap) return IP_OK;
   ip_ctx *ctx = s.ctx;
-  uint64_t cap = std::max<uint64_t>(need, s.out_cap * 2);
-  void *nb = nullptr;
-  IP_TRY(alloc(ctx, &nb, cap * sizeof(OutRec)));
-  if (n_used)
-    IP_TRY_HIP(ctx, hipMemcpyAsync(nb, s.out, n_used * sizeof(OutRec), hipMemcpyDeviceToDevice, ctx->stream));
-  IP_TRY_HIP(ctx, hipStreamSynchronize(ctx->stream));
-  if (s.out) release(ctx, s.out);
-  s.out = (OutRec *)nb;
-  s.out_cap = cap;
+  DevBuf &ob = s.tb->out;
+  if (need * sizeof(OutRec) > ob.bytes) {
+    const uint64_t cap = std::max<uint64_t>(need, s.out_cap * 2);
+    void *nb = nullptr;
+    IP_TRY(alloc(ctx, &nb, cap * sizeof(OutRec)));
+    if (n_used)
+      IP_TRY_HIP(ctx, hipMemcpyAsync(nb, ob.p, n_used * sizeof(OutRec), hipMemcpyDeviceToDevice, ctx->stream));
+    IP_TRY_HIP(ctx, hipStreamSynchronize(ctx->stream));
+    if (ob.p) release(ctx, ob.p);
+    ob = {nb, cap * sizeof(OutRec)};
+  }
+  s.out = (OutRec *)ob.p;
+  s.out_cap = ob.bytes / sizeof(OutRec);
   return IP_OK;
+}
+
+// The search's edges are no longer needed: a list above 1 GiB goes back to
+// the allocator (after the stream's work).
+void out_trim(Run &s) {
+  DevBuf &ob = s.tb->out;
+  s.out = nullptr;
+  s.out_cap = 0;
+  if (ob.bytes <= (1ull << 30)) return;
+  (void)hipStreamSynchronize(s.ctx->stream);
+  release(s.ctx, ob.p);
+  ob = {};
 }
 
 int cslot_reserve(Run &s, uint64_t need) {
   ip_ctx *ctx = s.ctx;
-  IP_TRY(ip_ensure(ctx, ctx->vt_aux, std::max<uint64_t>(need, 1024) * 4));
+  IP_TRY(ip_ensure(ctx, ctx->vt_aux, need * 4));
   s.cslot = (uint32_t *)ctx->vt_aux.p;
+  s.cslot_cap = ctx->vt_aux.bytes / 4;
   return IP_OK;
 }
 
@@ -655,28 +745,35 @@ int eval_pending(Run &s, uint64_t n) {
   return launch_feval64(ctx, s.p, s.L, s.fb, nfb, s.vt);
 }
 
-// eval_pending without the host read of the fallback count: the canonical
-// pass is sized on the device (at most n), and the caller takes the level's
-// fallback counts from its next counter read.
-int eval_pending_async(Run &s, uint64_t n) {
-  if (!s.cert) return launch_feval64(s.ctx, s.p, s.L, s.eval, n, s.vt);
+// eval_pending of the level chain: the count is in *n_dev (about `hint`), and
+// the canonical pass takes its own from the device too.
+int eval_chain(Run &s, const unsigned long long *n_dev, uint64_t hint) {
   ip_ctx *ctx = s.ctx;
-  if (n == 0) return IP_OK;
-  IP_TRY(zero_field(ctx, &ctx->ctr_dev->n_fb));
-  IP_TRY(zero_field(ctx, &ctx->ctr_dev->n_cert64));
-  IP_TRY(launch_feval32(ctx, s.p, s.L, s.eval, n, s.vt, s.vb, s.fb, &ctx->ctr_dev->n_fb));
-  return launch_feval64_dev(ctx, s.p, s.L, s.fb, n, &ctx->ctr_dev->n_fb, s.vt);
+  // levels grow faster than the counters are read: a block per CU at least
+  hint = std::max<uint64_t>(hint, 7168);
+  Counters *c = ctx->ctr_dev;
+  if (!s.cert) return launch_feval64(ctx, s.p, s.L, s.eval, s.vt_cap, s.vt, n_dev, hint, &c->t_eval);
+  IP_TRY(launch_feval32(ctx, s.p, s.L, s.eval, s.vt_cap, s.vt, s.vb, s.fb, &c->n_fb, n_dev, hint, &c->t_eval));
+  // rarely more than a few vertices
+  return launch_feval64(ctx, s.p, s.L, s.fb, s.vt_cap, s.vt, &c->n_fb, 1792);
 }
 
+// Pass 1 or 2 of a level, for a frontier of about `edges`.
 template <int D, bool EDGES>
-int level_pass(Run &s, uint64_t lo, uint64_t hi) {
+int level_pass(Run &s, uint32_t level, uint64_t edges) {
   ip_ctx *ctx = s.ctx;
-  unsigned grid = grid_for((hi - lo) * 4, 8192);
-  hipLaunchKernelGGL((expand_kernel<D, EDGES>), dim3(grid), dim3(kBlock), 0, ctx->stream, s.L, s.out, lo, hi, s.vt,
-                     s.vt_cap - 1, s.cslot, s.eval, ctx->ctr_dev);
+  // one wave per edge up to 16 waves per CU
+  const unsigned grid = (unsigned)std::min<uint64_t>(std::max<uint64_t>(edges / 16, 32), edges > 1048576 ? 512 : 256);
+  hipLaunchKernelGGL((expand_kernel<D, EDGES>), dim3(grid), dim3(kExpand), 0, ctx->stream, s.L, s.out, s.out_cap, s.vt,
+                     s.vt_cap - 1, s.cslot, s.cslot_cap, s.eval, ctx->ctr_dev, level);
   IP_TRY_HIP(ctx, hipGetLastError());
   return IP_OK;
 }
+
+// Levels queued between two reads of the counters, and the smallest buffers
+// a search starts with.
+constexpr uint32_t kChain = 3;
+constexpr uint64_t kOut0 = 1ull << 20, kCslot0 = 1ull << 22;
 
 // Direct trace on lattice s.L (fine, or coarse in batch mode).  On return
 // s.out[0 .. *n_out) holds the traced edges and VT holds f at their ends.
@@ -685,80 +782,110 @@ int trace_direct(Run &s, ip_stats &st, uint64_t *n_out_ret) {
   constexpr uint64_t MAXC = (1u << D) - 2;
   ip_ctx *ctx = s.ctx;
   const ip_problem *p = s.p;
-  Counters *c = ctx->ctr_host;
-  Timer tf, tx;
-  IP_TRY_HIP(ctx, hipMemsetAsync(ctx->ctr_dev, 0, sizeof(Counters), ctx->stream));
-  // locate
+  Counters *dev = ctx->ctr_dev;
+  // a level may stop and be mended while counters queued later are copied
+  struct Drain {
+    ip_ctx *ctx;
+    ~Drain() { (void)hipStreamSynchronize(ctx->stream); }
+  } drain{ctx};
+  // the seeds' vertices fill at most a quarter of the table
+  const uint64_t seed_verts = (uint64_t)p->n_seeds * (D + 1);
+  if (seed_verts * 4 > s.vt_cap) IP_TRY(vt_init(s, pow2_at_least(seed_verts * 4)));
+  IP_TRY(out_reserve(s, std::max<uint64_t>(kOut0, seed_verts * D / 2 + 1024), 0));
+  IP_TRY(cslot_reserve(s, std::max<uint64_t>(kCslot0, seed_verts * D / 2 * MAXC)));
+  IP_TRY_HIP(ctx, hipMemsetAsync(dev, 0, sizeof(Counters), ctx->stream));
   const unsigned sg = (unsigned)((p->n_seeds + 127) / 128);
-  for (int guard = 0;; ++guard) {
-    if (guard > 40) return ip_fail(ctx, IP_ENOMEM, "vertex table cannot grow");
-    hipLaunchKernelGGL((seed_vertices_kernel<D>), dim3(sg), dim3(128), 0, ctx->stream, s.L, p->seeds_dev, p->n_seeds,
-                       s.vt, s.vt_cap - 1, s.eval, ctx->ctr_dev);
-    IP_TRY_HIP(ctx, hipGetLastError());
-    IP_TRY(read_ctr(ctx));
-    if (!c->vt_fail) break;
-    IP_TRY(zero_fail_flags(ctx));
-    IP_TRY(vt_grow<D>(s, s.vt_cap * 4, 0));
-  }
-  IP_TRY(tf.start(ctx, &st.ms_feval));
-  IP_TRY(eval_pending(s, c->n_eval));
-  IP_TRY(tf.stop(ctx));
-  IP_TRY(out_reserve(s, (uint64_t)p->n_seeds * (D + 1) * D / 2 + 1024, 0));
-  hipLaunchKernelGGL((seed_edges_kernel<D>), dim3(sg), dim3(128), 0, ctx->stream, s.L, p->seeds_dev, p->n_seeds, s.vt,
-                     s.vt_cap - 1, s.out, ctx->ctr_dev);
+  hipLaunchKernelGGL((seed_vertices_kernel<D>), dim3(sg), dim3(128), 0, ctx->stream, s.L, p->seeds_dev, p->n_seeds,
+                     s.vt, s.vt_cap - 1, s.eval, dev);
   IP_TRY_HIP(ctx, hipGetLastError());
-  IP_TRY(read_ctr(ctx));
-  uint64_t lo = 0, hi = c->n_out;
-  int levels = 0;
-  uint64_t cof_total = 0;
-  while (hi > lo) {
-    ++levels;
-    IP_TRY(cslot_reserve(s, ((hi - lo + 63) / 64) * 64 * MAXC));
-    // pass 1: third vertices
-    IP_TRY(zero_field(ctx, &ctx->ctr_dev->n_eval));
-    IP_TRY(zero_field(ctx, &ctx->ctr_dev->n_cof));
-    IP_TRY(tx.start(ctx, &st.ms_expand));
-    IP_TRY((level_pass<D, false>(s, lo, hi)));
-    IP_TRY(tx.stop(ctx));
-    IP_TRY(read_ctr(ctx));
-    int guard = 0;
-    while (c->vt_fail || c->vt_count * 2 > s.vt_cap) {
-      if (++guard > 40) return ip_fail(ctx, IP_ENOMEM, "vertex table cannot grow");
+  IP_TRY(eval_chain(s, &dev->n_ev[1], seed_verts));
+  hipLaunchKernelGGL((seed_edges_kernel<D>), dim3(sg), dim3(128), 0, ctx->stream, s.L, p->seeds_dev, p->n_seeds, s.vt,
+                     s.vt_cap - 1, s.out, dev);
+  IP_TRY_HIP(ctx, hipGetLastError());
+  // estimates that shape the next launches: frontier edges, new vertices
+  uint64_t edges = seed_verts * D / 2, verts = seed_verts;
+  int64_t fb_seen = 0, c64_seen = 0;  // of evaluations whose level was queued again
+  uint32_t level = 0, chunk = 0;
+  bool from_edges = false;            // the first level queued starts with pass 2
+  auto queue = [&]() -> int {
+    for (uint32_t q = 0; q < kChain; ++q, ++level) {
+      if (!from_edges) {
+        IP_TRY((level_pass<D, false>(s, level, edges)));
+        IP_TRY(eval_chain(s, &dev->n_ev[level & 1u], verts));
+      }
+      from_edges = false;
+      IP_TRY((level_pass<D, true>(s, level, edges)));
+    }
+    const int i = (int)(chunk & 1u);
+    IP_TRY_HIP(ctx, hipMemcpyAsync(ctx->ctr_host + 1 + i, dev, sizeof(Counters), hipMemcpyDeviceToHost, ctx->stream));
+    IP_TRY_HIP(ctx, hipEventRecord(ctx->ctr_ev[i], ctx->stream));
+    ++chunk;
+    return IP_OK;
+  };
+  const Counters *c = nullptr;
+  IP_TRY(queue());
+  for (int guard = 0;;) {
+    // one chunk stays queued while the counters of the one before are read
+    IP_TRY(queue());
+    const int i = (int)(chunk & 1u);
+    IP_TRY_HIP(ctx, hipEventSynchronize(ctx->ctr_ev[i]));
+    c = ctx->ctr_host + 1 + i;
+    if (!c->stop) {
+      // the frontier and the vertices of the last whole level
+      const uint32_t done = (uint32_t)c->levels;
+      edges = 2 * (c->n_out - c->lv[done & 3u]) + 64;
+      verts = (c->vt_cnt[done & 1u] - c->vt_cnt[(done + 1) & 1u]) * 5 / 4 + 64;
+      continue;
+    }
+    IP_TRY(read_ctr(ctx));  // the chunk behind it has run out
+    c = ctx->ctr_host;
+    if (c->stop == IP_STOP_DONE && !c->vt_fail) break;
+    if (++guard > 200) return ip_fail(ctx, IP_ENOMEM, "search buffers cannot grow");
+    level = c->stop_level;
+    if (level == 0 && c->vt_fail) {
+      // perhaps a seed's vertex that found no place: from the start
+      if (s.vt_cap >= (1ull << 32)) return ip_fail(ctx, IP_ENOMEM, "vertex table above 2^32 entries");
+      IP_TRY(vt_init(s, s.vt_cap * 4));
+      ++s.regrows;
+      return trace_direct<D>(s, st, n_out_ret);
+    }
+    const uint32_t par = level & 1u;
+    const uint64_t lo = c->lv[level & 3u], hi = c->n_out;
+    uint64_t cof = 0;
+    for (int k = 0; k < IP_COF_SLOTS; ++k) cof += c->n_cofl[par][k * 8];
+    const uint64_t n_ev = c->n_ev[par] + c->n_held, nv = c->vt_cnt[par] + n_ev;
+    const uint32_t stop = c->stop;
+    edges = 2 * (hi - lo) + 64;
+    IP_TRY(set_counter(ctx, &dev->n_ev[par], n_ev));
+    IP_TRY(zero_field(ctx, &dev->n_held));
+    if (stop & IP_STOP_CSLOT) IP_TRY(cslot_reserve(s, (hi - lo) * MAXC * 2));
+    if (stop & IP_STOP_OUT) IP_TRY(out_reserve(s, hi + cof + 1, hi));
+    if (stop & IP_STOP_VT) {
       IP_TRY(zero_fail_flags(ctx));
-      IP_TRY(vt_grow<D>(s, pow2_at_least(c->vt_count * 4), hi));
-      // slots moved: replay pass 1 so CSL points into the new table; it
-      // finds the inserted vertices and lists the missing ones after the
-      // rebuilt pending list
-      IP_TRY(zero_field(ctx, &ctx->ctr_dev->n_cof));
-      IP_TRY((level_pass<D, false>(s, lo, hi)));
+      fb_seen += (int64_t)c->n_fb;
+      c64_seen += (int64_t)c->n_cert64;
+      verts = 2 * n_ev + 64;
+      IP_TRY(vt_grow<D>(s, pow2_at_least(std::max<uint64_t>(nv * 4, s.vt_cap * 2)), hi));
+      // slots moved: pass 1 again, so that CSL points into the new table;
+      // every vertex listed so far is evaluated and counted
+      IP_TRY(set_counter(ctx, &dev->vt_cnt[par], nv));
+      IP_TRY(zero_field(ctx, &dev->n_ev[par]));
+      IP_TRY(fill(ctx, dev->n_cofl[par], IP_COF_SLOTS * 8, 0ull));
       IP_TRY(read_ctr(ctx));
-      if (c->vt_fail & 2u) return ip_fail(ctx, IP_EDEVICE, "internal: traced edge lost its vertex");
+      if (c->vt_fail) return ip_fail(ctx, IP_EDEVICE, "internal: traced edge lost its vertex");
     }
-    cof_total += c->n_cof;
-    const bool evaluated = c->n_eval > 0;
-    IP_TRY(tf.start(ctx, &st.ms_feval));
-    IP_TRY(eval_pending_async(s, c->n_eval));
-    IP_TRY(tf.stop(ctx));
-    // pass 2: new edges; OUT must hold one new edge per coface at most
-    IP_TRY(out_reserve(s, hi + c->n_cof + 1, hi));
-    IP_TRY(tx.start(ctx, &st.ms_expand));
-    IP_TRY((level_pass<D, true>(s, lo, hi)));
-    IP_TRY(tx.stop(ctx));
-    IP_TRY(read_ctr(ctx));
-    if (s.cert && evaluated) {
-      // this level's FP32 evaluation left these counts
-      s.n_fallback += (int64_t)c->n_fb;
-      s.n_settled64 += (int64_t)c->n_cert64;
-    }
-    lo = hi;
-    hi = c->n_out;
+    from_edges = (stop & (IP_STOP_CSLOT | IP_STOP_VT)) == 0;
+    IP_TRY(zero_field(ctx, (unsigned long long *)&dev->stop));
+    IP_TRY(queue());
   }
-  IP_TRY(tf.flush(ctx));
-  IP_TRY(tx.flush(ctx));
-  st.levels += levels;
-  st.n_cofaces += (int64_t)cof_total;
-  st.n_vertices += (int64_t)c->vt_count;
-  *n_out_ret = hi;
+  s.n_fallback += (int64_t)c->fb_total + fb_seen;
+  s.n_settled64 += (int64_t)c->c64_total + c64_seen;
+  st.ms_feval += (double)c->ticks_eval / ctx->ticks_per_ms;
+  st.ms_expand += (double)c->ticks_expand / ctx->ticks_per_ms;
+  st.levels += (int)c->levels;
+  st.n_cofaces += (int64_t)c->cof_total;
+  st.n_vertices += (int64_t)c->vt_cnt[c->stop_level & 1u];
+  *n_out_ret = c->n_out;
   return IP_OK;
 }
 
@@ -1610,8 +1737,6 @@ __global__ __launch_bounds__(kBlock, 4) void subdivide_kernel(LatDev Lf, LatDev 
   if (nuns) atomicAdd(&ctr->n_unsettled, (unsigned long long)nuns);
 }
 
-__global__ void set_counter_kernel(unsigned long long *p, unsigned long long v) { *p = v; }
-
 // Ends of the listed edges as raw vertices: vraw[2r] = a, vraw[2r + 1] = b.
 template <int D>
 __global__ void redo_ends_kernel(LatDev L, const uint64_t *keys, const uint64_t *redo, uint64_t n, int32_t *vraw) {
@@ -1848,12 +1973,6 @@ struct BatchSink {
     return IP_OK;
   }
 };
-
-int set_counter(ip_ctx *ctx, unsigned long long *field, unsigned long long v) {
-  hipLaunchKernelGGL(set_counter_kernel, dim3(1), dim3(1), 0, ctx->stream, field, v);
-  IP_TRY_HIP(ctx, hipGetLastError());
-  return IP_OK;
-}
 
 // Runs `launch` (one subdivision launch) until it neither found the edge set
 // full nor overran the owner list.  Before the first launch the set is grown
@@ -2585,9 +2704,9 @@ int trace_batch(ip_ctx *ctx, const ip_problem *p, uint64_t budget, bool cert, ip
   IP_TRY(vt_init(s, 1ull << 16));
   uint64_t nc = 0;
   {
-    int rc = trace_direct<D>(s, st, &nc);
+    const int rc = trace_direct<D>(s, st, &nc);
     if (rc != IP_OK) {
-      if (s.out) release(ctx, s.out);
+      out_trim(s);
       return rc;
     }
   }
@@ -2595,13 +2714,8 @@ int trace_batch(ip_ctx *ctx, const ip_problem *p, uint64_t budget, bool cert, ip
   // ctx->vtc for the ownership test; the fine stage uses ctx->vtf
   const VEnt *cvt = s.vt;
   const uint64_t cvt_cap = s.vt_cap;
-  OutRec *coarse_edges = s.out;
-  s.out = nullptr;
-  s.out_cap = 0;
-  auto free_coarse = [&]() {
-    if (coarse_edges) release(ctx, coarse_edges);
-    coarse_edges = nullptr;
-  };
+  const OutRec *coarse_edges = s.out;
+  auto free_coarse = [&]() { out_trim(s); };
   // ---- Sigma: n-cofaces of the coarse edges, deduplicated
   void *sig_tab = nullptr, *sig_list = nullptr;
   uint64_t nsig = 0;
@@ -2751,10 +2865,7 @@ int trace_T(ip_ctx *ctx, const ip_problem *p, uint64_t budget, int32_t prec, ip_
   if (rc == IP_OK) rc = alloc(ctx, (void **)&keys, sizeof(uint64_t) * (size_t)(n ? n : 1));
   if (rc == IP_OK) rc = alloc(ctx, (void **)&pts, sizeof(double) * (size_t)(n ? n : 1) * D);
   if (rc == IP_OK && n) rc = direct_points<D>(s, n, keys, pts, st);
-  if (s.out) {
-    (void)hipStreamSynchronize(ctx->stream);
-    release(ctx, s.out);
-  }
+  out_trim(s);
   if (rc != IP_OK) {
     if (keys) release(ctx, keys);
     if (pts) release(ctx, pts);
@@ -3043,10 +3154,7 @@ int project_T(ip_ctx *ctx, const ip_problem *p, uint64_t *bytes, int64_t *n_coar
   ip_stats st = {};
   uint64_t nc = 0;
   const int rc = trace_direct<D>(s, st, &nc);
-  if (s.out) {
-    (void)hipStreamSynchronize(ctx->stream);
-    release(ctx, s.out);
-  }
+  out_trim(s);
   IP_TRY(rc);
   double cells = (double)nc * 1.25;
   for (int q = 0; q < D - 1; ++q) cells *= p->probe_k;
