@@ -185,36 +185,53 @@ struct PolyDev {
   double K32n;  // nested FP32 evaluation: |f32 - F| <= K32n * sum |c_m| |x^m| + E0
 };
 
-// Atomics on one address cost about 12 ns each whoever issues them, so sums
-// that many blocks add to are spread over lines.
-#define IP_COF_SLOTS 16
+// Atomics on one address, or on one cache line, cost about 12 ns each whoever
+// issues them.  Sums that many blocks add to are therefore spread over lines
+// (IP_LINE apart), append counters that run at the same time have a line of
+// their own, and a list that every wave appends to is filled as IP_REGIONS
+// lists side by side.
+#define IP_LINE 16
+#define IP_REGIONS 16
+#define IP_TALLIES 4
 
 struct Counters {
   unsigned long long n_eval;     // eval-list length (reset per pass)
-  unsigned long long n_out;      // output-list length (== edges in ET)
-  unsigned long long n_cof;      // cofaces expanded in the current level
   unsigned long long n_fb;       // FP64 fallback list length
   unsigned long long n_fb_total; // fallbacks over the whole call
-  unsigned long long n_aux;      // general-purpose append counter
   unsigned long long n_cert64;   // vertices settled by the FP64 monomial tier
-  unsigned long long n_pts;      // template points evaluated (fused subdivision)
-  unsigned long long n_unsettled;// template points left to the canonical tier
   unsigned long long n_direct;   // owner-emitted fine edges (batch mode)
-  unsigned long long n_shared;   // intersecting template edges sent to the edge set
   unsigned int vt_fail;          // vertex-table insert found the table full
   unsigned int et_fail;          // edge-table insert found the table full
   // breadth-first search (trace.hip, "Level chain"); the two-entry fields go
   // by the level's parity, lv by the level modulo 4
   unsigned long long lv[4];      // first traced edge of a level
-  unsigned long long n_ev[2];    // vertices the level added (its eval list)
-  unsigned long long n_cofl[2][IP_COF_SLOTS * 8];  // cofaces of the level's edges: partial sums, a cache line each
   unsigned long long vt_cnt[2];  // vertices before the level
   unsigned long long n_held;     // eval-list length of a level that stopped
   unsigned long long cof_total, levels, fb_total, c64_total;
   unsigned long long t_mark, t_eval;      // device clock at the last pass, at the level's evaluation
   unsigned long long ticks_expand, ticks_eval;
   unsigned int stop, stop_level;          // IP_STOP_*, and the level it stopped at
+  unsigned long long n_ev[2];    // vertices the level added (its eval list)
+  // a line each
+  __attribute__((aligned(8 * IP_LINE))) unsigned long long n_out;  // output-list length (== edges in ET)
+  __attribute__((aligned(8 * IP_LINE))) unsigned long long n_aux;  // general-purpose append counter
+  // partial sums: cofaces of the level's edges; subdivision tallies (IP_T_*);
+  // lengths of the owner-emitted lists of one subdivision launch
+  __attribute__((aligned(8 * IP_LINE))) unsigned long long n_cofl[2][IP_REGIONS * IP_LINE];
+  unsigned long long tally[IP_TALLIES][IP_REGIONS * IP_LINE];
+  unsigned long long region[IP_REGIONS * IP_LINE];
 };
+
+// Tallies of a subdivision launch: intersecting (simplex, template edge)
+// pairs, those sent to the edge set, template points evaluated, and left to
+// the canonical tier.
+enum { IP_T_HITS = 0, IP_T_SHARED = 1, IP_T_POINTS = 2, IP_T_UNSETTLED = 3 };
+
+__host__ __device__ inline unsigned long long line_sum(const unsigned long long *p) {
+  unsigned long long t = 0;
+  for (int k = 0; k < IP_REGIONS; ++k) t += p[k * IP_LINE];
+  return t;
+}
 
 // Why the level chain stopped: the frontier is empty; the coface slots or
 // the traced edges need a larger buffer; the vertex table needs growing.

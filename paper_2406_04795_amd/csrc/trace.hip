@@ -29,7 +29,7 @@
 namespace {
 
 constexpr int kBlock = 256;
-constexpr int kStage = 128;  // per-wave staged append entries
+constexpr int kStage = 256;  // per-wave staged append entries
 constexpr int kExpand = 1024;  // threads of an expand_kernel block
 
 struct OutRec {
@@ -228,8 +228,7 @@ __global__ __launch_bounds__(kExpand) void expand_kernel(LatDev L, OutRec *out, 
     }
   } else {
     const unsigned long long nv = ctr->vt_cnt[par] + ctr->n_ev[par];
-    unsigned long long nc = 0;
-    for (int k = 0; k < IP_COF_SLOTS; ++k) nc += ctr->n_cofl[par][k * 8];
+    const unsigned long long nc = line_sum(ctr->n_cofl[par]);
     if (ctr->vt_fail || nv * 2 > vt_mask + 1) halt |= IP_STOP_VT;
     if (hi + nc + 1 > out_cap) halt |= IP_STOP_OUT;
     if (first && !stopped) {
@@ -243,7 +242,7 @@ __global__ __launch_bounds__(kExpand) void expand_kernel(LatDev L, OutRec *out, 
         ctr->t_mark = now;
         ctr->vt_cnt[nxt] = nv;
         ctr->n_ev[nxt] = 0;
-        for (int k = 0; k < IP_COF_SLOTS; ++k) ctr->n_cofl[nxt][k * 8] = 0;
+        for (int k = 0; k < IP_REGIONS; ++k) ctr->n_cofl[nxt][k * IP_LINE] = 0;
         ctr->cof_total += nc;
         ctr->levels += 1;
         ctr->fb_total += ctr->n_fb;
@@ -369,7 +368,7 @@ __global__ __launch_bounds__(kExpand) void expand_kernel(LatDev L, OutRec *out, 
     if (threadIdx.x == 0) {
       unsigned long long t = 0;
       for (int w = 0; w < kExpand / 64; ++w) t += wcof[w];
-      if (t) atomicAdd(&ctr->n_cofl[par][(blockIdx.x % IP_COF_SLOTS) * 8], t);
+      if (t) atomicAdd(&ctr->n_cofl[par][(blockIdx.x % IP_REGIONS) * IP_LINE], t);
     }
   }
 }
@@ -817,7 +816,9 @@ int trace_direct(Run &s, ip_stats &st, uint64_t *n_out_ret) {
       IP_TRY((level_pass<D, true>(s, level, edges)));
     }
     const int i = (int)(chunk & 1u);
-    IP_TRY_HIP(ctx, hipMemcpyAsync(ctx->ctr_host + 1 + i, dev, sizeof(Counters), hipMemcpyDeviceToHost, ctx->stream));
+    // (the partial sums behind n_cofl are of no use before a stop)
+    IP_TRY_HIP(ctx, hipMemcpyAsync(ctx->ctr_host + 1 + i, dev, offsetof(Counters, n_cofl), hipMemcpyDeviceToHost,
+                                   ctx->stream));
     IP_TRY_HIP(ctx, hipEventRecord(ctx->ctr_ev[i], ctx->stream));
     ++chunk;
     return IP_OK;
@@ -850,9 +851,7 @@ int trace_direct(Run &s, ip_stats &st, uint64_t *n_out_ret) {
       return trace_direct<D>(s, st, n_out_ret);
     }
     const uint32_t par = level & 1u;
-    const uint64_t lo = c->lv[level & 3u], hi = c->n_out;
-    uint64_t cof = 0;
-    for (int k = 0; k < IP_COF_SLOTS; ++k) cof += c->n_cofl[par][k * 8];
+    const uint64_t lo = c->lv[level & 3u], hi = c->n_out, cof = line_sum(c->n_cofl[par]);
     const uint64_t n_ev = c->n_ev[par] + c->n_held, nv = c->vt_cnt[par] + n_ev;
     const uint32_t stop = c->stop;
     edges = 2 * (hi - lo) + 64;
@@ -870,7 +869,7 @@ int trace_direct(Run &s, ip_stats &st, uint64_t *n_out_ret) {
       // every vertex listed so far is evaluated and counted
       IP_TRY(set_counter(ctx, &dev->vt_cnt[par], nv));
       IP_TRY(zero_field(ctx, &dev->n_ev[par]));
-      IP_TRY(fill(ctx, dev->n_cofl[par], IP_COF_SLOTS * 8, 0ull));
+      IP_TRY(fill(ctx, dev->n_cofl[par], IP_REGIONS * IP_LINE, 0ull));
       IP_TRY(read_ctr(ctx));
       if (c->vt_fail) return ip_fail(ctx, IP_EDEVICE, "internal: traced edge lost its vertex");
     }
@@ -965,21 +964,27 @@ __global__ void count_ncof_kernel(const OutRec *edges, uint64_t n, int D, int B,
 }
 
 // Sec. V-B: n-simplex cofaces of the coarse intersecting edges, hashed to
-// remove duplicates; the winners are listed in discovery order.
+// remove duplicates; the winners are listed in discovery order.  Each wave
+// takes c edges as in expand_kernel (33 thousand coarse edges of 250 cofaces
+// each kept 509 waves busy at 64 edges per wave), and appends through a stage.
 template <int D>
-__global__ __launch_bounds__(kBlock) void sigma_kernel(LatDev Lc, int LB, const OutRec *__restrict__ edges,
+__global__ __launch_bounds__(kExpand) void sigma_kernel(LatDev Lc, int LB, const OutRec *__restrict__ edges,
                                                        uint64_t n, uint64_t *sig_tab, uint64_t sig_mask,
                                                        uint64_t *sig_list, Counters *ctr) {
-  const int lane = threadIdx.x & 63;
+  __shared__ uint64_t st[kExpand / 64][kStage];
+  const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
   const uint64_t wave = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const uint64_t n_waves = ((uint64_t)gridDim.x * blockDim.x) >> 6;
-  const uint64_t nchunks = (n + 63) >> 6;
-  const uint64_t below = (1ull << lane) - 1ull;
+  const uint64_t share = (n + n_waves - 1) / n_waves;
+  const uint64_t c = share > 64 ? 64 : share;
+  const uint64_t nchunks = (n + c - 1) / c;
+  int sn = 0;
+  auto put = [&](unsigned long long pos, uint64_t key) { sig_list[pos] = key; };
   for (uint64_t ch = wave; ch < nchunks; ch += n_waves) {
-    const uint64_t ei = ch * 64 + lane;
+    const uint64_t ei = ch * c + lane;
     uint64_t e = 0;
     int cnt = 0;
-    if (ei < n) {
+    if (lane < (int)c && ei < n) {
       e = edges[ei].key;
       cnt = n_cofacesn<D>((uint32_t)((e & ~IP_SIGN_BIT) >> (D * Lc.B)) & ((1u << D) - 1u));
     }
@@ -1018,18 +1023,18 @@ __global__ __launch_bounds__(kBlock) void sigma_kernel(LatDev Lc, int LB, const 
           uint32_t avail = R;
           for (int i = 0; i < nR; ++i) {
             int f = ifact(nR - 1 - i);
-            int c = (int)(code / (uint32_t)f);
+            int q = (int)(code / (uint32_t)f);
             code %= (uint32_t)f;
-            pi[i] = nth_bit(avail, c);
+            pi[i] = nth_bit(avail, q);
             avail &= ~(1u << pi[i]);
           }
           code = (uint32_t)(r % fQ);
           avail = Q;
           for (int i = 0; i < nQ; ++i) {
             int f = ifact(nQ - 1 - i);
-            int c = (int)(code / (uint32_t)f);
+            int q = (int)(code / (uint32_t)f);
             code %= (uint32_t)f;
-            rho[i] = nth_bit(avail, c);
+            rho[i] = nth_bit(avail, q);
             avail &= ~(1u << rho[i]);
           }
         }
@@ -1060,16 +1065,10 @@ __global__ __launch_bounds__(kBlock) void sigma_kernel(LatDev Lc, int LB, const 
           atomicOr(&ctr->vt_fail, 1u);
         }
       }
-      const uint64_t bal = __ballot(is_new);
-      if (bal) {
-        const int leader = __ffsll((long long)bal) - 1;
-        unsigned long long b0 = 0;
-        if (lane == leader) b0 = atomicAdd(&ctr->n_aux, (unsigned long long)__popcll(bal));
-        b0 = shfl64(b0, leader);
-        if (is_new) sig_list[b0 + __popcll(bal & below)] = key;
-      }
+      stage_put<kStage>(st[wib], sn, is_new, key, put, &ctr->n_aux);
     }
   }
+  stage_flush_block(st[wib], sn, put, &ctr->n_aux);
 }
 
 // Template point p of coarse simplex (v, w) in fine lattice coordinates:
@@ -1110,7 +1109,10 @@ __global__ __launch_bounds__(kBlock) void batch_vertices_kernel(LatDev Lf, LatDe
                                                                 VEnt *vt, uint64_t vt_mask,
                                                                 uint32_t *eval_list, uint32_t *pslot,
                                                                 Counters *ctr) {
-  const int lane = threadIdx.x & 63;
+  __shared__ uint32_t st[kBlock / 64][kStage];
+  const int wib = threadIdx.x >> 6;
+  int sn = 0;
+  auto put = [&](unsigned long long pos, uint32_t q) { eval_list[pos] = q; };
   const uint64_t total = nb * (uint64_t)NP;
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
   const uint64_t start = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1139,15 +1141,9 @@ __global__ __launch_bounds__(kBlock) void batch_vertices_kernel(LatDev Lf, LatDe
       }
       pslot[t] = ps;
     }
-    const uint64_t bal = __ballot(is_new);
-    if (bal) {
-      const int leader = __ffsll((long long)bal) - 1;
-      unsigned long long b0 = 0;
-      if (lane == leader) b0 = atomicAdd(&ctr->n_eval, (unsigned long long)__popcll(bal));
-      b0 = shfl64(b0, leader);
-      if (is_new) eval_list[b0 + __popcll(bal & ((1ull << lane) - 1ull))] = (uint32_t)slot;
-    }
+    stage_put<kStage>(st[wib], sn, is_new, (uint32_t)slot, put, &ctr->n_eval);
   }
+  stage_flush_block(st[wib], sn, put, &ctr->n_eval);
 }
 
 // Intersection points of the edges keys[lo .. hi) from the values of their
@@ -1228,16 +1224,17 @@ constexpr int kSubStage = 128;
 constexpr int kWaves = kBlock / 64;
 
 constexpr int kEdgeStage = 128;
+constexpr int kDeferStage = 32;
 
 // Dynamic LDS of one block, as byte offsets (each array 16-byte aligned).
 // Shared by the block: the fine frame (M row-major stride 8, then o, lo, hi),
 // the monomial coefficients (FP64 and FP32), the template points with their
 // face masks, the faces' point masks, the edges and face groups.  Per wave:
 // two append stages, the start bitmap, the sign masks over the points and
-// the list of the active groups, the edge stage, the active point list and
-// the sign codes.
+// the list of the active groups, the edge stage, the stage of the deferred
+// simplices, the active point list and the sign codes.
 struct SubLayout {
-  uint32_t lmat, lc, stage_s, stage_d, lpts, lpf, lpv, sbm, est, ledge, lgrp, lmask, agl, plist, code, total;
+  uint32_t lmat, lc, stage_s, stage_d, lpts, lpf, lpv, sbm, est, dst, ledge, lgrp, lmask, agl, plist, code, total;
 };
 
 __host__ __device__ inline uint32_t sub_take(uint32_t &o, size_t bytes) {
@@ -1264,6 +1261,7 @@ __host__ __device__ inline SubLayout sub_layout(int NP, int NE, int M, int NV) {
   L.lpv = sub_take(o, (size_t)NV * NPW * 8);
   L.sbm = sub_take(o, (size_t)kWaves * SBW * 8);
   L.est = sub_take(o, (size_t)kWaves * kEdgeStage * 4);
+  L.dst = sub_take(o, (size_t)kWaves * kDeferStage * 4);
   L.ledge = sub_take(o, (size_t)NE * 4);
   L.lgrp = sub_take(o, (size_t)NV * 4);
   L.lmask = sub_take(o, (size_t)kWaves * 2 * NPW * 8);
@@ -1301,8 +1299,8 @@ struct SubOut {
   uint64_t *et_keys;  // global edge set (edges without an owner)
   uint64_t et_mask;
   uint64_t *out_s;    // its keys in insertion order
-  uint64_t *out_d;    // owner-emitted keys
-  uint64_t dcap;      // capacity of out_d (appends past it are counted, not written)
+  uint64_t *out_d;    // owner-emitted keys: IP_REGIONS lists of rcap entries
+  uint64_t rcap;      // (appends past a list's end are counted, not written)
 };
 
 // Bit b of word t set when vertex i belongs to the vertex subset 64 t + b.
@@ -1495,11 +1493,19 @@ __global__ __launch_bounds__(kBlock, 4) void subdivide_kernel(LatDev Lf, LatDev 
   __syncthreads();
   int sn = 0, snd = 0;
   auto put_s = [&](unsigned long long pos, uint64_t key) { so.out_s[pos] = key; };
+  // blocks append to IP_REGIONS lists, each with its counter: with one list
+  // the 514 M keys of the benchmark took 4 M turns of 12 ns at its counter
+  const uint32_t reg = blockIdx.x % IP_REGIONS;
+  uint64_t *const out_d = so.out_d + (uint64_t)reg * so.rcap;
+  unsigned long long *const ctr_d = &ctr->region[reg * IP_LINE];
   auto put_d = [&](unsigned long long pos, uint64_t key) {
-    if (pos < so.dcap) so.out_d[pos] = key;
+    if (pos < so.rcap) out_d[pos] = key;
   };
+  uint32_t *dst = (uint32_t *)(smem + Ly.dst) + (size_t)wib * kDeferStage;
+  int sdf = 0;
+  auto put_df = [&](unsigned long long pos, uint32_t q) { defer[pos] = q; };
   // per-lane tallies (a lane sees far fewer than 2^32 events per launch)
-  uint32_t hits = 0, shits = 0, n64 = 0, npts = 0, nuns = 0;
+  uint32_t hits = 0, shits = 0, npts = 0, nuns = 0;
   const uint64_t wave = ((uint64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
   const uint64_t n_waves = ((uint64_t)gridDim.x * kBlock) >> 6;
   // MODE 0 and 3 walk sig[0 .. n); MODE 1 and 2 walk the deferred list.
@@ -1601,8 +1607,8 @@ __global__ __launch_bounds__(kBlock, 4) void subdivide_kernel(LatDev Lf, LatDev 
     }
     if (MODE == 1) continue;
     if (MODE == 0 && unsettled) {
-      if (lane == 0) defer[atomicAdd(&ctr->n_aux, 1ull)] = (uint32_t)s;
       wave_lds_sync();
+      stage_put<kDeferStage>(dst, sdf, lane == 0, (uint32_t)s, put_df, &ctr->n_aux);
       continue;
     }
     wave_lds_sync();
@@ -1690,7 +1696,7 @@ __global__ __launch_bounds__(kBlock, 4) void subdivide_kernel(LatDev Lf, LatDev 
           }
         }
         stage_put<kSubStage>(stage_s, sn, nw, key, put_s, &ctr->n_out);
-        stage_put<kSubStage>(stage_d, snd, dir, key, put_d, &ctr->n_direct);
+        stage_put<kSubStage>(stage_d, snd, dir, key, put_d, ctr_d);
       }
       wave_lds_sync();
       sne = 0;
@@ -1726,15 +1732,42 @@ __global__ __launch_bounds__(kBlock, 4) void subdivide_kernel(LatDev Lf, LatDev 
     }
     flush_edges();
   }
-  if (MODE != 1) {
-    stage_flush(stage_s, sn, put_s, &ctr->n_out);
-    stage_flush(stage_d, snd, put_d, &ctr->n_direct);
+  if (MODE == 1) return;
+  stage_flush_block(stage_s, sn, put_s, &ctr->n_out);
+  __syncthreads();
+  stage_flush_block(stage_d, snd, put_d, ctr_d);
+  if (MODE == 0) {
+    __syncthreads();
+    stage_flush_block(dst, sdf, put_df, &ctr->n_aux);
   }
-  if (hits) atomicAdd(&ctr->n_cof, (unsigned long long)hits);
-  if (shits) atomicAdd(&ctr->n_shared, (unsigned long long)shits);
-  if (n64) atomicAdd(&ctr->n_cert64, (unsigned long long)n64);
-  if (npts) atomicAdd(&ctr->n_pts, (unsigned long long)npts);
-  if (nuns) atomicAdd(&ctr->n_unsettled, (unsigned long long)nuns);
+  // the block's tallies, one atomic each
+  __shared__ uint32_t wt[kWaves][IP_TALLIES];
+  uint32_t tl[IP_TALLIES] = {hits, shits, npts, nuns};
+#pragma unroll
+  for (int k = 0; k < IP_TALLIES; ++k) {
+#pragma unroll
+    for (int off = 32; off; off >>= 1) tl[k] += __shfl_xor(tl[k], off, 64);
+    if (lane == 0) wt[wib][k] = tl[k];
+  }
+  __syncthreads();
+  if (threadIdx.x < IP_TALLIES) {
+    unsigned long long t = 0;
+    for (int w = 0; w < kWaves; ++w) t += wt[w][threadIdx.x];
+    if (t) atomicAdd(&ctr->tally[threadIdx.x][reg * IP_LINE], t);
+  }
+}
+
+// The IP_REGIONS lists of a subdivision launch one after the other: list r
+// (rcap apart, cnt[r * IP_LINE] entries) to out + the lengths before it.
+__global__ __launch_bounds__(256) void gather_regions_kernel(const uint64_t *__restrict__ src, uint64_t rcap,
+                                                             const unsigned long long *__restrict__ cnt,
+                                                             uint64_t *__restrict__ out) {
+  const uint32_t r = blockIdx.y;
+  uint64_t o = 0;
+  for (uint32_t q = 0; q < r; ++q) o += cnt[q * IP_LINE];
+  const uint64_t n = cnt[r * IP_LINE];
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
+    out[o + i] = src[r * rcap + i];
 }
 
 // Ends of the listed edges as raw vertices: vraw[2r] = a, vraw[2r + 1] = b.
@@ -1910,15 +1943,17 @@ int grow_points(ip_ctx *ctx, uint64_t lo, uint64_t hi, double *&pts, uint64_t &l
 // kept <= 1/2) with its keys in insertion order (skeys, capacity et_cap:
 // every key in the set was appended once).  FP64 mode keeps the points of
 // both lists too (dpts, spts, SoA with column strides dld, sld).
+// Each launch's owner-emitted keys arrive in IP_REGIONS lists (rkeys, rcap
+// entries each) and are appended to dkeys from there.
 struct BatchSink {
   ip_ctx *ctx = nullptr;
-  uint64_t *et = nullptr, *skeys = nullptr, *dkeys = nullptr;
-  uint64_t et_cap = 0, dcap = 0;
+  uint64_t *et = nullptr, *skeys = nullptr, *dkeys = nullptr, *rkeys = nullptr;
+  uint64_t et_cap = 0, dcap = 0, rcap = 0;
   double *dpts = nullptr, *spts = nullptr;
   uint64_t dld = 0, sld = 0;
   explicit BatchSink(ip_ctx *c) : ctx(c) {}
   ~BatchSink() {
-    for (void *p : {(void *)et, (void *)skeys, (void *)dkeys, (void *)dpts, (void *)spts})
+    for (void *p : {(void *)et, (void *)skeys, (void *)dkeys, (void *)rkeys, (void *)dpts, (void *)spts})
       if (p) ip_dfree(ctx, p);
   }
   // Grow the set to cap (power of two), rebuilt from its first n keys.
@@ -1952,8 +1987,24 @@ struct BatchSink {
     dcap = cap;
     return IP_OK;
   }
+  // Room for cap keys in each of a launch's lists (their contents go).
+  int reserve_regions(uint64_t cap) {
+    IP_TRY_HIP(ctx, hipStreamSynchronize(ctx->stream));
+    if (rkeys) ip_dfree(ctx, rkeys);
+    rkeys = nullptr;
+    rcap = 0;
+    IP_TRY(alloc(ctx, (void **)&rkeys, cap * IP_REGIONS * 8));
+    rcap = cap;
+    return IP_OK;
+  }
+  void drop_regions() {
+    (void)hipStreamSynchronize(ctx->stream);
+    if (rkeys) ip_dfree(ctx, rkeys);
+    rkeys = nullptr;
+    rcap = 0;
+  }
   SubOut sub_out(const VEnt *cvt, uint64_t cvt_mask) const {
-    return SubOut{cvt, cvt_mask, et, et_cap - 1, skeys, dkeys, dcap};
+    return SubOut{cvt, cvt_mask, et, et_cap - 1, skeys, rkeys, rcap};
   }
   // Final output: the set keys (and FP64 points) appended after the owner
   // keys; hands the key list over.
@@ -1975,12 +2026,13 @@ struct BatchSink {
 };
 
 // Runs `launch` (one subdivision launch) until it neither found the edge set
-// full nor overran the owner list.  Before the first launch the set is grown
-// to keep its load at most 1/2.  After a set overflow the set is grown from
-// its key list (which includes the partial appends of the failed launch) and
-// the launch replayed: set edges already present are skipped.  The owner
-// list is rewound to where the launch started and rewritten by the replay,
-// after growing it to the count the launch reported.
+// full nor overran a list of owner-emitted keys, then appends those lists to
+// the dir_lo keys that the sink holds (c->n_direct; updated).  Before the
+// first launch the set is grown to keep its load at most 1/2.  After a set
+// overflow the set is grown from its key list (which includes the partial
+// appends of the failed launch) and the launch replayed: set edges already
+// present are skipped.  The owner lists are rewritten by the replay, after
+// growing them to the longest that the launch reported.
 template <typename F>
 int run_with_replay(ip_ctx *ctx, BatchSink &g, int64_t &regrows, F launch) {
   Counters *c = ctx->ctr_host;
@@ -1995,18 +2047,34 @@ int run_with_replay(ip_ctx *ctx, BatchSink &g, int64_t &regrows, F launch) {
       IP_TRY(g.reserve_set(pow2_at_least(std::max<uint64_t>(n_keys * 4, g.et_cap * 2)), n_keys));
       ++regrows;
     }
-    IP_TRY(set_counter(ctx, &ctx->ctr_dev->n_direct, dir_lo));
+    static_assert(offsetof(Counters, region) == offsetof(Counters, tally) + sizeof(Counters::tally),
+                  "the tallies and the lists' lengths are cleared together");
+    IP_TRY(fill(ctx, ctx->ctr_dev->tally, (IP_TALLIES + 1) * IP_REGIONS * IP_LINE, 0ull));
     IP_TRY(launch());
     IP_TRY(read_ctr(ctx));
-    const bool dir_over = c->n_direct > g.dcap;
-    if (!c->et_fail && !dir_over) return IP_OK;
+    uint64_t longest = 0;
+    for (int r = 0; r < IP_REGIONS; ++r) longest = std::max<uint64_t>(longest, c->region[r * IP_LINE]);
+    const bool over = longest > g.rcap;
+    if (!c->et_fail && !over) break;
     set_failed = c->et_fail != 0;
     n_keys = c->n_out;
-    if (dir_over) {
-      IP_TRY(g.reserve_direct(c->n_direct + c->n_direct / 4 + 1024, dir_lo));
+    if (over) {
+      IP_TRY(g.reserve_regions(longest + longest / 4 + 1024));
       ++regrows;
     }
   }
+  const uint64_t n = line_sum(c->region);
+  if (n == 0) return IP_OK;
+  if (dir_lo + n > g.dcap) {
+    IP_TRY(g.reserve_direct(dir_lo + n + (dir_lo + n) / 4 + 1024, dir_lo));
+    ++regrows;
+  }
+  hipLaunchKernelGGL(gather_regions_kernel, dim3(grid_for(n / IP_REGIONS, 512), IP_REGIONS), dim3(256), 0, ctx->stream,
+                     (const uint64_t *)g.rkeys, g.rcap, (const unsigned long long *)ctx->ctr_dev->region,
+                     g.dkeys + dir_lo);
+  IP_TRY_HIP(ctx, hipGetLastError());
+  c->n_direct = dir_lo + n;
+  return set_counter(ctx, &ctx->ctr_dev->n_direct, dir_lo + n);
 }
 
 constexpr size_t kSubLdsMax = 64 * 1024;
@@ -2339,6 +2407,7 @@ int init_sink(BatchSink &g, uint64_t nc, int k, double frac = 1.0) {
   double est = (double)nc * std::min(1.0, frac);
   for (int q = 0; q < D - 1; ++q) est *= k;
   IP_TRY(g.reserve_direct((uint64_t)std::min(est * 1.6, 4.0e9) + 1024, 0));
+  IP_TRY(g.reserve_regions((uint64_t)std::min(est * 1.8, 4.0e9) / IP_REGIONS + 65536));
   IP_TRY(g.reserve_set(pow2_at_least((uint64_t)std::min(est * 0.5, 4.0e9)), 0));
   return IP_OK;
 }
@@ -2366,7 +2435,7 @@ int subdivide_fused(ip_ctx *ctx, const ip_problem *p, const SubArgs &a, const ui
   IP_TRY(init_sink<D>(g, nc, p->k, bs ? (double)B / (double)(nsig ? nsig : 1) : 1.0));
   Counters *c = ctx->ctr_host;
   IP_TRY_HIP(ctx, hipMemsetAsync(ctx->ctr_dev, 0, sizeof(Counters), ctx->stream));
-  int64_t regrows = 0, n_fallback = 0, n_settled64 = 0, n_pts = 0, batches = 0;
+  int64_t regrows = 0, n_fallback = 0, n_pts = 0, batches = 0;
   uint64_t set_done = 0;
   Timer tf, tx, tp, ts, tq;
   for (uint64_t b0 = 0; b0 < nsig; b0 += B) {
@@ -2380,21 +2449,15 @@ int subdivide_fused(ip_ctx *ctx, const ip_problem *p, const SubArgs &a, const ui
     if (bs) IP_TRY(set_counter(ctx, &ctx->ctr_dev->n_direct, 0));
     IP_TRY(run_with_replay(ctx, g, regrows, [&]() -> int {
       IP_TRY(zero_field(ctx, &ctx->ctr_dev->n_aux));
-      IP_TRY(zero_field(ctx, &ctx->ctr_dev->n_unsettled));
-      IP_TRY(zero_field(ctx, &ctx->ctr_dev->n_pts));
-      IP_TRY(zero_field(ctx, &ctx->ctr_dev->n_cert64));
-      IP_TRY(zero_field(ctx, &ctx->ctr_dev->n_cof));
-      IP_TRY(zero_field(ctx, &ctx->ctr_dev->n_shared));
       IP_TRY(ts.start(ctx, &st.ms_subdivide));
       IP_TRY((launch_sub<D, 0>(ctx, p, a, sig, nullptr, nb, nullptr, 0, nullptr, g, defer, prep)));
       ++st.subdivide_launches;
       return ts.stop(ctx);
     }));
-    const uint64_t n_def = c->n_aux, n_uns = c->n_unsettled;
-    n_pts += (int64_t)c->n_pts;
-    n_settled64 += (int64_t)c->n_cert64;
-    st.n_edge_hits += (int64_t)c->n_cof;
-    st.n_shared_probes += (int64_t)c->n_shared;
+    const uint64_t n_def = c->n_aux, n_uns = line_sum(c->tally[IP_T_UNSETTLED]);
+    n_pts += (int64_t)line_sum(c->tally[IP_T_POINTS]);
+    st.n_edge_hits += (int64_t)line_sum(c->tally[IP_T_HITS]);
+    st.n_shared_probes += (int64_t)line_sum(c->tally[IP_T_SHARED]);
     if (n_def) {
       // canonical FP64 for the points no certified tier settled
       const uint64_t fcap = pow2_at_least(2 * n_uns + 1024);
@@ -2417,15 +2480,13 @@ int subdivide_fused(ip_ctx *ctx, const ip_problem *p, const SubArgs &a, const ui
       IP_TRY(tf.stop(ctx));
       n_fallback += (int64_t)n_ev;
       IP_TRY(run_with_replay(ctx, g, regrows, [&]() -> int {
-        IP_TRY(zero_field(ctx, &ctx->ctr_dev->n_cof));
-        IP_TRY(zero_field(ctx, &ctx->ctr_dev->n_shared));
         IP_TRY(ts.start(ctx, &st.ms_subdivide));
         IP_TRY((launch_sub<D, 2>(ctx, p, a, sig, defer, n_def, fvt, fcap - 1, nullptr, g, nullptr, prep)));
         ++st.subdivide_launches;
         return ts.stop(ctx);
       }));
-      st.n_edge_hits += (int64_t)c->n_cof;
-      st.n_shared_probes += (int64_t)c->n_shared;
+      st.n_edge_hits += (int64_t)line_sum(c->tally[IP_T_HITS]);
+      st.n_shared_probes += (int64_t)line_sum(c->tally[IP_T_SHARED]);
       if (c->vt_fail) return ip_fail(ctx, IP_EDEVICE, "fallback vertex missing from its table");
     }
     st.n_template_edges += (int64_t)(nb * (uint64_t)NE);
@@ -2457,10 +2518,10 @@ int subdivide_fused(ip_ctx *ctx, const ip_problem *p, const SubArgs &a, const ui
     st.n_vertices += n_pts;
     st.regrows += regrows;
     st.n_fallback += n_fallback;
-    st.n_settled64 += n_settled64;
-    return IP_OK;
+      return IP_OK;
   }
   const uint64_t n_dir = c->n_direct, n_set = c->n_out, n = n_dir + n_set;
+  g.drop_regions();
   IP_TRY(g.assemble<D>(n_dir, n_set, false));
   double *pts = nullptr;
   uint64_t ld = 0;
@@ -2489,7 +2550,6 @@ int subdivide_fused(ip_ctx *ctx, const ip_problem *p, const SubArgs &a, const ui
   st.n_vertices += n_pts;
   st.regrows += regrows;
   st.n_fallback += n_fallback;
-  st.n_settled64 += n_settled64;
   return IP_OK;
 }
 
@@ -2523,21 +2583,32 @@ int subdivide_table(ip_ctx *ctx, const ip_problem *p, const SubArgs &a, const ui
   f.p = p;
   f.tb = &ctx->vtf;
   f.L = p->fine;
-  const uint64_t vcap = std::min<uint64_t>(vcap_b, pow2_at_least(B * (uint64_t)NP * 2));
-  IP_TRY(ip_ensure(ctx, ctx->vtf.keys, vcap * sizeof(VEnt)));
-  IP_TRY(ip_ensure(ctx, ctx->vtf.eval, vcap * 4));
-  IP_TRY(ip_ensure(ctx, ctx->vt_aux, B * (uint64_t)NP * 4));
-  f.vt = (VEnt *)ctx->vtf.keys.p;
-  f.eval = (uint32_t *)ctx->vtf.eval.p;
-  f.vt_cap = vcap;
-  f.cert = cert;
-  if (cert) {
+  // Simplices share their fine vertices (d = 6: 186 template points per
+  // distinct vertex at k = 2, 14 at k = 4), so the table starts at an eighth
+  // of a slot per template point and grows when its load passes 1/2, up to
+  // two slots per point: clearing and probing it costs by its size (at k = 2,
+  // 2.6 M simplices in 3 batches: 1.09 ms of clearing at two slots per point,
+  // and every probe a line from memory).
+  const uint64_t vcap_max = std::min<uint64_t>(vcap_b, pow2_at_least(B * (uint64_t)NP * 2));
+  uint64_t vcap = 0;
+  auto set_table = [&](uint64_t cap) -> int {
+    vcap = cap;
+    IP_TRY(ip_ensure(ctx, ctx->vtf.keys, vcap * sizeof(VEnt)));
+    IP_TRY(ip_ensure(ctx, ctx->vtf.eval, vcap * 4));
+    f.vt = (VEnt *)ctx->vtf.keys.p;
+    f.eval = (uint32_t *)ctx->vtf.eval.p;
+    f.vt_cap = vcap;
+    if (!cert) return IP_OK;
     IP_TRY(ip_ensure(ctx, ctx->vtf.vals, vcap * 4));
     IP_TRY(ip_ensure(ctx, ctx->vtf.fb, vcap * 4));
     f.vb = (float *)ctx->vtf.vals.p;
     f.fb = (uint32_t *)ctx->vtf.fb.p;
     f.fb_cap = ctx->vtf.fb.bytes / 4;
-  }
+    return IP_OK;
+  };
+  f.cert = cert;
+  IP_TRY(set_table(std::min<uint64_t>(vcap_max, pow2_at_least(B * (uint64_t)NP / 8))));
+  IP_TRY(ip_ensure(ctx, ctx->vt_aux, B * (uint64_t)NP * 4));
   uint32_t *pslot = (uint32_t *)ctx->vt_aux.p;
   DevTmp prep_hold(ctx);
   IP_TRY(prep_hold.get(B * sizeof(SubPrep<D>)));
@@ -2556,14 +2627,22 @@ int subdivide_table(ip_ctx *ctx, const ip_problem *p, const SubArgs &a, const ui
     IP_TRY(tq.start(ctx, &st.ms_prep));
     IP_TRY(launch_prep<D>(ctx, p, a, sig, nb, false, prep));
     IP_TRY(tq.stop(ctx));
-    IP_TRY(fill_vt(ctx, f.vt, vcap));
-    IP_TRY(zero_field(ctx, &ctx->ctr_dev->n_eval));
-    IP_TRY(tx.start(ctx, &st.ms_expand));
-    hipLaunchKernelGGL((batch_vertices_kernel<D>), dim3(grid_for(nb * NP)), dim3(kBlock), 0, ctx->stream, p->fine,
-                       p->coarse, a.LB, k, sig, nb, a.tpts, NP, f.vt, vcap - 1, f.eval, pslot, ctx->ctr_dev);
-    IP_TRY_HIP(ctx, hipGetLastError());
-    IP_TRY(tx.stop(ctx));
-    IP_TRY(read_ctr(ctx));
+    for (;;) {
+      IP_TRY(fill_vt(ctx, f.vt, vcap));
+      IP_TRY(zero_field(ctx, &ctx->ctr_dev->n_eval));
+      IP_TRY(tx.start(ctx, &st.ms_expand));
+      hipLaunchKernelGGL((batch_vertices_kernel<D>), dim3(grid_for(nb * NP, 2048)), dim3(kBlock), 0, ctx->stream,
+                         p->fine, p->coarse, a.LB, k, sig, nb, a.tpts, NP, f.vt, vcap - 1, f.eval, pslot,
+                         ctx->ctr_dev);
+      IP_TRY_HIP(ctx, hipGetLastError());
+      IP_TRY(tx.stop(ctx));
+      IP_TRY(read_ctr(ctx));
+      if (vcap == vcap_max || (!c->vt_fail && c->n_eval * 2 <= vcap)) break;
+      // fuller than 1/2: a larger table, and the batch's vertices again
+      IP_TRY(zero_fail_flags(ctx));
+      IP_TRY(set_table(std::min<uint64_t>(vcap_max, std::max<uint64_t>(vcap * 4, pow2_at_least(c->n_eval * 4)))));
+      ++f.regrows;
+    }
     if (c->vt_fail) return ip_fail(ctx, IP_ENOMEM, "batch vertex table overflow");
     const uint64_t n_ev = c->n_eval;
     IP_TRY(tf.start(ctx, &st.ms_feval));
@@ -2573,15 +2652,13 @@ int subdivide_table(ip_ctx *ctx, const ip_problem *p, const SubArgs &a, const ui
     // per-batch mode: the owner list starts empty for every batch
     if (bs) IP_TRY(set_counter(ctx, &ctx->ctr_dev->n_direct, 0));
     IP_TRY(run_with_replay(ctx, g, f.regrows, [&]() -> int {
-      IP_TRY(zero_field(ctx, &ctx->ctr_dev->n_cof));
-      IP_TRY(zero_field(ctx, &ctx->ctr_dev->n_shared));
       IP_TRY(ts.start(ctx, &st.ms_subdivide));
       IP_TRY((launch_sub<D, 3>(ctx, p, a, sig, nullptr, nb, f.vt, vcap - 1, nullptr, g, nullptr, prep, pslot)));
       ++st.subdivide_launches;
       return ts.stop(ctx);
     }));
-    st.n_edge_hits += (int64_t)c->n_cof;
-    st.n_shared_probes += (int64_t)c->n_shared;
+    st.n_edge_hits += (int64_t)line_sum(c->tally[IP_T_HITS]);
+    st.n_shared_probes += (int64_t)line_sum(c->tally[IP_T_SHARED]);
     st.n_template_edges += (int64_t)(nb * (uint64_t)NE);
     const uint64_t dir_hi = c->n_direct, set_hi = c->n_out;
     if (log_on())
@@ -2658,6 +2735,7 @@ int subdivide_table(ip_ctx *ctx, const ip_problem *p, const SubArgs &a, const ui
     st.n_settled64 += f.n_settled64;
     return IP_OK;
   }
+  g.drop_regions();
   IP_TRY(g.assemble<D>(dir_done, set_done, true));
   IP_TRY(tf.flush(ctx));
   IP_TRY(tx.flush(ctx));
@@ -2742,7 +2820,7 @@ int trace_batch(ip_ctx *ctx, const ip_problem *p, uint64_t budget, bool cert, ip
     Timer tsg;
     if (nc) {
       IP_TRY(tsg.start(ctx, &st.ms_sigma));
-      hipLaunchKernelGGL((sigma_kernel<D>), dim3(grid_for(nc * 4, 8192)), dim3(kBlock), 0, ctx->stream, p->coarse, LB,
+      hipLaunchKernelGGL((sigma_kernel<D>), dim3(512), dim3(kExpand), 0, ctx->stream, p->coarse, LB,
                          coarse_edges, nc, (uint64_t *)sig_tab, cap - 1, (uint64_t *)sig_list, ctx->ctr_dev);
       IP_TRY_HIP(ctx, hipGetLastError());
       IP_TRY(tsg.stop(ctx));
