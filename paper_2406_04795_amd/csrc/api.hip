@@ -349,7 +349,8 @@ int ip_create(ip_ctx **out, int device, void *stream) {
   ctx->stream = (hipStream_t)stream;
   hipError_t e = hipSetDevice(device);
   if (e == hipSuccess) e = hipMalloc((void **)&ctx->ctr_dev, sizeof(Counters));
-  if (e == hipSuccess) e = hipHostMalloc((void **)&ctx->ctr_host, 3 * sizeof(Counters), hipHostMallocDefault);
+  if (e == hipSuccess)
+    e = hipHostMalloc((void **)&ctx->ctr_host, 3 * sizeof(Counters) + kSceneSlots * kSceneSlot, hipHostMallocDefault);
   if (e == hipSuccess) e = hipEventCreate(&ctx->ev0);
   if (e == hipSuccess) e = hipEventCreate(&ctx->ev1);
   for (hipEvent_t &ev : ctx->ctr_ev)
@@ -367,6 +368,7 @@ int ip_create(ip_ctx **out, int device, void *stream) {
     return IP_EDEVICE;
   }
   memset(ctx->ctr_host, 0, 3 * sizeof(Counters));
+  ctx->scene_stage = (unsigned char *)(ctx->ctr_host + 3);
   if (ip_noalloc_setup(ctx) != IP_OK) {
     (void)hipFree(ctx->ctr_dev);
     (void)hipHostFree(ctx->ctr_host);

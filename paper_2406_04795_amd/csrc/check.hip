@@ -367,6 +367,10 @@ __global__ __launch_bounds__(256, 4) void check_kernel(SceneDev S, const double 
   }
 }
 
+// Doubles of a scene that check_sphere_kernel stages: 24 KiB, so that six
+// blocks share a CU's LDS.
+constexpr int kSceneLds = 3072;
+
 // Sphere-parallel layout (Sec. V-C: threads over the robot's spheres, then
 // over configurations), for batches too small to fill the device with one
 // lane per configuration: a group of NSP consecutive lanes (NSP a power of
@@ -376,10 +380,32 @@ __global__ __launch_bounds__(256, 4) void check_kernel(SceneDev S, const double 
 // the per-configuration kernel, and tests its sphere against every obstacle;
 // the group's hits are ORed with a ballot and its first lane writes the
 // verdict.  Robots with capsules use the per-configuration kernel.
-template <int NSP>
+// The scene (all of it up to the culling rows, and the integers) is staged
+// into LDS first: read from memory wave-uniformly, every joint and obstacle
+// is one more serial miss of the scalar cache.
+template <int NSP, bool LDS>
 __global__ __launch_bounds__(256) void check_sphere_kernel(SceneDev S, int n_lsph, const double *__restrict__ q,
                                                            int64_t n, int64_t ld, uint8_t *__restrict__ verdict) {
   constexpr int GPW = 64 / NSP;  // configurations per wave
+  __shared__ __align__(16) double sd[LDS ? kSceneLds : 1];
+  __shared__ int32_t si[LDS ? 3 * IP_MAX_D + 1 : 1];
+  const double *jT = S.joint_T, *lsph = S.lsph, *osph = S.osph, *obox = S.obox, *ocyl = S.ocyl;
+  const int32_t *axis = S.joint_axis, *pure = S.joint_pure, *loff = S.lsph_off;
+  if (LDS) {
+    // joint_T, lsph, (lcap), osph, obox, ocyl lie one after the other
+    const int nd = (int)(S.ocyl + 16 * S.n_ocyl - S.joint_T);
+    for (int i = threadIdx.x; i < nd; i += 256) sd[i] = S.joint_T[i];
+    for (int i = threadIdx.x; i < 3 * S.nj + 1; i += 256) si[i] = S.joint_axis[i];
+    __syncthreads();
+    lsph = sd + (S.lsph - S.joint_T);
+    osph = sd + (S.osph - S.joint_T);
+    obox = sd + (S.obox - S.joint_T);
+    ocyl = sd + (S.ocyl - S.joint_T);
+    jT = sd;
+    axis = si;
+    pure = si + (S.joint_pure - S.joint_axis);
+    loff = si + (S.lsph_off - S.joint_axis);
+  }
   const int lane = threadIdx.x & 63;
   const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int64_t n_waves = ((int64_t)gridDim.x * blockDim.x) >> 6;
@@ -389,19 +415,20 @@ __global__ __launch_bounds__(256) void check_sphere_kernel(SceneDev S, int n_lsp
     bool hit = false;
     if (c < n && a < n_lsph) {
       int li = 0;
-      while (li + 1 < S.nj && S.lsph_off[li + 1] <= a) ++li;
+      while (li + 1 < S.nj && loff[li + 1] <= a) ++li;
       double T[12] = {1, 0, 0, 0, 0, 1, 0, 0, 0, 0, 1, 0};
       for (int j = 0; j <= li; ++j) {
         double sn_, cs_;
         sincos_own(q[(int64_t)j * ld + c], &sn_, &cs_);
-        fk_step(T, S.joint_T + 12 * j, S.joint_pure[j] != 0, S.joint_axis[j], sn_, cs_);
+        fk_step(T, jT + 12 * j, pure[j] != 0, axis[j], sn_, cs_);
       }
-      const double *sp = S.lsph + 4 * a;
+      const double *sp = lsph + 4 * a;
       double cw[3];
       xform(T, sp, cw);
-      for (int b = 0; b < S.n_osph && !hit; ++b) hit = sphere_sphere(cw, sp[3], S.osph + 4 * b, S.osph[4 * b + 3]);
-      for (int b = 0; b < S.n_obox && !hit; ++b) hit = sphere_box(cw, sp[3], S.obox + 16 * b);
-      for (int b = 0; b < S.n_ocyl && !hit; ++b) hit = sphere_cyl(cw, sp[3], S.ocyl + 16 * b);
+      const double r = sp[3];
+      for (int b = 0; b < S.n_osph && !hit; ++b) hit = sphere_sphere(cw, r, osph + 4 * b, osph[4 * b + 3]);
+      for (int b = 0; b < S.n_obox && !hit; ++b) hit = sphere_box(cw, r, obox + 16 * b);
+      for (int b = 0; b < S.n_ocyl && !hit; ++b) hit = sphere_cyl(cw, r, ocyl + 16 * b);
     }
     const uint64_t bal = __ballot(hit);
     const uint64_t gmask = (NSP == 64 ? ~0ull : ((1ull << NSP) - 1ull)) << (g * NSP);
@@ -410,20 +437,31 @@ __global__ __launch_bounds__(256) void check_sphere_kernel(SceneDev S, int n_lsp
 }
 
 // Launches the verdict kernel for n configurations: the sphere-parallel
-// layout when one lane per configuration would start fewer than 8192 waves
-// and the robot is made of at most 64 spheres, else the per-configuration
-// kernel.
+// layout when the robot is made of at most 64 spheres and its lanes start
+// fewer than 8192 waves, else the per-configuration kernel.  The first pays
+// the kinematics once per sphere and does not cull, but has no serial chain
+// over links and obstacles; the second takes about the same time up to
+// 256 000 configurations.  Both in us for 18 spheres (32 lanes) against 16
+// obstacles: 6000 configurations 19 and 33, 16 000: 30 and 32, 64 000: 88 and
+// 31, 500 000: 603 and 51; for 8 spheres: 64 000: 24 and 30, 128 000: 38 and
+// 32.
 int launch_check(ip_ctx *ctx, const SceneDev &S, int n_lsph, int n_lcap, const double *q, int64_t n, int64_t ld,
                  uint8_t *verdict) {
   if (n == 0) return IP_OK;
-  if (n_lcap == 0 && n_lsph > 0 && n_lsph <= 64 && n < 8192 * 64) {
-    int nsp = 1;
-    while (nsp < n_lsph) nsp <<= 1;
+  int nsp = 1;
+  while (nsp < n_lsph && nsp < 64) nsp <<= 1;
+  if (n_lcap == 0 && n_lsph > 0 && n_lsph <= 64 && n < 8192 * 64 / nsp) {
     const int64_t per_block = 4 * (64 / nsp);
     const int64_t blocks = std::min<int64_t>((n + per_block - 1) / per_block, 65536);
-#define IP_CS(NN)                                                                                              \
-  hipLaunchKernelGGL((check_sphere_kernel<NN>), dim3((unsigned)blocks), dim3(256), 0, ctx->stream, S, n_lsph, q, \
+    const bool lds = S.ocyl + 16 * S.n_ocyl - S.joint_T <= kSceneLds;
+#define IP_CSK(NN, LL)                                                                                            \
+  hipLaunchKernelGGL((check_sphere_kernel<NN, LL>), dim3((unsigned)blocks), dim3(256), 0, ctx->stream, S, n_lsph, q, \
                      n, ld, verdict)
+#define IP_CS(NN)       \
+  if (lds)              \
+    IP_CSK(NN, true);   \
+  else                  \
+    IP_CSK(NN, false)
     switch (nsp) {
       case 1: IP_CS(1); break;
       case 2: IP_CS(2); break;
@@ -434,6 +472,7 @@ int launch_check(ip_ctx *ctx, const SceneDev &S, int n_lsph, int n_lcap, const d
       default: IP_CS(64); break;
     }
 #undef IP_CS
+#undef IP_CSK
   } else {
     int64_t blocks = (n + 255) / 256;
     if (blocks > 65536) blocks = 65536;
@@ -514,6 +553,10 @@ __global__ __launch_bounds__(256) void free_scatter_kernel(const uint8_t *__rest
     pos0 += wcount[0] + wcount[1] + wcount[2] + wcount[3];
     __syncthreads();
   }
+}
+
+__global__ __launch_bounds__(1024) void scene_copy_kernel(const uint32_t *src, uint32_t *dst, uint32_t n) {
+  for (uint32_t i = threadIdx.x; i < n; i += 1024) dst[i] = src[i];
 }
 
 int upload_scene(ip_ctx *ctx, const ip_scene *sc, SceneDev *out) {
@@ -692,12 +735,29 @@ int upload_scene(ip_ctx *ctx, const ip_scene *sc, SceneDev *out) {
   ints.insert(ints.end(), lsph_off.begin(), lsph_off.end());
   size_t o_lco = ints.size();
   ints.insert(ints.end(), lcap_off.begin(), lcap_off.end());
-  size_t bytes = n_dbl * 8 + ints.size() * 4;
+  const size_t bytes = n_dbl * 8 + ints.size() * 4;
   IP_TRY(ip_ensure(ctx, ctx->scene, bytes));
   char *base = (char *)ctx->scene.p;
-  IP_TRY_HIP(ctx, hipMemcpyAsync(base, blob.data(), n_dbl * 8, hipMemcpyHostToDevice, ctx->stream));
-  IP_TRY_HIP(ctx, hipMemcpyAsync(base + n_dbl * 8, ints.data(), ints.size() * 4, hipMemcpyHostToDevice, ctx->stream));
-  IP_TRY_HIP(ctx, hipStreamSynchronize(ctx->stream));
+  if (bytes <= kSceneSlot) {
+    // from a page-locked slot, read by a kernel: nothing waits for the device
+    // (two pageable copies and the wait for them were 25 us of a 41 us check
+    // of 1500 configurations)
+    if (ctx->scene_next == kSceneSlots) {
+      IP_TRY_HIP(ctx, hipStreamSynchronize(ctx->stream));
+      ctx->scene_next = 0;
+    }
+    unsigned char *slot = ctx->scene_stage + kSceneSlot * ctx->scene_next++;
+    memcpy(slot, blob.data(), n_dbl * 8);
+    memcpy(slot + n_dbl * 8, ints.data(), ints.size() * 4);
+    hipLaunchKernelGGL(scene_copy_kernel, dim3(1), dim3(1024), 0, ctx->stream, (const uint32_t *)slot,
+                       (uint32_t *)base, (uint32_t)(bytes / 4));
+    IP_TRY_HIP(ctx, hipGetLastError());
+  } else {
+    IP_TRY_HIP(ctx, hipMemcpyAsync(base, blob.data(), n_dbl * 8, hipMemcpyHostToDevice, ctx->stream));
+    IP_TRY_HIP(ctx,
+               hipMemcpyAsync(base + n_dbl * 8, ints.data(), ints.size() * 4, hipMemcpyHostToDevice, ctx->stream));
+    IP_TRY_HIP(ctx, hipStreamSynchronize(ctx->stream));
+  }
   const double *db = (const double *)base;
   const int32_t *ib = (const int32_t *)(base + n_dbl * 8);
   out->nj = nj;

@@ -704,6 +704,11 @@ struct ip_ctx {
   VtBufs vtf, vtc;
   DevBuf vt_aux, scratch;
   DevBuf scene;
+  // page-locked slots that scenes are uploaded from (behind ctr_host in its
+  // allocation): a slot is written again kSceneSlots uploads later, after a
+  // wait for the stream once per round
+  unsigned char *scene_stage = nullptr;
+  uint32_t scene_next = 0;
   DevCache cache;
   // this device's copy of the scratch array of ip_feval_noalloc
   void *noalloc_scratch = nullptr;
@@ -719,6 +724,9 @@ struct ip_ctx {
   void *dev_stage[2] = {nullptr, nullptr};
   size_t dev_stage_bytes[2] = {0, 0};
 };
+
+constexpr uint32_t kSceneSlots = 16;
+constexpr size_t kSceneSlot = 32 * 1024;
 
 struct ip_problem {
   ip_ctx *ctx = nullptr;

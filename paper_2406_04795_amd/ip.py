@@ -53,13 +53,14 @@ class ip_space(C.Structure):
 
 
 class ip_scene(C.Structure):
-    _fields_ = [("n_joints", C.c_int32), ("joint_T", _dp), ("joint_axis", _ip),
-                ("n_lsph", C.c_int32), ("lsph_link", _ip), ("lsph_c", _dp), ("lsph_r", _dp),
-                ("n_lcap", C.c_int32), ("lcap_link", _ip), ("lcap_p0", _dp), ("lcap_p1", _dp),
-                ("lcap_r", _dp),
-                ("n_osph", C.c_int32), ("osph_c", _dp), ("osph_r", _dp),
-                ("n_obox", C.c_int32), ("obox_T", _dp), ("obox_l", _dp),
-                ("n_ocyl", C.c_int32), ("ocyl_T", _dp), ("ocyl_rh", _dp)]
+    # array addresses as plain integers (see _scene_struct)
+    _fields_ = [("n_joints", C.c_int32), ("joint_T", _vp), ("joint_axis", _vp),
+                ("n_lsph", C.c_int32), ("lsph_link", _vp), ("lsph_c", _vp), ("lsph_r", _vp),
+                ("n_lcap", C.c_int32), ("lcap_link", _vp), ("lcap_p0", _vp), ("lcap_p1", _vp),
+                ("lcap_r", _vp),
+                ("n_osph", C.c_int32), ("osph_c", _vp), ("osph_r", _vp),
+                ("n_obox", C.c_int32), ("obox_T", _vp), ("obox_l", _vp),
+                ("n_ocyl", C.c_int32), ("ocyl_T", _vp), ("ocyl_rh", _vp)]
 
 
 class ip_stats(C.Structure):
@@ -280,15 +281,26 @@ def ip_cells_free(cells):
     _lib.ip_cells_free(cells)
 
 
+def _pack(keep, arrays, dtype):
+    """The arrays' values one after the other in one buffer, and the address
+    of each (asking numpy for 17 addresses took as long as a small check)."""
+    flat = [np.asarray(a, dtype).ravel() for a in arrays]
+    buf = np.concatenate(flat)
+    keep.append(buf)
+    at, out, size = buf.ctypes.data, [], buf.itemsize
+    for a in flat:
+        out.append(at)
+        at += a.size * size
+    return out
+
+
 def _scene_struct(sc, keep):
-    n = int(sc.joint_T.shape[0])
-    return ip_scene(n, _d(keep, sc.joint_T), _i(keep, sc.joint_axis),
-                    len(sc.lsph_r), _i(keep, sc.lsph_link), _d(keep, sc.lsph_c), _d(keep, sc.lsph_r),
-                    len(sc.lcap_r), _i(keep, sc.lcap_link), _d(keep, sc.lcap_p0),
-                    _d(keep, sc.lcap_p1), _d(keep, sc.lcap_r),
-                    len(sc.osph_r), _d(keep, sc.osph_c), _d(keep, sc.osph_r),
-                    len(sc.obox_l), _d(keep, sc.obox_T), _d(keep, sc.obox_l),
-                    len(sc.ocyl_rh), _d(keep, sc.ocyl_T), _d(keep, sc.ocyl_rh))
+    jT, lc, lr, p0, p1, cr, oc, orr, bT, bl, cT, ch = _pack(
+        keep, (sc.joint_T, sc.lsph_c, sc.lsph_r, sc.lcap_p0, sc.lcap_p1, sc.lcap_r, sc.osph_c, sc.osph_r,
+               sc.obox_T, sc.obox_l, sc.ocyl_T, sc.ocyl_rh), np.float64)
+    ja, ll, cl = _pack(keep, (sc.joint_axis, sc.lsph_link, sc.lcap_link), np.int32)
+    return ip_scene(int(sc.joint_T.shape[0]), jT, ja, len(sc.lsph_r), ll, lc, lr, len(sc.lcap_r), cl, p0, p1, cr,
+                    len(sc.osph_r), oc, orr, len(sc.obox_l), bT, bl, len(sc.ocyl_rh), cT, ch)
 
 
 def ip_check(ctx, scene, q_dev_ptr: int, n: int, ld: int, verdict_dev_ptr: int):
