@@ -738,7 +738,11 @@ int upload_scene(ip_ctx *ctx, const ip_scene *sc, SceneDev *out) {
   const size_t bytes = n_dbl * 8 + ints.size() * 4;
   IP_TRY(ip_ensure(ctx, ctx->scene, bytes));
   char *base = (char *)ctx->scene.p;
-  if (bytes <= kSceneSlot) {
+  // (a capture keeps the synchronous path, which it refuses: a replay would
+  // read a slot that later uploads have overwritten)
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (ctx->stream) IP_TRY_HIP(ctx, hipStreamIsCapturing(ctx->stream, &cap));
+  if (bytes <= kSceneSlot && cap == hipStreamCaptureStatusNone) {
     // from a page-locked slot, read by a kernel: nothing waits for the device
     // (two pageable copies and the wait for them were 25 us of a 41 us check
     // of 1500 configurations)

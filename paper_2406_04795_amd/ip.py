@@ -53,14 +53,18 @@ class ip_space(C.Structure):
 
 
 class ip_scene(C.Structure):
-    # array addresses as plain integers (see _scene_struct)
-    _fields_ = [("n_joints", C.c_int32), ("joint_T", _vp), ("joint_axis", _vp),
-                ("n_lsph", C.c_int32), ("lsph_link", _vp), ("lsph_c", _vp), ("lsph_r", _vp),
-                ("n_lcap", C.c_int32), ("lcap_link", _vp), ("lcap_p0", _vp), ("lcap_p1", _vp),
-                ("lcap_r", _vp),
-                ("n_osph", C.c_int32), ("osph_c", _vp), ("osph_r", _vp),
-                ("n_obox", C.c_int32), ("obox_T", _vp), ("obox_l", _vp),
-                ("n_ocyl", C.c_int32), ("ocyl_T", _vp), ("ocyl_rh", _vp)]
+    _fields_ = [("n_joints", C.c_int32), ("joint_T", _dp), ("joint_axis", _ip),
+                ("n_lsph", C.c_int32), ("lsph_link", _ip), ("lsph_c", _dp), ("lsph_r", _dp),
+                ("n_lcap", C.c_int32), ("lcap_link", _ip), ("lcap_p0", _dp), ("lcap_p1", _dp),
+                ("lcap_r", _dp),
+                ("n_osph", C.c_int32), ("osph_c", _dp), ("osph_r", _dp),
+                ("n_obox", C.c_int32), ("obox_T", _dp), ("obox_l", _dp),
+                ("n_ocyl", C.c_int32), ("ocyl_T", _dp), ("ocyl_rh", _dp)]
+
+
+class _SceneArgs(C.Structure):
+    # ip_scene with plain integers for the array addresses
+    _fields_ = [(name, _vp if t in (_dp, _ip) else t) for name, t in ip_scene._fields_]
 
 
 class ip_stats(C.Structure):
@@ -299,8 +303,9 @@ def _scene_struct(sc, keep):
         keep, (sc.joint_T, sc.lsph_c, sc.lsph_r, sc.lcap_p0, sc.lcap_p1, sc.lcap_r, sc.osph_c, sc.osph_r,
                sc.obox_T, sc.obox_l, sc.ocyl_T, sc.ocyl_rh), np.float64)
     ja, ll, cl = _pack(keep, (sc.joint_axis, sc.lsph_link, sc.lcap_link), np.int32)
-    return ip_scene(int(sc.joint_T.shape[0]), jT, ja, len(sc.lsph_r), ll, lc, lr, len(sc.lcap_r), cl, p0, p1, cr,
-                    len(sc.osph_r), oc, orr, len(sc.obox_l), bT, bl, len(sc.ocyl_rh), cT, ch)
+    args = _SceneArgs(int(sc.joint_T.shape[0]), jT, ja, len(sc.lsph_r), ll, lc, lr, len(sc.lcap_r), cl, p0, p1, cr,
+                      len(sc.osph_r), oc, orr, len(sc.obox_l), bT, bl, len(sc.ocyl_rh), cT, ch)
+    return ip_scene.from_buffer(args)  # the same memory
 
 
 def ip_check(ctx, scene, q_dev_ptr: int, n: int, ld: int, verdict_dev_ptr: int):
