@@ -166,6 +166,59 @@ __device__ __forceinline__ double sv_term(const FDev &F, const double *sv, const
   }
 }
 
+// The sums of alpha times the term over the support vectors at R points per
+// lane of a 256-thread block, in index order.  The records pass through LDS
+// in tiles of kRecTile (the next one in flight meanwhile), each read at one
+// address by the whole wave and used for R points; U records at a time, so
+// that U R chains overlap.  Every thread of the block must call it.
+constexpr int kRecTile = 64;
+
+template <int D, int P, int R, int U>
+__device__ __forceinline__ void tile_sum(const FDev &F, double (*tile)[kRecTile * 8], const double (*x)[D], double *acc) {
+  const int64_t nd = F.S * 8;
+  const int64_t nt = (F.S + kRecTile - 1) / kRecTile;
+#pragma unroll
+  for (int r = 0; r < R; ++r) acc[r] = 0.0;
+  double2 nx;
+  auto fetch = [&](int64_t t) {
+    const int64_t o = t * kRecTile * 8 + threadIdx.x * 2;
+    nx = o < nd ? *(const double2 *)(F.rec + o) : make_double2(0.0, 0.0);
+  };
+  fetch(0);
+  __syncthreads();
+  for (int64_t t = 0; t < nt; ++t) {
+    *(double2 *)&tile[t & 1][threadIdx.x * 2] = nx;
+    __syncthreads();
+    if (t + 1 < nt) fetch(t + 1);
+    const double *tl = tile[t & 1];
+    const int m = (int)(F.S - t * kRecTile < kRecTile ? F.S - t * kRecTile : kRecTile);
+    int s = 0;
+    for (; s + U <= m; s += U) {
+      double tp[U][R], al[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        double sv[8];
+#pragma unroll
+        for (int j = 0; j < (D + 2) / 2; ++j) {
+          const double2 z = *(const double2 *)&tl[(s + u) * 8 + 2 * j];
+          sv[2 * j] = z.x;
+          sv[2 * j + 1] = z.y;
+        }
+        al[u] = sv[D];
+#pragma unroll
+        for (int r = 0; r < R; ++r) tp[u][r] = sv_term<D, P>(F, sv, x[r]);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int r = 0; r < R; ++r) acc[r] = fma(al[u], tp[u][r], acc[r]);
+    }
+    for (; s < m; ++s)
+#pragma unroll
+      for (int r = 0; r < R; ++r) acc[r] = fma(tl[s * 8 + D], sv_term<D, P>(F, tl + s * 8, x[r]), acc[r]);
+  }
+}
+
 // FP32 monomial-basis form of f (see feval.hip).  c[0] is the constant term
 // (bias included), c[1..M-1] the monomial coefficients in depth-first order.
 // For every vertex in the domain: |f32 - F| <= K32 * S_abs + E0, with S_abs

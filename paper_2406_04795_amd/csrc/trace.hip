@@ -436,10 +436,12 @@ __device__ __forceinline__ void need_fp64(uint64_t i, uint64_t sa, uint64_t sb, 
 // Points of the traced edges, f read from the slots carried by the edges.
 // REDO = false: all edges (also clears the sign bits into keys);
 // REDO = true : the edges listed in redo, after their ends went to FP64.
+// ends: f at the two ends into the first two columns instead (see
+// refine_kernel).
 template <int D, bool REDO>
 __global__ void points_kernel(LatDev L, const OutRec *out, uint64_t n, const VEnt *vt, uint64_t *keys, double *pts,
                               int64_t ld, bool cert, const float *vb, PolyDev Q, uint64_t *redo, uint32_t *fb,
-                              uint32_t *qb, Counters *ctr) {
+                              uint32_t *qb, Counters *ctr, bool ends) {
   for (uint64_t q = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n; q += (uint64_t)gridDim.x * blockDim.x) {
     const uint64_t i = REDO ? redo[q] : q;
     const OutRec o = out[i];
@@ -451,6 +453,11 @@ __global__ void points_kernel(LatDev L, const OutRec *out, uint64_t n, const VEn
 #pragma unroll
     for (int j = 0; j < D; ++j) b[j] = a[j] + (int32_t)((R >> j) & 1u);
     const uint64_t sa = o.slots & 0xffffffffull, sb = o.slots >> 32;
+    if (ends) {
+      pts[i] = vt[sa].f;
+      pts[ld + (int64_t)i] = vt[sb].f;
+      continue;
+    }
     double p[D];
     const bool ok = edge_point<D>(L, Q, a, b, vt[sa].f, vt[sb].f, cert && !REDO, cert ? vb[sa] : -1.0f,
                                   cert ? vb[sb] : -1.0f, p);
@@ -1150,10 +1157,11 @@ __global__ __launch_bounds__(kBlock) void batch_vertices_kernel(LatDev Lf, LatDe
 // ends in the batch vertex table: canonical FP64 values, or (CERT) the
 // FP32-tier values with their bounds vb, an edge whose point the bound
 // cannot place within tolerance listed in redo (by its index in keys).
+// ends: f at the two ends into the first two columns instead.
 template <int D, bool CERT>
 __global__ void batch_points_kernel(LatDev L, const uint64_t *keys, uint64_t lo, uint64_t hi, const VEnt *vt,
                                     const float *vb, uint64_t vt_mask, double *pts, int64_t ld, PolyDev Q,
-                                    uint64_t *redo, Counters *ctr) {
+                                    uint64_t *redo, Counters *ctr, bool ends) {
   for (uint64_t i = lo + (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < hi; i += (uint64_t)gridDim.x * blockDim.x) {
     int32_t a[D], b[D];
     uint32_t R;
@@ -1164,6 +1172,11 @@ __global__ void batch_points_kernel(LatDev L, const uint64_t *keys, uint64_t lo,
     const int64_t hb = vt_find(vt, vt_mask, vpack<D>(L, b));
     const double fa = ha >= 0 ? vt[ha].f : NAN;
     const double fb = hb >= 0 ? vt[hb].f : NAN;
+    if (!CERT && ends) {
+      pts[i] = fa;
+      pts[ld + (int64_t)i] = fb;
+      continue;
+    }
     double p[D];
     const float ba = CERT && ha >= 0 ? vb[ha] : -1.0f, bb = CERT && hb >= 0 ? vb[hb] : -1.0f;
     const bool ok = edge_point<D>(L, Q, a, b, fa, fb, CERT, ba, bb, p);
@@ -2563,7 +2576,7 @@ int subdivide_fused(ip_ctx *ctx, const ip_problem *p, const SubArgs &a, const ui
 // that fits the budget fixes the batch size.
 template <int D>
 int subdivide_table(ip_ctx *ctx, const ip_problem *p, const SubArgs &a, const uint64_t *sig_all, uint64_t nsig,
-                    uint64_t nc, uint64_t budget, bool cert, ip_stats &st, ip_cells *res, BatchStream *bs) {
+                    uint64_t nc, uint64_t budget, bool cert, ip_stats &st, ip_cells *res, BatchStream *bs, bool ends) {
   const int k = p->k, NP = a.NP, NE = a.NE;
   // a slot: VEnt, eval-list entry and, certified, its bound and fallback
   // entry; per coarse simplex (one per 2 NP slots) its preparation record
@@ -2700,11 +2713,11 @@ int subdivide_table(ip_ctx *ctx, const ip_problem *p, const SubArgs &a, const ui
       if (cert)
         hipLaunchKernelGGL((batch_points_kernel<D, true>), dim3(grid_for(q.hi - q.lo)), dim3(kBlock), 0, ctx->stream,
                            p->fine, q.keys, q.lo, q.hi, (const VEnt *)f.vt, (const float *)f.vb, vcap - 1, q.pts,
-                           (int64_t)q.ld, p->poly, redo, ctx->ctr_dev);
+                           (int64_t)q.ld, p->poly, redo, ctx->ctr_dev, false);
       else
         hipLaunchKernelGGL((batch_points_kernel<D, false>), dim3(grid_for(q.hi - q.lo)), dim3(kBlock), 0, ctx->stream,
                            p->fine, q.keys, q.lo, q.hi, (const VEnt *)f.vt, (const float *)nullptr, vcap - 1, q.pts,
-                           (int64_t)q.ld, p->poly, (uint64_t *)nullptr, ctx->ctr_dev);
+                           (int64_t)q.ld, p->poly, (uint64_t *)nullptr, ctx->ctr_dev, ends);
       IP_TRY_HIP(ctx, hipGetLastError());
       IP_TRY(tp.stop(ctx));
       if (cert) {
@@ -2761,7 +2774,7 @@ int subdivide_table(ip_ctx *ctx, const ip_problem *p, const SubArgs &a, const ui
 }
 
 template <int D>
-int trace_batch(ip_ctx *ctx, const ip_problem *p, uint64_t budget, bool cert, ip_cells *res,
+int trace_batch(ip_ctx *ctx, const ip_problem *p, uint64_t budget, bool cert, ip_cells *res, bool ends,
                 BatchStream *bs = nullptr) {
   ip_stats &st = res->st;
   const int k = p->k;
@@ -2865,7 +2878,7 @@ int trace_batch(ip_ctx *ctx, const ip_problem *p, uint64_t budget, bool cert, ip
   if (cert && p->poly.ok)
     rc = subdivide_fused<D>(ctx, p, a, (const uint64_t *)sig_list, nsig, nc, budget, st, res, bs);
   else
-    rc = subdivide_table<D>(ctx, p, a, (const uint64_t *)sig_list, nsig, nc, budget, cert, st, res, bs);
+    rc = subdivide_table<D>(ctx, p, a, (const uint64_t *)sig_list, nsig, nc, budget, cert, st, res, bs, ends);
   (void)hipStreamSynchronize(ctx->stream);
   st.regrows += s.regrows;
   st.n_fallback += s.n_fallback;
@@ -2876,7 +2889,7 @@ int trace_batch(ip_ctx *ctx, const ip_problem *p, uint64_t budget, bool cert, ip
 // Points of OUT[0 .. n) into keys / pts; in FP32 mode the edges whose point
 // the bound cannot certify get FP64 values at their ends and are redone.
 template <int D>
-int direct_points(Run &s, uint64_t n, uint64_t *keys, double *pts, ip_stats &st) {
+int direct_points(Run &s, uint64_t n, uint64_t *keys, double *pts, ip_stats &st, bool ends) {
   ip_ctx *ctx = s.ctx;
   uint64_t *redo = nullptr;
   DevTmp qb_hold(ctx);
@@ -2897,7 +2910,7 @@ int direct_points(Run &s, uint64_t n, uint64_t *keys, double *pts, ip_stats &st)
   Timer tp;
   IP_TRY(tp.start(ctx, &st.ms_points));
   hipLaunchKernelGGL((points_kernel<D, false>), dim3(grid_for(n)), dim3(kBlock), 0, ctx->stream, s.L, s.out, n, s.vt,
-                     keys, pts, (int64_t)n, s.cert, (const float *)s.vb, s.p->poly, redo, s.fb, qb, ctx->ctr_dev);
+                     keys, pts, (int64_t)n, s.cert, (const float *)s.vb, s.p->poly, redo, s.fb, qb, ctx->ctr_dev, ends);
   IP_TRY_HIP(ctx, hipGetLastError());
   IP_TRY(tp.stop(ctx));
   if (s.cert) {
@@ -2908,7 +2921,7 @@ int direct_points(Run &s, uint64_t n, uint64_t *keys, double *pts, ip_stats &st)
       IP_TRY(launch_set_vb(ctx, s.fb, nfb, s.vb, -1.0f));
       hipLaunchKernelGGL((points_kernel<D, true>), dim3(grid_for(nredo)), dim3(kBlock), 0, ctx->stream, s.L, s.out,
                          nredo, s.vt, keys, pts, (int64_t)n, true, (const float *)s.vb, s.p->poly, redo, s.fb,
-                         qb, ctx->ctr_dev);
+                         qb, ctx->ctr_dev, false);
       IP_TRY_HIP(ctx, hipGetLastError());
       s.n_fallback += (int64_t)nfb;
     }
@@ -2918,13 +2931,14 @@ int direct_points(Run &s, uint64_t n, uint64_t *keys, double *pts, ip_stats &st)
 }
 
 template <int D>
-int trace_T(ip_ctx *ctx, const ip_problem *p, uint64_t budget, int32_t prec, ip_cells *res) {
+int trace_T(ip_ctx *ctx, const ip_problem *p, uint64_t budget, int32_t prec, int iters, ip_cells *res) {
   // RBF manifolds trace in canonical FP64 in either mode: the FP32 tier's
   // bound, loose through the cancellation in the sum of exponentials, settles
   // signs but cannot place the intersection points, so every traced vertex
   // would need its FP64 value as well (ip_feval keeps the FP32 tier)
   const bool cert = prec == IP_FP32_CERTIFY && p->f.kernel == IP_KERNEL_POLY && ip_has_fp32_form(p);
-  if (p->k != 1) return trace_batch<D>(ctx, p, budget, cert, res);
+  const bool ends = !cert && iters > 0;  // the canonical refinement starts from f at the ends
+  if (p->k != 1) return trace_batch<D>(ctx, p, budget, cert, res, ends);
   Run s;
   s.ctx = ctx;
   s.p = p;
@@ -2942,7 +2956,7 @@ int trace_T(ip_ctx *ctx, const ip_problem *p, uint64_t budget, int32_t prec, ip_
   double *pts = nullptr;
   if (rc == IP_OK) rc = alloc(ctx, (void **)&keys, sizeof(uint64_t) * (size_t)(n ? n : 1));
   if (rc == IP_OK) rc = alloc(ctx, (void **)&pts, sizeof(double) * (size_t)(n ? n : 1) * D);
-  if (rc == IP_OK && n) rc = direct_points<D>(s, n, keys, pts, st);
+  if (rc == IP_OK && n) rc = direct_points<D>(s, n, keys, pts, st, ends);
   out_trim(s);
   if (rc != IP_OK) {
     if (keys) release(ctx, keys);
@@ -3057,21 +3071,31 @@ int region_eval_T(ip_ctx *ctx, const ip_problem *p, const int32_t *simp, int64_t
 // smaller endpoint); each step evaluates f at the false-position point m,
 // moves the end whose sign bit s = !(f < 0) equals s(m), and halves the value
 // kept at the other end when the same end moved twice in a row; the result
-// is the false-position point of the final bracket.  CANON: f in the
-// canonical FP64 order (the support vectors as wave-uniform scalar loads),
-// so the points equal the oracle's bit for bit; otherwise f from the FP64
-// monomial form (FP32-certified mode, points within the stated tolerance).
-// R edges per lane share each support-vector load.
-template <int D, int P, int R, bool CANON>
-__global__ __launch_bounds__(256) void refine_kernel(LatDev L, const uint64_t *__restrict__ keys, uint64_t n,
-                                                     double *pts, int64_t ld, FDev F, PolyDev Q, int iters) {
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x * R;
-  for (uint64_t base = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) * R; base < n; base += stride) {
+// is the false-position point of the final bracket.
+//   CANON: f in the canonical FP64 order, so the points equal the oracle's
+// bit for bit; f at the two ends is read from the first two point columns,
+// where the trace left the vertex table's values.  The support vectors pass
+// through LDS tiles (tile_sum): one wave-uniform scalar load per record had
+// bound the kernel to the scalar cache's misses, and f at the ends was a
+// third of the evaluations (760 thousand cells, d = 5, S = 300 Gaussian, 4
+// steps: 2.59 ms, now about 1.3).  The loop is uniform across the block.
+//   Otherwise f from the FP64 monomial form (FP32-certified mode, points
+// within the stated tolerance).
+template <int D, int P, int R, int U, bool CANON>
+__global__ __launch_bounds__(256, CANON && R == 1 ? 4 : 2) void refine_kernel(LatDev L,
+                                                                            const uint64_t *__restrict__ keys,
+                                                                            uint64_t n, double *pts, int64_t ld,
+                                                                            FDev F, PolyDev Q, int iters) {
+  __shared__ __align__(16) double tile[CANON ? 2 : 1][CANON ? kRecTile * 8 : 2];
+  for (uint64_t blk = (uint64_t)blockIdx.x * 256 * R; blk < n; blk += (uint64_t)gridDim.x * 256 * R) {
     double a[R][D], b[R][D], m[R][D], fa[R], fb[R], fm[R];
     int last[R];
+    uint64_t at[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const uint64_t i = base + r < n ? base + r : n - 1;
+      const uint64_t q = blk + r * 256 + threadIdx.x;
+      const uint64_t i = q < n ? q : n - 1;
+      at[r] = i;
       int32_t va[D], vb[D];
       uint32_t Rm;
       eunpack<D>(L, keys[i], va, &Rm);
@@ -3080,62 +3104,15 @@ __global__ __launch_bounds__(256) void refine_kernel(LatDev L, const uint64_t *_
       lat_coords<D>(L, va, a[r]);
       lat_coords<D>(L, vb, b[r]);
       last[r] = 0;
-    }
-    // f at the R points held in x[r]: canonical order or monomial form
-    auto feval = [&](double (*x)[D], double *out) {
-      if (CANON && F.kernel == IP_KERNEL_RBF) {
-        double acc[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) acc[r] = 0.0;
-        for (int64_t s = 0; s < F.S; ++s) {
-          const double *rec = F.rec + s * 8;
-          double sv[D];
-#pragma unroll
-          for (int j = 0; j < D; ++j) sv[j] = rec[j];
-          const double al = rec[D];
-#pragma unroll
-          for (int r = 0; r < R; ++r) acc[r] = rbf_term<D>(sv, al, F.gamma, x[r], acc[r]);
-        }
-#pragma unroll
-        for (int r = 0; r < R; ++r) out[r] = acc[r] + F.bias;
-      } else if (CANON) {
-        double acc[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) acc[r] = 0.0;
-        for (int64_t s = 0; s < F.S; ++s) {
-          const double *rec = F.rec + s * 8;
-          double sv[D];
-#pragma unroll
-          for (int j = 0; j < D; ++j) sv[j] = rec[j];
-          const double al = rec[D];
-#pragma unroll
-          for (int r = 0; r < R; ++r) {
-            double dot = 0.0;
-#pragma unroll
-            for (int j = 0; j < D; ++j) dot = fma(sv[j], x[r][j], dot);
-            const double t = fma(F.gamma, dot, F.coef0);
-            double tp = t;
-            if (P > 0) {
-#pragma unroll
-              for (int q = 1; q < P; ++q) tp = tp * t;
-            } else {
-              for (int q = 1; q < F.p; ++q) tp = tp * t;
-            }
-            acc[r] = fma(al, tp, acc[r]);
-          }
-        }
-#pragma unroll
-        for (int r = 0; r < R; ++r) out[r] = acc[r] + F.bias;
+      if (CANON) {
+        fa[r] = pts[i];
+        fb[r] = pts[ld + (int64_t)i];
       } else {
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          double bnd;
-          out[r] = poly64<D, (P > 0 ? P : 4)>(Q, x[r], &bnd);
-        }
+        double bnd;
+        fa[r] = poly64<D, (P > 0 ? P : 4)>(Q, a[r], &bnd);
+        fb[r] = poly64<D, (P > 0 ? P : 4)>(Q, b[r], &bnd);
       }
-    };
-    feval(a, fa);
-    feval(b, fb);
+    }
     for (int it = 0; it < iters; ++it) {
 #pragma unroll
       for (int r = 0; r < R; ++r) {
@@ -3143,7 +3120,15 @@ __global__ __launch_bounds__(256) void refine_kernel(LatDev L, const uint64_t *_
 #pragma unroll
         for (int j = 0; j < D; ++j) m[r][j] = fma(t, b[r][j] - a[r][j], a[r][j]);
       }
-      feval(m, fm);
+      if constexpr (CANON) {
+        tile_sum<D, P, R, U>(F, tile, m, fm);
+#pragma unroll
+        for (int r = 0; r < R; ++r) fm[r] = fm[r] + F.bias;
+      } else {
+        double bnd;
+#pragma unroll
+        for (int r = 0; r < R; ++r) fm[r] = poly64<D, (P > 0 ? P : 4)>(Q, m[r], &bnd);
+      }
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         if (!(fm[r] < 0.0) == !(fa[r] < 0.0)) {
@@ -3163,24 +3148,36 @@ __global__ __launch_bounds__(256) void refine_kernel(LatDev L, const uint64_t *_
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      if (base + r >= n) continue;
+      if (blk + r * 256 + threadIdx.x >= n) continue;
       const double t = fa[r] / (fa[r] - fb[r]);
 #pragma unroll
-      for (int j = 0; j < D; ++j) pts[(int64_t)j * ld + (int64_t)(base + r)] = fma(t, b[r][j] - a[r][j], a[r][j]);
+      for (int j = 0; j < D; ++j) pts[(int64_t)j * ld + (int64_t)at[r]] = fma(t, b[r][j] - a[r][j], a[r][j]);
     }
   }
 }
 
+// Cells per lane: two share a record's read, one once two would leave SIMDs
+// without a wave, and one for the Gaussian, whose term is long (the rule of
+// the canonical evaluation in feval.hip).
 template <int D, bool CANON>
 void launch_refine(ip_ctx *ctx, const ip_problem *p, const ip_cells *c, int iters) {
-  constexpr int R = 2;
   const uint64_t n = (uint64_t)c->n;
-  const uint64_t blocks = std::min<uint64_t>((n + 256 * R - 1) / (256 * R), 65536);
-  const int P = CANON ? p->f.p : p->poly.p;
-#define IP_RF(PP)                                                                                              \
-  hipLaunchKernelGGL((refine_kernel<D, PP, R, CANON>), dim3((unsigned)blocks), dim3(256), 0, ctx->stream, p->fine, \
-                     (const uint64_t *)c->keys, n, c->pts, c->ld, p->f, p->poly, iters)
-  switch (P) {
+#define IP_RFK(PP, R, U)                                                                                        \
+  hipLaunchKernelGGL((refine_kernel<D, PP, R, U, CANON>),                                                       \
+                     dim3((unsigned)std::min<uint64_t>((n + 256 * R - 1) / (256 * R), 65536)), dim3(256), 0,    \
+                     ctx->stream, p->fine, (const uint64_t *)c->keys, n, c->pts, c->ld, p->f, p->poly, iters)
+#define IP_RF(PP)                \
+  if (CANON && n <= 98304)       \
+    IP_RFK(PP, 1, 4);            \
+  else                           \
+    IP_RFK(PP, 2, 4)
+  if constexpr (CANON) {
+    if (p->f.kernel == IP_KERNEL_RBF) {
+      IP_RFK(-1, 1, 2);
+      return;
+    }
+  }
+  switch (CANON ? p->f.p : p->poly.p) {
     case 1: IP_RF(1); break;
     case 2: IP_RF(2); break;
     case 3: IP_RF(3); break;
@@ -3188,6 +3185,7 @@ void launch_refine(ip_ctx *ctx, const ip_problem *p, const ip_cells *c, int iter
     default: IP_RF(0); break;
   }
 #undef IP_RF
+#undef IP_RFK
 }
 
 // Refine the points of the traced cells in place (no effect for iters = 0).
@@ -3283,7 +3281,7 @@ int trace_batches_T(ip_ctx *ctx, const ip_problem *p, uint64_t budget, int32_t p
   IP_TRY(bs.init());
   ip_cells res;
   res.ctx = ctx;
-  IP_TRY(trace_batch<D>(ctx, p, budget, cert, &res, &bs));
+  IP_TRY(trace_batch<D>(ctx, p, budget, cert, &res, !cert && iters > 0, &bs));
   unsigned long long dg[2] = {0, 0};
   IP_TRY_HIP(ctx, hipMemcpyAsync(dg, bs.dg, 16, hipMemcpyDeviceToHost, ctx->stream));
   IP_TRY_HIP(ctx, hipStreamSynchronize(ctx->stream));
@@ -3321,12 +3319,12 @@ int ip_trace_impl(ip_ctx *ctx, const ip_problem *p, uint64_t budget, int32_t pre
                   ip_cells *out) {
   const int iters = (int)((flags >> 4) & 15u);
   switch (p->d) {
-    case 2: IP_TRY(trace_T<2>(ctx, p, budget, prec, out)); return refine_T<2>(ctx, p, prec, iters, out);
-    case 3: IP_TRY(trace_T<3>(ctx, p, budget, prec, out)); return refine_T<3>(ctx, p, prec, iters, out);
-    case 4: IP_TRY(trace_T<4>(ctx, p, budget, prec, out)); return refine_T<4>(ctx, p, prec, iters, out);
-    case 5: IP_TRY(trace_T<5>(ctx, p, budget, prec, out)); return refine_T<5>(ctx, p, prec, iters, out);
-    case 6: IP_TRY(trace_T<6>(ctx, p, budget, prec, out)); return refine_T<6>(ctx, p, prec, iters, out);
-    case 7: IP_TRY(trace_T<7>(ctx, p, budget, prec, out)); return refine_T<7>(ctx, p, prec, iters, out);
+    case 2: IP_TRY(trace_T<2>(ctx, p, budget, prec, iters, out)); return refine_T<2>(ctx, p, prec, iters, out);
+    case 3: IP_TRY(trace_T<3>(ctx, p, budget, prec, iters, out)); return refine_T<3>(ctx, p, prec, iters, out);
+    case 4: IP_TRY(trace_T<4>(ctx, p, budget, prec, iters, out)); return refine_T<4>(ctx, p, prec, iters, out);
+    case 5: IP_TRY(trace_T<5>(ctx, p, budget, prec, iters, out)); return refine_T<5>(ctx, p, prec, iters, out);
+    case 6: IP_TRY(trace_T<6>(ctx, p, budget, prec, iters, out)); return refine_T<6>(ctx, p, prec, iters, out);
+    case 7: IP_TRY(trace_T<7>(ctx, p, budget, prec, iters, out)); return refine_T<7>(ctx, p, prec, iters, out);
     default: return ip_fail(ctx, IP_EINVAL, "dimension out of range");
   }
 }
