@@ -194,7 +194,8 @@ __global__ __launch_bounds__(256, (P < 0 || R < 4) ? 4 : 2) void feval64_tile_ke
 // Which kernel, by the vertex count n (times in us at d = 6, p = 3,
 // S = 2000).  Up to 16384 vertices one lane each fills less than one wave per
 // CU, and the split form is the faster (4096: 25 against 90; 16384: 68
-// against 92).  Above, the least number of vertices per lane that still
+// against 92), with as few vertices per forming wave as still give each CU a
+// block (1000: 23.5 with one, 27.8 with four; S = 200: 7.3 and 8.0).  Above, the least number of vertices per lane that still
 // fills the SIMDs once: 65 536 lanes are one wave on each (65536: 1 per lane
 // 101, 2 per lane 148; 200003: 1, 2 and 4 per lane 264, 209, 232; 1048576:
 // 1006, 772, 730).  The Gaussian term is 34 operations long and needs no
@@ -221,7 +222,11 @@ void launch64(const Eval64 &e, const FDev &F, const LatDev &L) {
 #define IP_L64(KERNEL, PER, BLOCK)                                                                                  \
   hipLaunchKernelGGL(KERNEL, dim3((unsigned)std::min<uint64_t>((n + (PER) - 1) / (PER), 65536)), dim3(BLOCK), 0, e.st, \
                      F, L, e.list, e.n, e.n_dev, e.keys, e.vraw, e.out, e.stamp)
-  if (n <= kSplitMax) {
+  if (n <= 1792) {
+    IP_L64((feval64_split_kernel<D, P, MODE, 1>), 7, 512);
+  } else if (n <= 3584) {
+    IP_L64((feval64_split_kernel<D, P, MODE, 2>), 14, 512);
+  } else if (n <= kSplitMax) {
     IP_L64((feval64_split_kernel<D, P, MODE, 4>), 28, 512);
   } else if (P < 0) {
     IP_L64((feval64_tile_kernel<D, P, 1, 2, MODE>), 256, 256);
@@ -286,8 +291,10 @@ __global__ __launch_bounds__(256) void feval32_kernel(PolyDev Q, LatDev L, const
                                                       float *vb, const int32_t *__restrict__ vraw, double *out,
                                                       double *bout, uint32_t *fb, unsigned long long *fb_ctr,
                                                       unsigned long long *c64_ctr, unsigned long long *stamp) {
-  put_stamp(stamp);
-  if (n_dev) n = (uint64_t)*n_dev < n ? (uint64_t)*n_dev : n;
+  if constexpr (MODE == 0) {
+    put_stamp(stamp);
+    if (n_dev) n = (uint64_t)*n_dev < n ? (uint64_t)*n_dev : n;
+  }
   constexpr int kStage = 128;
   __shared__ uint32_t st[4][kStage];
   const int wib = threadIdx.x >> 6;

@@ -756,12 +756,12 @@ int eval_pending(Run &s, uint64_t n) {
 int eval_chain(Run &s, const unsigned long long *n_dev, uint64_t hint) {
   ip_ctx *ctx = s.ctx;
   // levels grow faster than the counters are read: a block per CU at least
-  hint = std::max<uint64_t>(hint, 7168);
+  hint = std::max<uint64_t>(hint, 1792);
   Counters *c = ctx->ctr_dev;
   if (!s.cert) return launch_feval64(ctx, s.p, s.L, s.eval, s.vt_cap, s.vt, n_dev, hint, &c->t_eval);
   IP_TRY(launch_feval32(ctx, s.p, s.L, s.eval, s.vt_cap, s.vt, s.vb, s.fb, &c->n_fb, n_dev, hint, &c->t_eval));
   // rarely more than a few vertices
-  return launch_feval64(ctx, s.p, s.L, s.fb, s.vt_cap, s.vt, &c->n_fb, 1792);
+  return launch_feval64(ctx, s.p, s.L, s.fb, s.vt_cap, s.vt, &c->n_fb, 448);
 }
 
 // Pass 1 or 2 of a level, for a frontier of about `edges`.
