@@ -1583,6 +1583,18 @@ __global__ __launch_bounds__(kBlock, 4) void subdivide_kernel(LatDev Lf, LatDev 
   uint64_t st_key = 0;
   SubPrep<D> st_p = {};
   int jn = 64;
+  // MODE 3, at most one template point per lane: the slots of the simplex
+  // after next and the values of the next are in flight while one is worked
+  // on (two dependent reads per simplex, 1.5 us of 4 waves' time; active and
+  // inactive points alike: the latter end no edge of an active face).
+  const bool ahead = MODE == 3 && NP <= 64;
+  uint32_t ps_c = 0xffffffffu, ps_n = 0xffffffffu;
+  double f_c = 0.0;
+  if (ahead && lane < NP) {
+    if (wave < n) ps_c = pslot[wave * (uint64_t)NP + lane];
+    if (wave + n_waves < n) ps_n = pslot[(wave + n_waves) * (uint64_t)NP + lane];
+    if (ps_c != 0xffffffffu) f_c = fvt[ps_c].f;
+  }
   for (uint64_t it = wave; it < n; it += n_waves) {
     if (jn == 64) {
       const uint64_t itj = it + (uint64_t)lane * n_waves;
@@ -1594,9 +1606,12 @@ __global__ __launch_bounds__(kBlock, 4) void subdivide_kernel(LatDev Lf, LatDev 
       jn = 0;
     }
     const uint64_t s = (uint32_t)__builtin_amdgcn_readlane((int)st_s, jn);
+    const uint64_t skey = readlane64(st_key, jn);
     int32_t v[D], w[D], winv[D];
-    sig_unpack<D>(Lc, readlane64(st_key, jn), LB, v, w);
-    perm_inverse<D>(w, winv);
+    if (MODE != 3) {
+      sig_unpack<D>(Lc, skey, LB, v, w);
+      perm_inverse<D>(w, winv);
+    }
     const double B1 = __longlong_as_double((long long)readlane64((uint64_t)__double_as_longlong(st_p.B1), jn));
     uint64_t A[NVW], TR[NVW];
 #pragma unroll
@@ -1605,88 +1620,101 @@ __global__ __launch_bounds__(kBlock, 4) void subdivide_kernel(LatDev Lf, LatDev 
       TR[t] = readlane64(st_p.TR[t], jn);
     }
     ++jn;
-    // active template points: an end of an edge of an active face; every
-    // code starts at 2
-    int NPA = 0;
-    for (int p0 = 0; p0 < NP; p0 += 64) {
-      const int pt = p0 + lane;
-      bool a = false;
-      if (pt < NP) {
-        uint64_t hit = 0;
+    uint64_t ng0 = 0, ps0 = 0;
+    if (ahead) {
+      // the sign of point `lane`, asked for one and two simplices ago
+      const uint32_t c = ps_c == 0xffffffffu ? 2u : f_c < 0.0 ? 0u : 1u;
+      ps_c = ps_n;
+      if (ps_n != 0xffffffffu) f_c = fvt[ps_n].f;
+      const uint64_t s2 = s + 2 * n_waves;
+      ps_n = s2 < n && lane < NP ? pslot[s2 * (uint64_t)NP + lane] : 0xffffffffu;
+      if (lane < NP) code[lane] = (uint8_t)c;
+      ng0 = __ballot(c == 0u);
+      ps0 = __ballot(c == 1u);
+    } else {
+      // active template points: an end of an edge of an active face; every
+      // code starts at 2
+      int NPA = 0;
+      for (int p0 = 0; p0 < NP; p0 += 64) {
+        const int pt = p0 + lane;
+        bool a = false;
+        if (pt < NP) {
+          uint64_t hit = 0;
 #pragma unroll
-        for (int t = 0; t < NVW; ++t) hit |= lpf[pt * NVW + t] & A[t];
-        a = hit != 0ull;
-        code[pt] = 2;
+          for (int t = 0; t < NVW; ++t) hit |= lpf[pt * NVW + t] & A[t];
+          a = hit != 0ull;
+          code[pt] = 2;
+        }
+        const uint64_t bal = __ballot(a);
+        if (a) plist[NPA + __popcll(bal & lt_mask)] = (uint16_t)pt;
+        NPA += __popcll(bal);
       }
-      const uint64_t bal = __ballot(a);
-      if (a) plist[NPA + __popcll(bal & lt_mask)] = (uint16_t)pt;
-      NPA += __popcll(bal);
-    }
-    wave_lds_sync();
-    bool unsettled = false;
-    for (int i0 = 0; i0 < NPA; i0 += 64) {
-      const int i = i0 + lane;
-      uint32_t c = 2;
-      if (i < NPA) {
-        const int pt = plist[i];
-        if (MODE == 3) {
-          const uint32_t ps = pslot[s * (uint64_t)NP + pt];
-          if (ps != 0xffffffffu) c = fvt[ps].f < 0.0 ? 0u : 1u;
-        } else {
-          int32_t y[D];
-          template_point_inv<D>(v, winv, k, lpts[pt], y);
-          // an opaque zero base keeps the frame and coefficient reads in the
-          // loop (hoisted, the 36 matrix entries alone would pin 72 vector
-          // registers), each at an immediate offset from it
-          int z = 0;
-          asm volatile("" : "+v"(z));
-          const double *Mz = lmat + z;
-          double x[D];
-          lat_coords_m<D>(Mz, y, x);
-          if (in_box_m<D>(Mz, x)) {
-            double fv;
-            PolyDev Qz = Q;
-            Qz.c = lc + z;
-            const int tier = cert_eval_region<D, P>(Qz, x, B1, &fv);
-            if (MODE == 0) ++npts;
-            if (tier < 3) {
-              c = fv < 0.0 ? 0u : 1u;
-            } else if (MODE == 0) {
-              c = 3;
-              ++nuns;
-            } else if (MODE == 1) {
-              uint64_t slot;
-              const int ins = vt_insert(fvt, fvt_mask, vpack<D>(Lf, y), &slot);
-              if (ins == 1)
-                eval_list[atomicAdd(&ctr->n_eval, 1ull)] = (uint32_t)slot;
-              else if (ins < 0)
-                atomicOr(&ctr->vt_fail, 1u);
-            } else {
-              const int64_t h = vt_find(fvt, fvt_mask, vpack<D>(Lf, y));
-              if (h < 0) atomicOr(&ctr->vt_fail, 1u);
-              c = (h >= 0 && !(fvt[h].f < 0.0)) ? 1u : 0u;
+      wave_lds_sync();
+      bool unsettled = false;
+      for (int i0 = 0; i0 < NPA; i0 += 64) {
+        const int i = i0 + lane;
+        uint32_t c = 2;
+        if (i < NPA) {
+          const int pt = plist[i];
+          if (MODE == 3) {
+            const uint32_t ps = pslot[s * (uint64_t)NP + pt];
+            if (ps != 0xffffffffu) c = fvt[ps].f < 0.0 ? 0u : 1u;
+          } else {
+            int32_t y[D];
+            template_point_inv<D>(v, winv, k, lpts[pt], y);
+            // an opaque zero base keeps the frame and coefficient reads in the
+            // loop (hoisted, the 36 matrix entries alone would pin 72 vector
+            // registers), each at an immediate offset from it
+            int z = 0;
+            asm volatile("" : "+v"(z));
+            const double *Mz = lmat + z;
+            double x[D];
+            lat_coords_m<D>(Mz, y, x);
+            if (in_box_m<D>(Mz, x)) {
+              double fv;
+              PolyDev Qz = Q;
+              Qz.c = lc + z;
+              const int tier = cert_eval_region<D, P>(Qz, x, B1, &fv);
+              if (MODE == 0) ++npts;
+              if (tier < 3) {
+                c = fv < 0.0 ? 0u : 1u;
+              } else if (MODE == 0) {
+                c = 3;
+                ++nuns;
+              } else if (MODE == 1) {
+                uint64_t slot;
+                const int ins = vt_insert(fvt, fvt_mask, vpack<D>(Lf, y), &slot);
+                if (ins == 1)
+                  eval_list[atomicAdd(&ctr->n_eval, 1ull)] = (uint32_t)slot;
+                else if (ins < 0)
+                  atomicOr(&ctr->vt_fail, 1u);
+              } else {
+                const int64_t h = vt_find(fvt, fvt_mask, vpack<D>(Lf, y));
+                if (h < 0) atomicOr(&ctr->vt_fail, 1u);
+                c = (h >= 0 && !(fvt[h].f < 0.0)) ? 1u : 0u;
+              }
             }
           }
+          code[pt] = (uint8_t)c;
         }
-        code[pt] = (uint8_t)c;
+        if (MODE == 0 && __ballot(c == 3)) unsettled = true;
       }
-      if (MODE == 0 && __ballot(c == 3)) unsettled = true;
-    }
-    if (MODE == 1) continue;
-    if (MODE == 0 && unsettled) {
+      if (MODE == 1) continue;
+      if (MODE == 0 && unsettled) {
+        wave_lds_sync();
+        stage_put<kDeferStage>(dst, sdf, lane == 0, (uint32_t)s, put_df, &ctr->n_aux);
+        continue;
+      }
       wave_lds_sync();
-      stage_put<kDeferStage>(dst, sdf, lane == 0, (uint32_t)s, put_df, &ctr->n_aux);
-      continue;
-    }
-    wave_lds_sync();
-    // sign masks over the template points (f < 0, f >= 0)
-    for (int q = 0; q < NPW; ++q) {
-      const int pt = 64 * q + lane;
-      const uint32_t c = pt < NP ? code[pt] : 2u;
-      const uint64_t ng = __ballot(c == 0u), ps = __ballot(c == 1u);
-      if (lane == 0) {
-        mneg[q] = ng;
-        mpos[q] = ps;
+      // sign masks over the template points (f < 0, f >= 0)
+      for (int q = 0; q < NPW; ++q) {
+        const int pt = 64 * q + lane;
+        const uint32_t c = pt < NP ? code[pt] : 2u;
+        const uint64_t ng = __ballot(c == 0u), ps = __ballot(c == 1u);
+        if (lane == 0) {
+          mneg[q] = ng;
+          mpos[q] = ps;
+        }
       }
     }
     for (int i = lane; i < SBW; i += 64) sbm[i] = 0ull;
@@ -1706,8 +1734,8 @@ __global__ __launch_bounds__(kBlock, 4) void subdivide_kernel(LatDev Lf, LatDev 
         uint64_t hn = 0, hp = 0;
         for (int q = 0; q < NPW; ++q) {
           const uint64_t pv = lpv[V * NPW + q];
-          hn |= pv & mneg[q];
-          hp |= pv & mpos[q];
+          hn |= pv & (ahead ? ng0 : mneg[q]);
+          hp |= pv & (ahead ? ps0 : mpos[q]);
         }
         act = hn != 0ull && hp != 0ull;
       }
@@ -1729,6 +1757,11 @@ __global__ __launch_bounds__(kBlock, 4) void subdivide_kernel(LatDev Lf, LatDev 
       }
       T += (int)tot;
       G += __popcll(ba);
+    }
+    if (MODE == 3) {
+      if (T == 0) continue;
+      sig_unpack<D>(Lc, skey, LB, v, w);
+      perm_inverse<D>(w, winv);
     }
     // edge pass over the active groups: sign test from LDS; the edges to
     // emit (owner) or to dedup (no owner) are staged by index, and their keys
