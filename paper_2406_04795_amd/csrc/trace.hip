@@ -1605,6 +1605,37 @@ __global__ __launch_bounds__(kBlock, 4) void subdivide_kernel(LatDev Lf, LatDev 
   uint32_t *dst = (uint32_t *)(smem + Ly.dst) + (size_t)wib * kDeferStage;
   int sdf = 0;
   auto put_df = [&](unsigned long long pos, uint32_t q) { defer[pos] = q; };
+  // MODE 3: the keys of several simplices (the sign bit set: for the edge
+  // set) are inserted together.  A simplex has one or two edges, and the wave
+  // waited for the probes of each.
+  constexpr int kKeyStage = 128;
+  __shared__ uint64_t kst_[MODE == 3 ? kWaves : 1][MODE == 3 ? kKeyStage : 1];
+  uint64_t *const kst = kst_[MODE == 3 ? wib : 0];
+  int kn = 0;
+  auto drain_keys = [&]() {
+    wave_lds_sync();
+    for (int b = 0; b < kn; b += 64) {
+      bool dir = false, nw = false;
+      uint64_t key = 0;
+      if (b + lane < kn) {
+        const uint64_t e = kst[b + lane];
+        key = e & ~IP_SIGN_BIT;
+        dir = !(e & IP_SIGN_BIT);
+        if (!dir) {
+          uint64_t slot;
+          const int ins = ht_insert(so.et_keys, so.et_mask, key, &slot);
+          if (ins == 1)
+            nw = true;
+          else if (ins < 0)
+            atomicOr(&ctr->et_fail, 1u);
+        }
+      }
+      stage_put<kSubStage>(stage_s, sn, nw, key, put_s, &ctr->n_out);
+      stage_put<kSubStage>(stage_d, snd, dir, key, put_d, ctr_d);
+    }
+    wave_lds_sync();
+    kn = 0;
+  };
   // per-lane tallies (a lane sees far fewer than 2^32 events per launch)
   uint32_t hits = 0, shits = 0, npts = 0, nuns = 0;
   const uint64_t wave = ((uint64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
@@ -1792,22 +1823,27 @@ __global__ __launch_bounds__(kBlock, 4) void subdivide_kernel(LatDev Lf, LatDev 
       T += (int)tot;
       G += __popcll(ba);
     }
-    if (MODE == 3) {
-      if (T == 0) continue;
-      sig_unpack<D>(Lc, skey, LB, v, w);
-      perm_inverse<D>(w, winv);
-    }
+    if (MODE == 3 && T == 0) continue;
     // edge pass over the active groups: sign test from LDS; the edges to
     // emit (owner) or to dedup (no owner) are staged by index, and their keys
     // are formed and written 64 at a time, so the sparse hits do not
     // serialize the wave
     int sne = 0;
     auto flush_edges = [&]() {
+      if (MODE == 3) {
+        if (sne == 0) return;
+        sig_unpack<D>(Lc, skey, LB, v, w);
+        perm_inverse<D>(w, winv);
+      }
       wave_lds_sync();
       for (int b = 0; b < sne; b += 64) {
         const int idx = b + lane;
         bool dir = false, nw = false;
         uint64_t key = 0;
+        if (MODE == 3) {
+          const int nb = sne - b < 64 ? sne - b : 64;
+          if (kn + nb > kKeyStage) drain_keys();
+        }
         if (idx < sne) {
           const uint32_t item = est[idx];
           const uint32_t te = ledge[item & 0x7fffffffu];
@@ -1818,7 +1854,9 @@ __global__ __launch_bounds__(kBlock, 4) void subdivide_kernel(LatDev Lf, LatDev 
 #pragma unroll
           for (int c = 0; c < D; ++c) Rg |= ((Rl >> winv[c]) & 1u) << c;
           key = ekey<D>(Lf, y, Rg);
-          if (item >> 31) {
+          if (MODE == 3) {
+            kst[kn + lane] = key | (item >> 31 ? IP_SIGN_BIT : 0ull);
+          } else if (item >> 31) {
             uint64_t slot;
             const int ins = ht_insert(so.et_keys, so.et_mask, key, &slot);
             if (ins == 1)
@@ -1829,8 +1867,12 @@ __global__ __launch_bounds__(kBlock, 4) void subdivide_kernel(LatDev Lf, LatDev 
             dir = true;
           }
         }
-        stage_put<kSubStage>(stage_s, sn, nw, key, put_s, &ctr->n_out);
-        stage_put<kSubStage>(stage_d, snd, dir, key, put_d, ctr_d);
+        if (MODE == 3) {
+          kn += sne - b < 64 ? sne - b : 64;
+        } else {
+          stage_put<kSubStage>(stage_s, sn, nw, key, put_s, &ctr->n_out);
+          stage_put<kSubStage>(stage_d, snd, dir, key, put_d, ctr_d);
+        }
       }
       wave_lds_sync();
       sne = 0;
@@ -1867,6 +1909,7 @@ __global__ __launch_bounds__(kBlock, 4) void subdivide_kernel(LatDev Lf, LatDev 
     flush_edges();
   }
   if (MODE == 1) return;
+  if (MODE == 3) drain_keys();
   stage_flush_block(stage_s, sn, put_s, &ctr->n_out);
   __syncthreads();
   stage_flush_block(stage_d, snd, put_d, ctr_d);
