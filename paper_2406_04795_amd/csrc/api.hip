@@ -621,9 +621,26 @@ namespace {
 
 // Order-independent digest of the traced edge keys: (sum, xor) of the
 // SplitMix64-finalized keys.
-__global__ void digest_kernel(const uint64_t *keys, int64_t n, unsigned long long *sum, unsigned long long *x) {
+// (one atomic per block and sum: with one per wave of 1024 blocks, 12 ns each
+// in turn on one address, 9 thousand cells took 51 us, 52 M cells 157)
+__global__ __launch_bounds__(1024) void digest_kernel(const uint64_t *__restrict__ keys, int64_t n,
+                                                     unsigned long long *sum, unsigned long long *x) {
+  __shared__ unsigned long long ws[16], wx[16];
   unsigned long long s = 0, q = 0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+  const int64_t stride = (int64_t)gridDim.x * 1024;
+  int64_t i = (int64_t)blockIdx.x * 1024 + threadIdx.x;
+  for (; i + 3 * stride < n; i += 4 * stride) {
+    uint64_t k[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) k[u] = keys[i + u * stride];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const uint64_t h = mix64(k[u]);
+      s += h;
+      q ^= h;
+    }
+  }
+  for (; i < n; i += stride) {
     const uint64_t h = mix64(keys[i]);
     s += h;
     q ^= h;
@@ -633,10 +650,21 @@ __global__ void digest_kernel(const uint64_t *keys, int64_t n, unsigned long lon
     q ^= __shfl_xor(q, off, 64);
   }
   if ((threadIdx.x & 63) == 0) {
+    ws[threadIdx.x >> 6] = s;
+    wx[threadIdx.x >> 6] = q;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 16; ++w) {
+      s += ws[w];
+      q ^= wx[w];
+    }
     atomicAdd(sum, s);
     atomicXor(x, q);
   }
 }
+
+unsigned digest_grid(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + 4095) / 4096, 512)); }
 
 // Rows idx[0 .. n) of the cells: keys, points (row-major n x d), verdicts.
 __global__ void gather_kernel(const uint64_t *keys, const double *pts, int64_t ld, const uint8_t *verdict,
@@ -664,7 +692,7 @@ __global__ void interleave_kernel(const double *soa, int64_t ld, int64_t n, int 
 
 extern "C++" int ip_digest_accumulate(ip_ctx *ctx, const uint64_t *keys, int64_t n, unsigned long long *acc) {
   if (n <= 0) return IP_OK;
-  hipLaunchKernelGGL(digest_kernel, dim3(1024), dim3(256), 0, ctx->stream, keys, n, acc, acc + 1);
+  hipLaunchKernelGGL(digest_kernel, dim3(digest_grid(n)), dim3(1024), 0, ctx->stream, keys, n, acc, acc + 1);
   IP_TRY_HIP(ctx, hipGetLastError());
   return IP_OK;
 }
@@ -703,7 +731,7 @@ int ip_cells_digest(ip_ctx *ctx, const ip_cells *c, uint64_t digest[2]) {
   IP_TRY_HIP(ctx, hipSetDevice(ctx->device));
   IP_TRY_HIP(ctx, hipMemsetAsync(ctx->ctr_dev, 0, sizeof(Counters), ctx->stream));
   if (c->n > 0) {
-    hipLaunchKernelGGL(digest_kernel, dim3(1024), dim3(256), 0, ctx->stream, (const uint64_t *)c->keys, c->n,
+    hipLaunchKernelGGL(digest_kernel, dim3(digest_grid(c->n)), dim3(1024), 0, ctx->stream, (const uint64_t *)c->keys, c->n,
                        &ctx->ctr_dev->n_eval, &ctx->ctr_dev->n_aux);
     IP_TRY_HIP(ctx, hipGetLastError());
   }

@@ -259,13 +259,20 @@ __device__ __forceinline__ bool ball_near_cyl(const double *c, double R, const d
 }
 
 // OR over the wave, returned as a wave-uniform value (so that obstacle
-// indices derived from it address the scene with scalar loads).
+// indices derived from it address the scene with scalar loads): within rows
+// of 16 lanes by lane permutations of the vector unit, then over the four
+// rows (six shuffles through LDS waited for each other).
+__device__ __forceinline__ uint32_t wave_or32(uint32_t x) {
+  x |= (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0xB1, 0xf, 0xf, true);   // lanes 1 0 3 2
+  x |= (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x4E, 0xf, 0xf, true);   // lanes 2 3 0 1
+  x |= (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x141, 0xf, 0xf, true);  // half rows mirrored
+  x |= (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x140, 0xf, 0xf, true);  // rows mirrored
+  return (uint32_t)(__builtin_amdgcn_readlane((int)x, 0) | __builtin_amdgcn_readlane((int)x, 16) |
+                    __builtin_amdgcn_readlane((int)x, 32) | __builtin_amdgcn_readlane((int)x, 48));
+}
+
 __device__ __forceinline__ uint64_t wave_or64(uint64_t x) {
-#pragma unroll
-  for (int off = 32; off; off >>= 1) x |= __shfl_xor(x, off, 64);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(x >> 32));
-  return ((uint64_t)hi << 32) | lo;
+  return ((uint64_t)wave_or32((uint32_t)(x >> 32)) << 32) | wave_or32((uint32_t)x);
 }
 
 // One lane per configuration: forward kinematics link by link; per link,
