@@ -67,9 +67,12 @@ __device__ __forceinline__ uint64_t load_vertex(const LatDev &L, const uint32_t 
 // V vertices each in registers and form their terms one support vector per
 // lane (the vectors as columns, read coalesced one tile of 64 ahead); the
 // eighth adds the terms of the tile before in index order, one vertex per
-// lane, from LDS.  What is left serial is the chain of S dependent fma
-// (8 cycles each): d = 6, S = 2000 takes 25 us for up to 4096 vertices, where
-// one vertex per lane took 314 us.
+// lane, from LDS.  A dependent fma takes 4.4 cycles; what bounds the chain of
+// S of them is its operands' way through LDS, 8 cycles per double and wave
+// whatever lanes use it, so terms lie in a row per vertex and are read in
+// pairs like the weights (alone in a block: 16 cycles a term, 21 with the
+// terms of a support vector side by side).  d = 6, S = 2000: 21 us for up
+// to 1792 vertices, where one vertex per lane took 314.
 template <int D, int P, int MODE, int V>
 __global__ __launch_bounds__(512) void feval64_split_kernel(FDev F, LatDev L, const uint32_t *__restrict__ list,
                                                             uint64_t n, const unsigned long long *n_dev,
@@ -77,9 +80,9 @@ __global__ __launch_bounds__(512) void feval64_split_kernel(FDev F, LatDev L, co
                                                             const int32_t *__restrict__ vraw,
                                                             double *__restrict__ out, unsigned long long *stamp) {
   put_stamp(stamp);
-  constexpr int T = IP_COL_PAD, NW = 7, G = NW * V, LD = G | 1;
+  constexpr int T = IP_COL_PAD, NW = 7, G = NW * V, TS = T + 2;
   constexpr uint64_t S4 = MODE == 0 ? 4 : 1;
-  __shared__ double term[2][T * LD];
+  __shared__ __align__(16) double term[2][G * TS];  // a row per vertex
   __shared__ __align__(16) double alpha[2][T];
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
@@ -106,9 +109,9 @@ __global__ __launch_bounds__(512) void feval64_split_kernel(FDev F, LatDev L, co
       for (int t = 0; t <= nt; ++t) {
         if (t < nt && v0 < n) {
           if (wv == 0) alpha[t & 1][lane] = al;
-          double *tw = &term[t & 1][lane * LD + wv * V];
+          double *tw = &term[t & 1][wv * V * TS + lane];
 #pragma unroll
-          for (int r = 0; r < V; ++r) tw[r] = sv_term<D, P>(F, sv, x[r]);
+          for (int r = 0; r < V; ++r) tw[r * TS] = sv_term<D, P>(F, sv, x[r]);
           __builtin_amdgcn_sched_barrier(0);
           fetch((t + 1 < nt ? (int64_t)(t + 1) * T : 0) + lane);
         }
@@ -119,7 +122,7 @@ __global__ __launch_bounds__(512) void feval64_split_kernel(FDev F, LatDev L, co
       const int c = lane < G ? lane : 0;
       for (int t = 0; t <= nt; ++t) {
         if (t > 0) {
-          const double *tr = term[(t - 1) & 1] + c;
+          const double *tr = term[(t - 1) & 1] + c * TS;
           const double *al = alpha[(t - 1) & 1];
           const int64_t m = F.S - (int64_t)(t - 1) * T;
           if (m >= T) {
@@ -129,14 +132,14 @@ __global__ __launch_bounds__(512) void feval64_split_kernel(FDev F, LatDev L, co
 #pragma unroll
             for (int s = 0; s < H; ++s) {
               a0[s] = al[s];
-              b0[s] = tr[s * LD];
+              b0[s] = tr[s];
             }
 #pragma unroll
             for (int h = 0; h < T; h += 2 * H) {
 #pragma unroll
               for (int s = 0; s < H; ++s) {
                 a1[s] = al[h + H + s];
-                b1[s] = tr[(h + H + s) * LD];
+                b1[s] = tr[h + H + s];
               }
               __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -145,7 +148,7 @@ __global__ __launch_bounds__(512) void feval64_split_kernel(FDev F, LatDev L, co
 #pragma unroll
                 for (int s = 0; s < H; ++s) {
                   a0[s] = al[h + 2 * H + s];
-                  b0[s] = tr[(h + 2 * H + s) * LD];
+                  b0[s] = tr[h + 2 * H + s];
                 }
               }
               __builtin_amdgcn_sched_barrier(0);
@@ -153,7 +156,7 @@ __global__ __launch_bounds__(512) void feval64_split_kernel(FDev F, LatDev L, co
               for (int s = 0; s < H; ++s) acc = fma(a1[s], b1[s], acc);
             }
           } else {
-            for (int s = 0; s < (int)m; ++s) acc = fma(al[s], tr[s * LD], acc);
+            for (int s = 0; s < (int)m; ++s) acc = fma(al[s], tr[s], acc);
           }
         }
         __syncthreads();
@@ -193,9 +196,9 @@ __global__ __launch_bounds__(256, (P < 0 || R < 4) ? 4 : 2) void feval64_tile_ke
 
 // Which kernel, by the vertex count n (times in us at d = 6, p = 3,
 // S = 2000).  Up to 16384 vertices one lane each fills less than one wave per
-// CU, and the split form is the faster (4096: 25 against 90; 16384: 68
+// CU, and the split form is the faster (4096: 23 against 90; 16384: 60
 // against 92), with as few vertices per forming wave as still give each CU a
-// block (1000: 23.5 with one, 27.8 with four; S = 200: 7.3 and 8.0).  Above, the least number of vertices per lane that still
+// block (1000: 21 with one, 24 with four).  Above, the least number of vertices per lane that still
 // fills the SIMDs once: 65 536 lanes are one wave on each (65536: 1 per lane
 // 101, 2 per lane 148; 200003: 1, 2 and 4 per lane 264, 209, 232; 1048576:
 // 1006, 772, 730).  The Gaussian term is 34 operations long and needs no
