@@ -198,12 +198,12 @@ __global__ __launch_bounds__(256, (P < 0 || R < 4) ? 4 : 2) void feval64_tile_ke
 // S = 2000).  Up to 16384 vertices one lane each fills less than one wave per
 // CU, and the split form is the faster (4096: 23 against 90; 16384: 60
 // against 92), with as few vertices per forming wave as still give each CU a
-// block (1000: 21 with one, 24 with four).  Above, the least number of vertices per lane that still
-// fills the SIMDs once: 65 536 lanes are one wave on each (65536: 1 per lane
-// 101, 2 per lane 148; 200003: 1, 2 and 4 per lane 264, 209, 232; 1048576:
-// 1006, 772, 730).  The Gaussian term is 34 operations long and needs no
-// sharing of the records (d = 5, S = 300, 1048576 vertices: 351 with one per
-// lane, 438 with two).
+// block (1000: 21 with one, 24 with four).  Above, the least number of
+// vertices per lane that still fills the SIMDs once: 65 536 lanes are one wave
+// on each (65536: 1 per lane 101, 2 per lane 148; 200003: 1, 2 and 4 per lane
+// 264, 209, 232; 1048576: 1006, 772, 730).  The Gaussian term is 34 operations
+// long and needs no sharing of the records (d = 5, S = 300, 1048576 vertices:
+// 351 with one per lane, 438 with two).
 constexpr uint64_t kSplitMax = 16384;
 
 // One call of the canonical sum: see the MODEs above and launch_feval64.
@@ -652,8 +652,9 @@ __global__ __launch_bounds__(256) void seed_kernel(FDev F, LatDev L, const doubl
 // gradient weight), one tile of 48 vectors ahead; waves 0 and 1 add them, one
 // lane per (sum, start), f and the d gradient components side by side, each
 // in index order.  Serial per step: S dependent fma instead of S times the
-// whole term (d = 6, S = 2000, 20 steps, 3001 starts: 7.06 ms with one lane
-// per start).
+// whole term; both operands of each come through LDS, which bounds it, as rows
+// read in pairs (d = 6, S = 2000, 20 steps, 3001 starts: 7.06 ms with one lane
+// per start, 0.76 with single reads, 0.67 now).
 constexpr int kSeedG = 16, kSeedT = 48;
 // One lane per start takes the same time up to 65 536 starts (a wave per
 // SIMD); the split form grows from four blocks per CU on.  Both at d = 5,
@@ -665,8 +666,9 @@ template <int D, bool RBF>
 __global__ __launch_bounds__(512) void seed_split_kernel(FDev F, LatDev L, const double *__restrict__ q0, uint64_t n,
                                                          int iters, double *__restrict__ q, double *__restrict__ fq) {
   constexpr int G = kSeedG, T = kSeedT, NR = T / 24;  // 24 vectors per round of the six forming waves
-  __shared__ double val[2][2][T * G];  // [buffer][sum factor, gradient weight]
-  __shared__ double recs[2][T * 8];
+  constexpr int TS = T + 2;                           // a row per start or component, read in pairs
+  __shared__ __align__(16) double val[2][2][G * TS];  // [buffer][sum factor, gradient weight]
+  __shared__ __align__(16) double recs[2][(D + 1) * TS];
   __shared__ double xs[G * 8], res[8 * G];
   __shared__ int done[G];
   const int tid = threadIdx.x, g = tid & (G - 1);
@@ -691,8 +693,8 @@ __global__ __launch_bounds__(512) void seed_split_kernel(FDev F, LatDev L, const
         const int col = cc ? cc - 1 : D;
         for (int t = 0; t <= nt; ++t) {
           if (t > 0) {
-            const double *v = &val[(t - 1) & 1][cc ? 1 : 0][g];
-            const double *r = &recs[(t - 1) & 1][col];
+            const double *v = &val[(t - 1) & 1][cc ? 1 : 0][g * TS];
+            const double *r = &recs[(t - 1) & 1][col * TS];
             const int m = (int)(F.S - (int64_t)(t - 1) * T < T ? F.S - (int64_t)(t - 1) * T : T);
             int s = 0;
             if (m == T) {
@@ -702,8 +704,8 @@ __global__ __launch_bounds__(512) void seed_split_kernel(FDev F, LatDev L, const
               auto get = [&](double *a, double *b, int s0) {
 #pragma unroll
                 for (int u = 0; u < H; ++u) {
-                  a[u] = v[(s0 + u) * G];
-                  b[u] = r[(s0 + u) * 8];
+                  a[u] = v[s0 + u];
+                  b[u] = r[s0 + u];
                 }
               };
               auto add = [&](const double *a, const double *b) {
@@ -721,7 +723,7 @@ __global__ __launch_bounds__(512) void seed_split_kernel(FDev F, LatDev L, const
                 add(a1, b1);
               }
             }
-            for (; s < m; ++s) acc = fma(v[s * G], RBF && cc ? xc - r[s * 8] : r[s * 8], acc);
+            for (; s < m; ++s) acc = fma(v[s], RBF && cc ? xc - r[s] : r[s], acc);
           }
           __syncthreads();
         }
@@ -749,11 +751,11 @@ __global__ __launch_bounds__(512) void seed_split_kernel(FDev F, LatDev L, const
               const int s = k * 24 + sr;
               double e, w;
               grad_factors<D, RBF>(F, sv[k], x, pg, &e, &w);
-              val[t & 1][0][s * G + g] = e;
-              val[t & 1][1][s * G + g] = w;
+              val[t & 1][0][g * TS + s] = e;
+              val[t & 1][1][g * TS + s] = w;
               if (g == 0) {
 #pragma unroll
-                for (int j = 0; j <= D; ++j) recs[t & 1][s * 8 + j] = sv[k][j];
+                for (int j = 0; j <= D; ++j) recs[t & 1][j * TS + s] = sv[k][j];
               }
             }
             __builtin_amdgcn_sched_barrier(0);
