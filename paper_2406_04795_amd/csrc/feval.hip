@@ -646,6 +646,68 @@ __global__ __launch_bounds__(256) void seed_kernel(FDev F, LatDev L, const doubl
   }
 }
 
+// Canonical polynomial f and gradient at x (the order of ip.h's ip_seed_search): per
+// support vector in index order, read as a wave-uniform record.
+template <int D>
+__device__ __forceinline__ double f_grad(const FDev &F, const double *x, double *g) {
+  double acc = 0.0;
+#pragma unroll
+  for (int j = 0; j < D; ++j) g[j] = 0.0;
+  const double pg = (double)F.p * F.gamma;
+  for (int64_t i = 0; i < F.S; ++i) {
+    const double *rec = F.rec + i * 8;
+    double dot = 0.0;
+#pragma unroll
+    for (int j = 0; j < D; ++j) dot = fma(rec[j], x[j], dot);
+    const double t = fma(F.gamma, dot, F.coef0);
+    double tp1 = 1.0;
+    if (F.p > 1) {
+      tp1 = t;
+      for (int r = 2; r < F.p; ++r) tp1 = tp1 * t;
+    }
+    acc = fma(rec[D], tp1 * t, acc);
+    const double w = (rec[D] * tp1) * pg;
+#pragma unroll
+    for (int j = 0; j < D; ++j) g[j] = fma(w, rec[j], g[j]);
+  }
+  return acc + F.bias;
+}
+
+// Very many starts of a polynomial, one lane per start: with three waves on
+// every SIMD a scalar load per record is hidden, and is cheaper than the
+// record's way through LDS and into vector registers (d = 6, S = 2000, 20
+// steps: 131 072 starts 6.87 ms, 2^20 27.6; through LDS 5.37 and 31.0; two
+// starts per lane 31.0 too; d = 5, S = 500, 10 steps: 131 072: 0.93 and 0.72,
+// 262 144: 1.15 and 1.33).  The Gaussian is faster through LDS at any count.
+constexpr int64_t kSeedMany = 196608;
+
+template <int D>
+__global__ __launch_bounds__(256) void seed_many_kernel(FDev F, LatDev L, const double *__restrict__ q0,
+                                                        uint64_t n, int iters, double *__restrict__ q, double *__restrict__ fq) {
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
+    double x[D], g[D];
+#pragma unroll
+    for (int j = 0; j < D; ++j) x[j] = q0[i * D + j];
+    for (int it = 0; it < iters; ++it) {
+      const double fv = f_grad<D>(F, x, g);
+      double n2 = 0.0;
+#pragma unroll
+      for (int j = 0; j < D; ++j) n2 = fma(g[j], g[j], n2);
+      if (!(n2 > 0.0)) break;
+      const double c = fv / n2;
+#pragma unroll
+      for (int j = 0; j < D; ++j) {
+        const double v = fma(-c, g[j], x[j]);
+        x[j] = v < L.lo[j] ? L.lo[j] : (v > L.hi[j] ? L.hi[j] : v);
+      }
+    }
+    const double fv = f_grad<D>(F, x, g);
+#pragma unroll
+    for (int j = 0; j < D; ++j) q[i * D + j] = x[j];
+    fq[i] = fv;
+  }
+}
+
 // The same search with the sums of a step formed side by side, for few starts:
 // a block takes 16 starts.  Waves 2 to 7 form, per support vector and start,
 // the two factors that the sums share (t^p or the exponential, and the
@@ -811,6 +873,8 @@ int ip_seed_search_impl(ip_ctx *ctx, const ip_problem *p, const double *q0, int6
     IP_SDK((seed_split_kernel<DD, false>), 512); \
   else if (rbf)                                  \
     IP_SDK((seed_kernel<DD, true>), 256);        \
+  else if (n > kSeedMany)                        \
+    IP_SDK((seed_many_kernel<DD>), 256);         \
   else                                           \
     IP_SDK((seed_kernel<DD, false>), 256)
   switch (p->d) {

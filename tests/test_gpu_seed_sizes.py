@@ -29,7 +29,7 @@ def ctx(ip):
 @pytest.mark.parametrize("d,S,p,n,iters", [
     (2, 1, 1, 1, 3), (3, 47, 2, 15, 4), (4, 48, 3, 16, 5), (5, 49, 4, 17, 6), (6, 97, 5, 33, 3), (7, 96, 3, 12288, 0),
     (3, 3, 3, 12288, 1), (6, 65, 3, 12289, 2), (2, 64, 1, 12289, 1), (7, 5, 4, 13000, 1), (4, 50, 0, 31, 4),
-    (7, 48, 0, 16, 2), (5, 65, 0, 12289, 1)])
+    (7, 48, 0, 16, 2), (5, 65, 0, 12289, 1), (2, 7, 2, 196608, 1), (2, 7, 2, 196609, 1)])
 def test_seed_search_launch_edges(ip, ctx, d, S, p, n, iters):
     import torch
     rng = np.random.default_rng(100 * d + S)
