@@ -1332,10 +1332,10 @@ constexpr int kDeferStage = 32;
 // the monomial coefficients (FP64 and FP32), the template points with their
 // face masks, the faces' point masks, the edges and face groups.  Per wave:
 // two append stages, the start bitmap, the sign masks over the points and
-// the list of the active groups, the edge stage, the stage of the deferred
-// simplices, the active point list and the sign codes.
+// the list of the active groups, the edge stage, the active point list, the
+// sign codes and, in the pass that defers simplices (MODE 0), their stage.
 struct SubLayout {
-  uint32_t lmat, lc, stage_s, stage_d, lpts, lpf, lpv, sbm, est, dst, ledge, lgrp, lmask, agl, plist, code, total;
+  uint32_t lmat, lc, stage_s, stage_d, lpts, lpf, lpv, sbm, est, ledge, lgrp, lmask, agl, plist, code, dst, total;
 };
 
 __host__ __device__ inline uint32_t sub_take(uint32_t &o, size_t bytes) {
@@ -1345,11 +1345,13 @@ __host__ __device__ inline uint32_t sub_take(uint32_t &o, size_t bytes) {
 }
 
 // NP template points, NE template edges, M monomials (0: no coefficients),
-// NV = 2^(d+1) vertex subsets.
+// NV = 2^(d+1) vertex subsets, `defers`: with the stage of the deferred
+// simplices, which comes last: whether a template fits (kSubLdsMax) is judged
+// without it (at d = 4, k = 9 its 512 bytes pass that limit).
 // The frame and the FP32 coefficients come first, at fixed offsets (0 and
 // kSubLc), so that the evaluation reads them with immediate offsets.
 constexpr uint32_t kSubLc = 88 * 8;
-__host__ __device__ inline SubLayout sub_layout(int NP, int NE, int M, int NV) {
+__host__ __device__ inline SubLayout sub_layout(int NP, int NE, int M, int NV, bool defers) {
   const int NVW = (NV + 63) / 64, NPW = (NP + 63) / 64, SBW = (NE + 63) / 64;
   SubLayout L;
   uint32_t o = 0;
@@ -1362,13 +1364,13 @@ __host__ __device__ inline SubLayout sub_layout(int NP, int NE, int M, int NV) {
   L.lpv = sub_take(o, (size_t)NV * NPW * 8);
   L.sbm = sub_take(o, (size_t)kWaves * SBW * 8);
   L.est = sub_take(o, (size_t)kWaves * kEdgeStage * 4);
-  L.dst = sub_take(o, (size_t)kWaves * kDeferStage * 4);
   L.ledge = sub_take(o, (size_t)NE * 4);
   L.lgrp = sub_take(o, (size_t)NV * 4);
   L.lmask = sub_take(o, (size_t)kWaves * 2 * NPW * 8);
   L.agl = sub_take(o, (size_t)kWaves * NV * 4);
   L.plist = sub_take(o, (size_t)kWaves * NP * 2);
   L.code = sub_take(o, (size_t)kWaves * NP);
+  L.dst = sub_take(o, defers ? (size_t)kWaves * kDeferStage * 4 : 0);
   L.total = o;
   return L;
 }
@@ -1554,7 +1556,7 @@ __global__ __launch_bounds__(kBlock, 4) void subdivide_kernel(LatDev Lf, LatDev 
   const int M = MODE == 3 ? 0 : Q.M;
   const int SBW = (NE + 63) / 64;
   const int NPW = (NP + 63) / 64;
-  const SubLayout Ly = sub_layout(NP, NE, M, NV);
+  const SubLayout Ly = sub_layout(NP, NE, M, NV, MODE == 0);
   uint64_t *stage_s = (uint64_t *)(smem + Ly.stage_s) + (size_t)wib * kSubStage;
   uint64_t *stage_d = (uint64_t *)(smem + Ly.stage_d) + (size_t)wib * kSubStage;
   // fine frame and FP32 coefficients in LDS at fixed offsets: read at
@@ -2254,6 +2256,8 @@ int run_with_replay(ip_ctx *ctx, BatchSink &g, int64_t &regrows, F launch) {
   return set_counter(ctx, &ctx->ctr_dev->n_direct, dir_lo + n);
 }
 
+// Largest template, in LDS per block without the stage of the deferred
+// simplices (of the 160 KiB of a CU).
 constexpr size_t kSubLdsMax = 64 * 1024;
 constexpr uint64_t kSubGrid = 4096;
 
@@ -2290,7 +2294,7 @@ int launch_sub(ip_ctx *ctx, const ip_problem *p, const SubArgs &a, const uint64_
                uint64_t n, VEnt *fvt, uint64_t fvt_mask, uint32_t *eval, const BatchSink &g, uint32_t *defer,
                const SubPrep<D> *prep, const uint32_t *pslot = nullptr) {
   if (n == 0) return IP_OK;
-  const size_t lds = sub_layout(a.NP, a.NE, MODE == 3 ? 0 : p->poly.M, 1 << (D + 1)).total;
+  const size_t lds = sub_layout(a.NP, a.NE, MODE == 3 ? 0 : p->poly.M, 1 << (D + 1), MODE == 0).total;
   const uint64_t blocks = std::min<uint64_t>((n + kWaves - 1) / kWaves, kSubGrid);
   const SubOut so = g.sub_out(a.cvt, a.cvt_mask);
 #define IP_SUB(PP)                                                                                                  \
@@ -2950,7 +2954,7 @@ int trace_batch(ip_ctx *ctx, const ip_problem *p, uint64_t budget, bool cert, ip
     return ip_fail(ctx, IP_ERANGE, "coarse simplex keys do not fit 63 bits for this domain and k");
   Template T = make_template(D, k);
   const int NP = (int)T.pts.size(), NE = (int)T.edges.size();
-  if (sub_layout(NP, NE, p->poly.M, 1 << (D + 1)).total > kSubLdsMax || NE > 0x7fff)
+  if (sub_layout(NP, NE, p->poly.M, 1 << (D + 1), false).total > kSubLdsMax || NE > 0x7fff)
     return ip_fail(ctx, IP_EINVAL, "subdivision template does not fit one workgroup's LDS (reduce k)");
   // ---- coarse trace (Sec. V-B: trace at scale k * lambda)
   Run s;
