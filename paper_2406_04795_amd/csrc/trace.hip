@@ -222,6 +222,12 @@ __global__ __launch_bounds__(kExpand) void expand_kernel(LatDev L, OutRec *out, 
         if (level) ctr->ticks_expand += now - ctr->t_mark;
         ctr->t_mark = now;
         ctr->lv[(level + 1) & 3u] = hi;
+      }
+      if (!stopped && halt != IP_STOP_CSLOT) {
+        // what the evaluation before left open: that of the last level, of
+        // the seeds (level 0), or of this level before a larger vertex table
+        ctr->fb_total += ctr->n_fb;
+        ctr->c64_total += ctr->n_cert64;
         ctr->n_fb = 0;
         ctr->n_cert64 = 0;
       }
@@ -245,8 +251,6 @@ __global__ __launch_bounds__(kExpand) void expand_kernel(LatDev L, OutRec *out, 
         for (int k = 0; k < IP_REGIONS; ++k) ctr->n_cofl[nxt][k * IP_LINE] = 0;
         ctr->cof_total += nc;
         ctr->levels += 1;
-        ctr->fb_total += ctr->n_fb;
-        ctr->c64_total += ctr->n_cert64;
       }
     }
   }
@@ -810,7 +814,6 @@ int trace_direct(Run &s, ip_stats &st, uint64_t *n_out_ret) {
   IP_TRY_HIP(ctx, hipGetLastError());
   // estimates that shape the next launches: frontier edges, new vertices
   uint64_t edges = seed_verts * D / 2, verts = seed_verts;
-  int64_t fb_seen = 0, c64_seen = 0;  // of evaluations whose level was queued again
   uint32_t level = 0, chunk = 0;
   bool from_edges = false;            // the first level queued starts with pass 2
   auto queue = [&]() -> int {
@@ -868,8 +871,6 @@ int trace_direct(Run &s, ip_stats &st, uint64_t *n_out_ret) {
     if (stop & IP_STOP_OUT) IP_TRY(out_reserve(s, hi + cof + 1, hi));
     if (stop & IP_STOP_VT) {
       IP_TRY(zero_fail_flags(ctx));
-      fb_seen += (int64_t)c->n_fb;
-      c64_seen += (int64_t)c->n_cert64;
       verts = 2 * n_ev + 64;
       IP_TRY(vt_grow<D>(s, pow2_at_least(std::max<uint64_t>(nv * 4, s.vt_cap * 2)), hi));
       // slots moved: pass 1 again, so that CSL points into the new table;
@@ -884,8 +885,8 @@ int trace_direct(Run &s, ip_stats &st, uint64_t *n_out_ret) {
     IP_TRY(zero_field(ctx, (unsigned long long *)&dev->stop));
     IP_TRY(queue());
   }
-  s.n_fallback += (int64_t)c->fb_total + fb_seen;
-  s.n_settled64 += (int64_t)c->c64_total + c64_seen;
+  s.n_fallback += (int64_t)c->fb_total;
+  s.n_settled64 += (int64_t)c->c64_total;
   st.ms_feval += (double)c->ticks_eval / ctx->ticks_per_ms;
   st.ms_expand += (double)c->ticks_expand / ctx->ticks_per_ms;
   st.levels += (int)c->levels;
