@@ -183,7 +183,9 @@ __global__ void seed_edges_kernel(LatDev L, const double *seeds, int64_t ns, VEn
 // block decides from values that no block changes meanwhile; when it cannot,
 // block 0 sets `stop`, the passes queued behind do nothing, and the host,
 // which reads the counters some levels late, mends the cause and queues
-// level `stop_level` again.  Pass 1 is idempotent.
+// level `stop_level` again.  Pass 1 is idempotent.  Time is charged from
+// t_mark, the start of the pass before; the host clears it when it goes on
+// after a stop, so that mending is charged to neither sum.
 template <int D, bool EDGES>
 __global__ __launch_bounds__(kExpand) void expand_kernel(LatDev L, OutRec *out, uint64_t out_cap, VEnt *vt,
                                                         uint64_t vt_mask, uint32_t *cslot, uint64_t cslot_cap,
@@ -209,6 +211,10 @@ __global__ __launch_bounds__(kExpand) void expand_kernel(LatDev L, OutRec *out, 
       halt = IP_STOP_CSLOT;
     if (first) {
       const unsigned long long now = wall_clock64();
+      if (!stopped) {
+        if (ctr->t_mark) ctr->ticks_expand += now - ctr->t_mark;
+        ctr->t_mark = now;
+      }
       if (stopped) {
         // nothing for the evaluations queued behind the level that stopped
         if (level == ctr->stop_level + 1) {
@@ -219,8 +225,6 @@ __global__ __launch_bounds__(kExpand) void expand_kernel(LatDev L, OutRec *out, 
         ctr->stop = halt;
         ctr->stop_level = level;
       } else {
-        if (level) ctr->ticks_expand += now - ctr->t_mark;
-        ctr->t_mark = now;
         ctr->lv[(level + 1) & 3u] = hi;
       }
       if (!stopped && halt != IP_STOP_CSLOT) {
@@ -238,14 +242,16 @@ __global__ __launch_bounds__(kExpand) void expand_kernel(LatDev L, OutRec *out, 
     if (ctr->vt_fail || nv * 2 > vt_mask + 1) halt |= IP_STOP_VT;
     if (hi + nc + 1 > out_cap) halt |= IP_STOP_OUT;
     if (first && !stopped) {
+      const unsigned long long now = wall_clock64();
+      if (ctr->t_mark) {
+        ctr->ticks_expand += ctr->t_eval - ctr->t_mark;
+        ctr->ticks_eval += now - ctr->t_eval;
+      }
+      ctr->t_mark = now;
       if (halt) {
         ctr->stop = halt;
         ctr->stop_level = level;
       } else {
-        const unsigned long long now = wall_clock64();
-        ctr->ticks_expand += ctr->t_eval - ctr->t_mark;
-        ctr->ticks_eval += now - ctr->t_eval;
-        ctr->t_mark = now;
         ctr->vt_cnt[nxt] = nv;
         ctr->n_ev[nxt] = 0;
         for (int k = 0; k < IP_REGIONS; ++k) ctr->n_cofl[nxt][k * IP_LINE] = 0;
@@ -882,6 +888,7 @@ int trace_direct(Run &s, ip_stats &st, uint64_t *n_out_ret) {
       if (c->vt_fail) return ip_fail(ctx, IP_EDEVICE, "internal: traced edge lost its vertex");
     }
     from_edges = (stop & (IP_STOP_CSLOT | IP_STOP_VT)) == 0;
+    IP_TRY(zero_field(ctx, &dev->t_mark));
     IP_TRY(zero_field(ctx, (unsigned long long *)&dev->stop));
     IP_TRY(queue());
   }
