@@ -239,10 +239,9 @@ struct PolyDev {
 };
 
 // Atomics on one address, or on one cache line, cost about 12 ns each whoever
-// issues them.  Sums that many blocks add to are therefore spread over lines
-// (IP_LINE apart), append counters that run at the same time have a line of
-// their own, and a list that every wave appends to is filled as IP_REGIONS
-// lists side by side.
+// issues them.  Sums that many blocks add to are therefore spread over
+// IP_REGIONS lines (IP_LINE apart), and append counters that run at the same time have a line
+// of their own.
 #define IP_LINE 16
 #define IP_REGIONS 16
 #define IP_TALLIES 4
@@ -252,7 +251,6 @@ struct Counters {
   unsigned long long n_fb;       // FP64 fallback list length
   unsigned long long n_fb_total; // fallbacks over the whole call
   unsigned long long n_cert64;   // vertices settled by the FP64 monomial tier
-  unsigned long long n_direct;   // owner-emitted fine edges (batch mode)
   unsigned int vt_fail;          // vertex-table insert found the table full
   unsigned int et_fail;          // edge-table insert found the table full
   // breadth-first search (trace.hip, "Level chain"); the two-entry fields go
@@ -268,11 +266,10 @@ struct Counters {
   // a line each
   __attribute__((aligned(8 * IP_LINE))) unsigned long long n_out;  // output-list length (== edges in ET)
   __attribute__((aligned(8 * IP_LINE))) unsigned long long n_aux;  // general-purpose append counter
-  // partial sums: cofaces of the level's edges; subdivision tallies (IP_T_*);
-  // lengths of the owner-emitted lists of one subdivision launch
+  __attribute__((aligned(8 * IP_LINE))) unsigned long long n_direct;  // owner-emitted fine edges (batch mode)
+  // partial sums: cofaces of the level's edges; subdivision tallies (IP_T_*)
   __attribute__((aligned(8 * IP_LINE))) unsigned long long n_cofl[2][IP_REGIONS * IP_LINE];
   unsigned long long tally[IP_TALLIES][IP_REGIONS * IP_LINE];
-  unsigned long long region[IP_REGIONS * IP_LINE];
 };
 
 // Tallies of a subdivision launch: intersecting (simplex, template edge)

@@ -1410,8 +1410,8 @@ struct SubOut {
   uint64_t *et_keys;  // global edge set (edges without an owner)
   uint64_t et_mask;
   uint64_t *out_s;    // its keys in insertion order
-  uint64_t *out_d;    // owner-emitted keys: IP_REGIONS lists of rcap entries
-  uint64_t rcap;      // (appends past a list's end are counted, not written)
+  uint64_t *out_d;    // owner-emitted keys
+  uint64_t dcap;      // capacity of out_d (appends past it are counted, not written)
 };
 
 // Bit b of word t set when vertex i belongs to the vertex subset 64 t + b.
@@ -1604,13 +1604,11 @@ __global__ __launch_bounds__(kBlock, 4) void subdivide_kernel(LatDev Lf, LatDev 
   __syncthreads();
   int sn = 0, snd = 0;
   auto put_s = [&](unsigned long long pos, uint64_t key) { so.out_s[pos] = key; };
-  // blocks append to IP_REGIONS lists, each with its counter: with one list
-  // the 514 M keys of the benchmark took 4 M turns of 12 ns at its counter
-  const uint32_t reg = blockIdx.x % IP_REGIONS;
-  uint64_t *const out_d = so.out_d + (uint64_t)reg * so.rcap;
-  unsigned long long *const ctr_d = &ctr->region[reg * IP_LINE];
+  // one list for all waves: 16 lists side by side with a counter each, and a
+  // gather behind, took the same time at the benchmark (60.4 and 1.1 ms
+  // against 61.6) and 14 bytes more per cell
   auto put_d = [&](unsigned long long pos, uint64_t key) {
-    if (pos < so.rcap) out_d[pos] = key;
+    if (pos < so.dcap) so.out_d[pos] = key;
   };
   uint32_t *dst = (uint32_t *)(smem + Ly.dst) + (size_t)wib * kDeferStage;
   int sdf = 0;
@@ -1641,7 +1639,7 @@ __global__ __launch_bounds__(kBlock, 4) void subdivide_kernel(LatDev Lf, LatDev 
         }
       }
       stage_put<kSubStage>(stage_s, sn, nw, key, put_s, &ctr->n_out);
-      stage_put<kSubStage>(stage_d, snd, dir, key, put_d, ctr_d);
+      stage_put<kSubStage>(stage_d, snd, dir, key, put_d, &ctr->n_direct);
     }
     wave_lds_sync();
     kn = 0;
@@ -1881,7 +1879,7 @@ __global__ __launch_bounds__(kBlock, 4) void subdivide_kernel(LatDev Lf, LatDev 
           kn += sne - b < 64 ? sne - b : 64;
         } else {
           stage_put<kSubStage>(stage_s, sn, nw, key, put_s, &ctr->n_out);
-          stage_put<kSubStage>(stage_d, snd, dir, key, put_d, ctr_d);
+          stage_put<kSubStage>(stage_d, snd, dir, key, put_d, &ctr->n_direct);
         }
       }
       wave_lds_sync();
@@ -1922,7 +1920,7 @@ __global__ __launch_bounds__(kBlock, 4) void subdivide_kernel(LatDev Lf, LatDev 
   if (MODE == 3) drain_keys();
   stage_flush_block(stage_s, sn, put_s, &ctr->n_out);
   __syncthreads();
-  stage_flush_block(stage_d, snd, put_d, ctr_d);
+  stage_flush_block(stage_d, snd, put_d, &ctr->n_direct);
   if (MODE == 0) {
     __syncthreads();
     stage_flush_block(dst, sdf, put_df, &ctr->n_aux);
@@ -1940,21 +1938,8 @@ __global__ __launch_bounds__(kBlock, 4) void subdivide_kernel(LatDev Lf, LatDev 
   if (threadIdx.x < IP_TALLIES) {
     unsigned long long t = 0;
     for (int w = 0; w < kWaves; ++w) t += wt[w][threadIdx.x];
-    if (t) atomicAdd(&ctr->tally[threadIdx.x][reg * IP_LINE], t);
+    if (t) atomicAdd(&ctr->tally[threadIdx.x][(blockIdx.x % IP_REGIONS) * IP_LINE], t);
   }
-}
-
-// The IP_REGIONS lists of a subdivision launch one after the other: list r
-// (rcap apart, cnt[r * IP_LINE] entries) to out + the lengths before it.
-__global__ __launch_bounds__(256) void gather_regions_kernel(const uint64_t *__restrict__ src, uint64_t rcap,
-                                                             const unsigned long long *__restrict__ cnt,
-                                                             uint64_t *__restrict__ out) {
-  const uint32_t r = blockIdx.y;
-  uint64_t o = 0;
-  for (uint32_t q = 0; q < r; ++q) o += cnt[q * IP_LINE];
-  const uint64_t n = cnt[r * IP_LINE];
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
-    out[o + i] = src[r * rcap + i];
 }
 
 // Ends of the listed edges as raw vertices: vraw[2r] = a, vraw[2r + 1] = b.
@@ -2130,17 +2115,15 @@ int grow_points(ip_ctx *ctx, uint64_t lo, uint64_t hi, double *&pts, uint64_t &l
 // kept <= 1/2) with its keys in insertion order (skeys, capacity et_cap:
 // every key in the set was appended once).  FP64 mode keeps the points of
 // both lists too (dpts, spts, SoA with column strides dld, sld).
-// Each launch's owner-emitted keys arrive in IP_REGIONS lists (rkeys, rcap
-// entries each) and are appended to dkeys from there.
 struct BatchSink {
   ip_ctx *ctx = nullptr;
-  uint64_t *et = nullptr, *skeys = nullptr, *dkeys = nullptr, *rkeys = nullptr;
-  uint64_t et_cap = 0, dcap = 0, rcap = 0;
+  uint64_t *et = nullptr, *skeys = nullptr, *dkeys = nullptr;
+  uint64_t et_cap = 0, dcap = 0;
   double *dpts = nullptr, *spts = nullptr;
   uint64_t dld = 0, sld = 0;
   explicit BatchSink(ip_ctx *c) : ctx(c) {}
   ~BatchSink() {
-    for (void *p : {(void *)et, (void *)skeys, (void *)dkeys, (void *)rkeys, (void *)dpts, (void *)spts})
+    for (void *p : {(void *)et, (void *)skeys, (void *)dkeys, (void *)dpts, (void *)spts})
       if (p) ip_dfree(ctx, p);
   }
   // Grow the set to cap (power of two), rebuilt from its first n keys.
@@ -2174,24 +2157,8 @@ struct BatchSink {
     dcap = cap;
     return IP_OK;
   }
-  // Room for cap keys in each of a launch's lists (their contents go).
-  int reserve_regions(uint64_t cap) {
-    IP_TRY_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    if (rkeys) ip_dfree(ctx, rkeys);
-    rkeys = nullptr;
-    rcap = 0;
-    IP_TRY(alloc(ctx, (void **)&rkeys, cap * IP_REGIONS * 8));
-    rcap = cap;
-    return IP_OK;
-  }
-  void drop_regions() {
-    (void)hipStreamSynchronize(ctx->stream);
-    if (rkeys) ip_dfree(ctx, rkeys);
-    rkeys = nullptr;
-    rcap = 0;
-  }
   SubOut sub_out(const VEnt *cvt, uint64_t cvt_mask) const {
-    return SubOut{cvt, cvt_mask, et, et_cap - 1, skeys, rkeys, rcap};
+    return SubOut{cvt, cvt_mask, et, et_cap - 1, skeys, dkeys, dcap};
   }
   // Final output: the set keys (and FP64 points) appended after the owner
   // keys; hands the key list over.
@@ -2213,13 +2180,12 @@ struct BatchSink {
 };
 
 // Runs `launch` (one subdivision launch) until it neither found the edge set
-// full nor overran a list of owner-emitted keys, then appends those lists to
-// the dir_lo keys that the sink holds (c->n_direct; updated).  Before the
-// first launch the set is grown to keep its load at most 1/2.  After a set
-// overflow the set is grown from its key list (which includes the partial
-// appends of the failed launch) and the launch replayed: set edges already
-// present are skipped.  The owner lists are rewritten by the replay, after
-// growing them to the longest that the launch reported.
+// full nor overran the owner list.  Before the first launch the set is grown
+// to keep its load at most 1/2.  After a set overflow the set is grown from
+// its key list (which includes the partial appends of the failed launch) and
+// the launch replayed: set edges already present are skipped.  The owner
+// list is rewound to where the launch started and rewritten by the replay,
+// after growing it to the count the launch reported.
 template <typename F>
 int run_with_replay(ip_ctx *ctx, BatchSink &g, int64_t &regrows, F launch) {
   Counters *c = ctx->ctr_host;
@@ -2228,44 +2194,27 @@ int run_with_replay(ip_ctx *ctx, BatchSink &g, int64_t &regrows, F launch) {
   uint64_t n_keys = c->n_out;
   bool set_failed = false;
   for (int guard = 0;; ++guard) {
-    if (guard > 40) return ip_fail(ctx, IP_ENOMEM, "edge tables cannot grow");
-    if (n_keys * 2 > g.et_cap || set_failed) {
-      IP_TRY(zero_fail_flags(ctx));
+    if (guard > 40) return ip_fail(ctx, IP_ENOMEM, "edge set cannot grow");
+    if (set_failed || n_keys * 2 > g.et_cap) {
+      if (set_failed) IP_TRY(zero_fail_flags(ctx));
       IP_TRY(g.reserve_set(pow2_at_least(std::max<uint64_t>(n_keys * 4, g.et_cap * 2)), n_keys));
       ++regrows;
     }
-    static_assert(offsetof(Counters, region) == offsetof(Counters, tally) + sizeof(Counters::tally),
-                  "the tallies and the lists' lengths are cleared together");
-    IP_TRY(fill(ctx, ctx->ctr_dev->tally, (IP_TALLIES + 1) * IP_REGIONS * IP_LINE, 0ull));
+    IP_TRY(set_counter(ctx, &ctx->ctr_dev->n_direct, dir_lo));
+    IP_TRY(fill(ctx, ctx->ctr_dev->tally, IP_TALLIES * IP_REGIONS * IP_LINE, 0ull));
     IP_TRY(launch());
     IP_TRY(read_ctr(ctx));
-    uint64_t longest = 0;
-    for (int r = 0; r < IP_REGIONS; ++r) longest = std::max<uint64_t>(longest, c->region[r * IP_LINE]);
-    const bool over = longest > g.rcap;
-    if (!c->et_fail && !over) break;
+    const bool dir_over = c->n_direct > g.dcap;
+    if (!c->et_fail && !dir_over) return IP_OK;
     set_failed = c->et_fail != 0;
     n_keys = c->n_out;
-    if (over) {
-      IP_TRY(g.reserve_regions(longest + longest / 4 + 1024));
+    if (dir_over) {
+      IP_TRY(g.reserve_direct(c->n_direct + c->n_direct / 4 + 1024, dir_lo));
       ++regrows;
     }
   }
-  const uint64_t n = line_sum(c->region);
-  if (n == 0) return IP_OK;
-  if (dir_lo + n > g.dcap) {
-    IP_TRY(g.reserve_direct(dir_lo + n + (dir_lo + n) / 4 + 1024, dir_lo));
-    ++regrows;
-  }
-  hipLaunchKernelGGL(gather_regions_kernel, dim3(grid_for(n / IP_REGIONS, 512), IP_REGIONS), dim3(256), 0, ctx->stream,
-                     (const uint64_t *)g.rkeys, g.rcap, (const unsigned long long *)ctx->ctr_dev->region,
-                     g.dkeys + dir_lo);
-  IP_TRY_HIP(ctx, hipGetLastError());
-  c->n_direct = dir_lo + n;
-  return set_counter(ctx, &ctx->ctr_dev->n_direct, dir_lo + n);
 }
 
-// Largest template, in LDS per block without the stage of the deferred
-// simplices (of the 160 KiB of a CU).
 constexpr size_t kSubLdsMax = 64 * 1024;
 constexpr uint64_t kSubGrid = 4096;
 
@@ -2596,7 +2545,6 @@ int init_sink(BatchSink &g, uint64_t nc, int k, double frac = 1.0) {
   double est = (double)nc * std::min(1.0, frac);
   for (int q = 0; q < D - 1; ++q) est *= k;
   IP_TRY(g.reserve_direct((uint64_t)std::min(est * 1.6, 4.0e9) + 1024, 0));
-  IP_TRY(g.reserve_regions((uint64_t)std::min(est * 1.8, 4.0e9) / IP_REGIONS + 65536));
   IP_TRY(g.reserve_set(pow2_at_least((uint64_t)std::min(est * 0.5, 4.0e9)), 0));
   return IP_OK;
 }
@@ -2710,7 +2658,6 @@ int subdivide_fused(ip_ctx *ctx, const ip_problem *p, const SubArgs &a, const ui
       return IP_OK;
   }
   const uint64_t n_dir = c->n_direct, n_set = c->n_out, n = n_dir + n_set;
-  g.drop_regions();
   IP_TRY(g.assemble<D>(n_dir, n_set, false));
   double *pts = nullptr;
   uint64_t ld = 0;
@@ -2927,7 +2874,6 @@ int subdivide_table(ip_ctx *ctx, const ip_problem *p, const SubArgs &a, const ui
     st.n_settled64 += f.n_settled64;
     return IP_OK;
   }
-  g.drop_regions();
   IP_TRY(g.assemble<D>(dir_done, set_done, true));
   IP_TRY(tf.flush(ctx));
   IP_TRY(tx.flush(ctx));
