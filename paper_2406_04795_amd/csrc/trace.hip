@@ -789,7 +789,7 @@ int level_pass(Run &s, uint32_t level, uint64_t edges) {
 // Levels queued between two reads of the counters, and the smallest buffers
 // a search starts with.
 constexpr uint32_t kChain = 3;
-constexpr uint64_t kOut0 = 1ull << 20, kCslot0 = 1ull << 22;
+constexpr uint64_t kOut0 = 1ull << 20, kCslot0 = 1ull << 22, kSeedVt = 1ull << 22;
 
 // Direct trace on lattice s.L (fine, or coarse in batch mode).  On return
 // s.out[0 .. *n_out) holds the traced edges and VT holds f at their ends.
@@ -804,11 +804,14 @@ int trace_direct(Run &s, ip_stats &st, uint64_t *n_out_ret) {
     ip_ctx *ctx;
     ~Drain() { (void)hipStreamSynchronize(ctx->stream); }
   } drain{ctx};
-  // the seeds' vertices fill at most a quarter of the table
+  // the seeds' vertices fill at most a quarter of the table, up to kSeedVt
+  // entries (many seeds share few vertices; if they do not, the search starts
+  // again with a larger one)
   const uint64_t seed_verts = (uint64_t)p->n_seeds * (D + 1);
-  if (seed_verts * 4 > s.vt_cap) IP_TRY(vt_init(s, pow2_at_least(seed_verts * 4)));
+  const uint64_t seed_vt = std::min<uint64_t>(pow2_at_least(seed_verts * 4), kSeedVt);
+  if (seed_vt > s.vt_cap) IP_TRY(vt_init(s, seed_vt));
   IP_TRY(out_reserve(s, std::max<uint64_t>(kOut0, seed_verts * D / 2 + 1024), 0));
-  IP_TRY(cslot_reserve(s, std::max<uint64_t>(kCslot0, seed_verts * D / 2 * MAXC)));
+  IP_TRY(cslot_reserve(s, kCslot0));
   IP_TRY_HIP(ctx, hipMemsetAsync(dev, 0, sizeof(Counters), ctx->stream));
   const unsigned sg = (unsigned)((p->n_seeds + 127) / 128);
   hipLaunchKernelGGL((seed_vertices_kernel<D>), dim3(sg), dim3(128), 0, ctx->stream, s.L, p->seeds_dev, p->n_seeds,
@@ -862,7 +865,7 @@ int trace_direct(Run &s, ip_stats &st, uint64_t *n_out_ret) {
     if (level == 0 && c->vt_fail) {
       // perhaps a seed's vertex that found no place: from the start
       if (s.vt_cap >= (1ull << 32)) return ip_fail(ctx, IP_ENOMEM, "vertex table above 2^32 entries");
-      IP_TRY(vt_init(s, s.vt_cap * 4));
+      IP_TRY(vt_init(s, std::min<uint64_t>(s.vt_cap * 4, 1ull << 32)));
       ++s.regrows;
       return trace_direct<D>(s, st, n_out_ret);
     }

@@ -46,3 +46,49 @@ def test_batch_trace(ip):
             + 8 * st["n_ncofaces"] + (12 + 16 + 40) * st["n_sigma"] + (64 << 20))
     print(f"{st['hip_malloc_bytes'] / 1e6:.1f} MB of {want / 1e6:.1f}", flush=True)
     assert st["hip_malloc_bytes"] <= want
+
+
+def test_many_seeds(ip):
+    """400 000 seeds on a small manifold: the seeds' edges (24 bytes of
+    coordinates aside, 16 bytes for each of 21 per seed) are all that grows
+    with their number; the table stops at 4 M entries of 36 bytes."""
+    d, n = 6, 400000
+    wl = I.sphere_case(d, 1.0, 0.6, n_seeds=4)
+    few, dg = _first_trace(ip, wl)
+    wl.seeds = np.ascontiguousarray(np.tile(wl.seeds, (n // 4, 1)))
+    st, dm = _first_trace(ip, wl)
+    want = few["hip_malloc_bytes"] + n * 21 * 16 + (1 << 22) * 36 + (16 << 20)
+    print(f"{st['hip_malloc_bytes'] / 1e6:.1f} MB of {want / 1e6:.1f}; 4 seeds {few['hip_malloc_bytes'] / 1e6:.1f}",
+          flush=True)
+    assert dm == dg and st["n_cells"] == few["n_cells"] > 0 and st["n_vertices"] == few["n_vertices"]
+    assert st["hip_malloc_bytes"] <= want
+
+
+def test_seeds_that_fill_the_table(ip):
+    """900 000 distinct seeds of a fine lattice: their vertices do not fit the
+    4 M entries, and the search starts again.  f is positive everywhere, so the
+    vertices of the seeds' simplices are all there is."""
+    d, n, lam = 5, 900000, 0.02
+    rng = np.random.default_rng(3)
+    fm = I.Manifold(d=d, p=1, gamma=1.0, coef0=1.0, bias=0.0, sv=np.zeros((1, d)), alpha=np.ones(1))
+    lat = I.make_lattice(d, lam, rng)
+    wl = I.Workload("fill", fm, lat, I.box(d), rng.uniform(-3.0, 3.0, (n, d)))
+    st, _ = _first_trace(ip, wl)
+    y = (wl.seeds - lat.o) @ lat.Minv.T
+    base = np.floor(y).astype(np.int64)
+    order = np.argsort(-(y - base), axis=1, kind="stable")
+    v, verts = base.copy(), [base]
+    for j in range(d):
+        v = v.copy()
+        v[np.arange(n), order[:, j]] += 1
+        verts.append(v)
+    v = np.concatenate(verts)
+    x = lat.o + v @ lat.M.T
+    v = v[(np.abs(x) <= I.PI).all(axis=1)] - v.min()
+    key = np.zeros(len(v), dtype=np.int64)
+    for j in range(d):
+        key = key * (int(v.max()) + 1) + v[:, j]
+    want = len(np.unique(key))
+    print(f"vertices {st['n_vertices']} of {want}, regrows {st['regrows']}", flush=True)
+    assert want > 4.2e6 and st["regrows"] > 0 and st["n_cells"] == 0
+    assert abs(st["n_vertices"] - want) <= 1000       # seeds within rounding of a simplex's face
