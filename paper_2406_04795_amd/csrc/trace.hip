@@ -132,6 +132,11 @@ __global__ void seed_edges_kernel(LatDev L, const double *seeds, int64_t ns, VEn
                                   OutRec *out, Counters *ctr) {
   int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= ns) return;
+  if (s == 0) {
+    // what the evaluation of their vertices left open (pass 1 clears it)
+    ctr->fb_total = ctr->n_fb;
+    ctr->c64_total = ctr->n_cert64;
+  }
   int32_t v[D], w[D], u[D + 1][D];
   locate<D>(L, seeds + s * D, v, w);
 #pragma unroll
@@ -210,30 +215,24 @@ __global__ __launch_bounds__(kExpand) void expand_kernel(LatDev L, OutRec *out, 
     else if ((hi - lo) * MAXC > cslot_cap)
       halt = IP_STOP_CSLOT;
     if (first) {
-      const unsigned long long now = wall_clock64();
-      if (!stopped) {
-        if (ctr->t_mark) ctr->ticks_expand += now - ctr->t_mark;
-        ctr->t_mark = now;
-      }
       if (stopped) {
         // nothing for the evaluations queued behind the level that stopped
         if (level == ctr->stop_level + 1) {
           ctr->n_held = ctr->n_ev[nxt];
           ctr->n_ev[0] = ctr->n_ev[1] = 0;
         }
-      } else if (halt) {
-        ctr->stop = halt;
-        ctr->stop_level = level;
       } else {
-        ctr->lv[(level + 1) & 3u] = hi;
-      }
-      if (!stopped && halt != IP_STOP_CSLOT) {
-        // what the evaluation before left open: that of the last level, of
-        // the seeds (level 0), or of this level before a larger vertex table
-        ctr->fb_total += ctr->n_fb;
-        ctr->c64_total += ctr->n_cert64;
-        ctr->n_fb = 0;
-        ctr->n_cert64 = 0;
+        const unsigned long long now = wall_clock64();
+        if (ctr->t_mark) ctr->ticks_expand += now - ctr->t_mark;
+        ctr->t_mark = now;
+        if (halt) {
+          ctr->stop = halt;
+          ctr->stop_level = level;
+        } else {
+          ctr->lv[(level + 1) & 3u] = hi;
+          ctr->n_fb = 0;
+          ctr->n_cert64 = 0;
+        }
       }
     }
   } else {
@@ -257,6 +256,8 @@ __global__ __launch_bounds__(kExpand) void expand_kernel(LatDev L, OutRec *out, 
         for (int k = 0; k < IP_REGIONS; ++k) ctr->n_cofl[nxt][k * IP_LINE] = 0;
         ctr->cof_total += nc;
         ctr->levels += 1;
+        ctr->fb_total += ctr->n_fb;
+        ctr->c64_total += ctr->n_cert64;
       }
     }
   }
@@ -823,6 +824,7 @@ int trace_direct(Run &s, ip_stats &st, uint64_t *n_out_ret) {
   IP_TRY_HIP(ctx, hipGetLastError());
   // estimates that shape the next launches: frontier edges, new vertices
   uint64_t edges = seed_verts * D / 2, verts = seed_verts;
+  int64_t fb_seen = 0, c64_seen = 0;  // of evaluations whose level was queued again
   uint32_t level = 0, chunk = 0;
   bool from_edges = false;            // the first level queued starts with pass 2
   auto queue = [&]() -> int {
@@ -880,6 +882,8 @@ int trace_direct(Run &s, ip_stats &st, uint64_t *n_out_ret) {
     if (stop & IP_STOP_OUT) IP_TRY(out_reserve(s, hi + cof + 1, hi));
     if (stop & IP_STOP_VT) {
       IP_TRY(zero_fail_flags(ctx));
+      fb_seen += (int64_t)c->n_fb;
+      c64_seen += (int64_t)c->n_cert64;
       verts = 2 * n_ev + 64;
       IP_TRY(vt_grow<D>(s, pow2_at_least(std::max<uint64_t>(nv * 4, s.vt_cap * 2)), hi));
       // slots moved: pass 1 again, so that CSL points into the new table;
@@ -895,8 +899,8 @@ int trace_direct(Run &s, ip_stats &st, uint64_t *n_out_ret) {
     IP_TRY(zero_field(ctx, (unsigned long long *)&dev->stop));
     IP_TRY(queue());
   }
-  s.n_fallback += (int64_t)c->fb_total;
-  s.n_settled64 += (int64_t)c->c64_total;
+  s.n_fallback += (int64_t)c->fb_total + fb_seen;
+  s.n_settled64 += (int64_t)c->c64_total + c64_seen;
   st.ms_feval += (double)c->ticks_eval / ctx->ticks_per_ms;
   st.ms_expand += (double)c->ticks_expand / ctx->ticks_per_ms;
   st.levels += (int)c->levels;
