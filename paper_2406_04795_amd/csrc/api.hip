@@ -63,6 +63,22 @@ int ip_dalloc(ip_ctx *ctx, void **p, size_t bytes) {
   return IP_OK;
 }
 
+int ip_dalloc_again(ip_ctx *ctx, void **p, size_t bytes, size_t last, size_t *got) {
+  if (last > bytes) {
+    std::lock_guard<std::mutex> lk(ctx->cache.mu);
+    auto it = ctx->cache.idle.lower_bound(last);
+    if (it != ctx->cache.idle.end() && it->first <= 2 * last) {
+      *p = it->second;
+      *got = it->first;
+      ctx->cache.idle_bytes -= it->first;
+      ctx->cache.idle.erase(it);
+      return IP_OK;
+    }
+  }
+  *got = bytes;
+  return ip_dalloc(ctx, p, bytes);
+}
+
 void ip_dfree(ip_ctx *ctx, void *p) {
   if (!p) return;
   std::lock_guard<std::mutex> lk(ctx->cache.mu);
@@ -395,7 +411,7 @@ void ip_destroy(ip_ctx *ctx) {
   (void)hipSetDevice(ctx->device);
   (void)hipStreamSynchronize(ctx->stream);
   DevBuf *bufs[] = {&ctx->vtf.keys, &ctx->vtf.eval, &ctx->vtf.vals, &ctx->vtf.fb, &ctx->vtc.keys,
-                    &ctx->vtc.eval, &ctx->vtc.vals, &ctx->vtc.fb, &ctx->vtf.out,  &ctx->vtc.out, &ctx->vt_aux, &ctx->scratch, &ctx->scene};
+                    &ctx->vtc.eval, &ctx->vtc.vals, &ctx->vtc.fb, &ctx->vt_aux, &ctx->scratch, &ctx->scene};
   for (DevBuf *b : bufs)
     if (b->p) ip_dfree(ctx, b->p);
   ip_cache_release(ctx);

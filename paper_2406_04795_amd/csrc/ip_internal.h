@@ -734,10 +734,11 @@ struct DevCache {
 };
 
 // Buffers of one vertex table: its VEnt entries, the pending-evaluation
-// list, in FP32 mode the per-slot bounds and the FP64 fallback list, and the
-// edges traced through it.
+// list, and in FP32 mode the per-slot bounds and the FP64 fallback list;
+// out_last: bytes of the edge list that the last search through it ended with.
 struct VtBufs {
-  DevBuf keys, eval, vals, fb, out;
+  DevBuf keys, eval, vals, fb;
+  size_t out_last = 0;
 };
 
 struct ip_ctx {
@@ -814,6 +815,9 @@ struct ip_cells {
 
 // Device memory through the context's cache (see DevCache).
 int ip_dalloc(ip_ctx *ctx, void **p, size_t bytes);
+// The same for a buffer that had `last` bytes the time before: an idle block of
+// that size to twice that, if there is one.  *got: the bytes it may use.
+int ip_dalloc_again(ip_ctx *ctx, void **p, size_t bytes, size_t last, size_t *got);
 void ip_dfree(ip_ctx *ctx, void *p);
 void ip_cache_release(ip_ctx *ctx);
 

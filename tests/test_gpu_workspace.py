@@ -92,3 +92,27 @@ def test_seeds_that_fill_the_table(ip):
     print(f"vertices {st['n_vertices']} of {want}, regrows {st['regrows']}", flush=True)
     assert want > 4.2e6 and st["regrows"] > 0 and st["n_cells"] == 0
     assert abs(st["n_vertices"] - want) <= 1000       # seeds within rounding of a simplex's face
+
+
+def test_held_after_a_request(ip):
+    """What a server's slot keeps of a request with 5.6 M cells, at a pool of
+    64 MiB: the vertex table (36 bytes an entry, four times the vertices
+    rounded up), the slots of its largest frontier (62 of 4 bytes an edge, here
+    a sixth of the cells, a quarter assumed, up to 256 MiB more for growth),
+    and 64 MiB of idle blocks; its edge lists only as one of those; 64 MiB for
+    the rest."""
+    import torch
+    wl = I.subbox_case(6, 40, 0.05, 8e6, seed=4, eps=0.05)
+    srv = ip.ip_server_create(0, 64 << 20, 1)
+    try:
+        ip.ip_server_wait(srv, ip.ip_server_submit(srv, I.config_c1()))
+        free0 = torch.cuda.mem_get_info()[0]
+        r = ip.ip_server_wait(srv, ip.ip_server_submit(srv, wl))
+        held = free0 - torch.cuda.mem_get_info()[0]
+    finally:
+        ip.ip_server_destroy(srv)
+    st = r["stats"]
+    slots = st["n_cells"] / 4 * 62 * 4
+    want = 36 * _pow2(4 * st["n_vertices"]) + slots + min(slots, 256 << 20) + (128 << 20)
+    print(f"held {held / 1e6:.1f} MB of {want / 1e6:.1f}", flush=True)
+    assert st["n_cells"] > 5e6 and held <= want
