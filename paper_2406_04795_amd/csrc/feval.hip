@@ -205,6 +205,8 @@ __global__ __launch_bounds__(256, (P < 0 || R < 4) ? 4 : 2) void feval64_tile_ke
 // long and needs no sharing of the records (d = 5, S = 300, 1048576 vertices:
 // 351 with one per lane, 438 with two).
 constexpr uint64_t kSplitMax = 16384;
+// Threads that fill the chip (1024 on each CU).
+constexpr uint64_t kFill = 262144;
 
 // One call of the canonical sum: see the MODEs above and launch_feval64.
 struct Eval64 {
@@ -217,14 +219,19 @@ struct Eval64 {
   double *out;
   uint64_t hint;  // items the launch is shaped for
   unsigned long long *stamp;
+  uint64_t spread;  // the grid covers this many, up to what fills the chip (0: hint)
 };
 
 template <int D, int P, int MODE>
 void launch64(const Eval64 &e, const FDev &F, const LatDev &L) {
   const uint64_t n = e.hint;
-#define IP_L64(KERNEL, PER, BLOCK)                                                                                  \
-  hipLaunchKernelGGL(KERNEL, dim3((unsigned)std::min<uint64_t>((n + (PER) - 1) / (PER), 65536)), dim3(BLOCK), 0, e.st, \
-                     F, L, e.list, e.n, e.n_dev, e.keys, e.vraw, e.out, e.stamp)
+  auto grid = [&](uint64_t per, uint64_t fill) {
+    const uint64_t more = std::min<uint64_t>((e.spread + per - 1) / per, fill);
+    return dim3((unsigned)std::max(more, std::min<uint64_t>((n + per - 1) / per, 65536)));
+  };
+#define IP_L64(KERNEL, PER, BLOCK)                                                                              \
+  hipLaunchKernelGGL(KERNEL, grid(PER, kFill / (BLOCK)), dim3(BLOCK), 0, e.st, F, L, e.list, e.n, e.n_dev, e.keys, \
+                     e.vraw, e.out, e.stamp)
   if (n <= 1792) {
     IP_L64((feval64_split_kernel<D, P, MODE, 1>), 7, 512);
   } else if (n <= 3584) {
@@ -261,9 +268,10 @@ void launch64_p(const Eval64 &e, const FDev &F, const LatDev &L) {
 template <int MODE>
 int dispatch64(ip_ctx *ctx, const FDev &F, const LatDev &L, const uint32_t *list, uint64_t n,
                const uint64_t *keys, const int32_t *vraw, double *out,
-               const unsigned long long *n_dev = nullptr, uint64_t hint = 0, unsigned long long *stamp = nullptr) {
+               const unsigned long long *n_dev = nullptr, uint64_t hint = 0, unsigned long long *stamp = nullptr,
+               uint64_t spread = 0) {
   if (n == 0) return IP_OK;
-  const Eval64 e{ctx->stream, list, n, n_dev, keys, vraw, out, hint ? std::min(hint, n) : n, stamp};
+  const Eval64 e{ctx->stream, list, n, n_dev, keys, vraw, out, hint ? std::min(hint, n) : n, stamp, spread};
   switch (L.d) {
     case 2: launch64_p<2, MODE>(e, F, L); break;
     case 3: launch64_p<3, MODE>(e, F, L); break;
@@ -932,9 +940,15 @@ int ip_feval_noalloc_impl(ip_ctx *ctx, const ip_problem *p, const int32_t *v_dev
   IP_TRY_HIP(ctx, hipGetLastError());
   IP_TRY(dispatch32_p<1>(ctx, p, p->fine, nullptr, (uint64_t)n, nullptr, nullptr, v_dev, f_dev, bound_dev, fbl,
                          hdr, hdr + 1));
-  // shaped for one vertex in eight left over: few are near f = 0 (none of
-  // 1 000 003 uniform ones), and the blocks that find nothing to do still cost
-  return dispatch64<2>(ctx, p->f, p->fine, fbl, (uint64_t)n, nullptr, v_dev, f_dev, hdr, ((uint64_t)n + 7) / 8);
+  // None or all of the vertices may be left over, and the launch cannot know.
+  // Up to 65 536 the form for an eighth of them: a few take 21 us at S = 2000
+  // instead of the 90 of a lane each, all of 60 000 take 207.  Above, a lane
+  // each or more (all of 140 000: 252).  The grid is for all of them, up to
+  // what fills the chip: with the grid for an eighth, all of 140 000 took
+  // 748.
+  const uint64_t eighth = ((uint64_t)n + 7) / 8;
+  const uint64_t hint = (uint64_t)n <= 65536 ? eighth : std::max<uint64_t>(eighth, 65536);
+  return dispatch64<2>(ctx, p->f, p->fine, fbl, (uint64_t)n, nullptr, v_dev, f_dev, hdr, hint, nullptr, (uint64_t)n);
 }
 
 int launch_feval64(ip_ctx *ctx, const ip_problem *p, const LatDev &L, const uint32_t *list, uint64_t n, VEnt *vt,

@@ -761,17 +761,20 @@ int eval_pending(Run &s, uint64_t n) {
   return launch_feval64(ctx, s.p, s.L, s.fb, nfb, s.vt);
 }
 
+// Fewest vertices that the canonical pass of a certified level is shaped for:
+// a quarter of the CUs, as most manifolds leave it a few vertices or none.
+constexpr uint64_t kOpen0 = 448;
+
 // eval_pending of the level chain: the count is in *n_dev (about `hint`), and
-// the canonical pass takes its own from the device too.
-int eval_chain(Run &s, const unsigned long long *n_dev, uint64_t hint) {
+// the canonical pass takes its own from the device too (about `open`).
+int eval_chain(Run &s, const unsigned long long *n_dev, uint64_t hint, uint64_t open) {
   ip_ctx *ctx = s.ctx;
   // levels grow faster than the counters are read: a block per CU at least
   hint = std::max<uint64_t>(hint, 1792);
   Counters *c = ctx->ctr_dev;
   if (!s.cert) return launch_feval64(ctx, s.p, s.L, s.eval, s.vt_cap, s.vt, n_dev, hint, &c->t_eval);
   IP_TRY(launch_feval32(ctx, s.p, s.L, s.eval, s.vt_cap, s.vt, s.vb, s.fb, &c->n_fb, n_dev, hint, &c->t_eval));
-  // rarely more than a few vertices
-  return launch_feval64(ctx, s.p, s.L, s.fb, s.vt_cap, s.vt, &c->n_fb, 448);
+  return launch_feval64(ctx, s.p, s.L, s.fb, s.vt_cap, s.vt, &c->n_fb, std::max<uint64_t>(open, kOpen0));
 }
 
 // Pass 1 or 2 of a level, for a frontier of about `edges`.
@@ -817,12 +820,13 @@ int trace_direct(Run &s, ip_stats &st, uint64_t *n_out_ret) {
   hipLaunchKernelGGL((seed_vertices_kernel<D>), dim3(sg), dim3(128), 0, ctx->stream, s.L, p->seeds_dev, p->n_seeds,
                      s.vt, s.vt_cap - 1, s.eval, dev);
   IP_TRY_HIP(ctx, hipGetLastError());
-  IP_TRY(eval_chain(s, &dev->n_ev[1], seed_verts));
+  IP_TRY(eval_chain(s, &dev->n_ev[1], seed_verts, 0));
   hipLaunchKernelGGL((seed_edges_kernel<D>), dim3(sg), dim3(128), 0, ctx->stream, s.L, p->seeds_dev, p->n_seeds, s.vt,
                      s.vt_cap - 1, s.out, dev);
   IP_TRY_HIP(ctx, hipGetLastError());
-  // estimates that shape the next launches: frontier edges, new vertices
-  uint64_t edges = seed_verts * D / 2, verts = seed_verts;
+  // estimates that shape the next launches: frontier edges, new vertices, and
+  // those of them that no bound settles
+  uint64_t edges = seed_verts * D / 2, verts = seed_verts, open = 0;
   int64_t fb_seen = 0, c64_seen = 0;  // of evaluations whose level was queued again
   uint32_t level = 0, chunk = 0;
   bool from_edges = false;            // the first level queued starts with pass 2
@@ -830,7 +834,7 @@ int trace_direct(Run &s, ip_stats &st, uint64_t *n_out_ret) {
     for (uint32_t q = 0; q < kChain; ++q, ++level) {
       if (!from_edges) {
         IP_TRY((level_pass<D, false>(s, level, edges)));
-        IP_TRY(eval_chain(s, &dev->n_ev[level & 1u], verts));
+        IP_TRY(eval_chain(s, &dev->n_ev[level & 1u], verts, open));
       }
       from_edges = false;
       IP_TRY((level_pass<D, true>(s, level, edges)));
@@ -856,6 +860,7 @@ int trace_direct(Run &s, ip_stats &st, uint64_t *n_out_ret) {
       const uint32_t done = (uint32_t)c->levels;
       edges = 2 * (c->n_out - c->lv[done & 3u]) + 64;
       verts = (c->vt_cnt[done & 1u] - c->vt_cnt[(done + 1) & 1u]) * 5 / 4 + 64;
+      open = c->n_fb * 5 / 4;
       continue;
     }
     IP_TRY(read_ctr(ctx));  // the chunk behind it has run out
@@ -888,6 +893,7 @@ int trace_direct(Run &s, ip_stats &st, uint64_t *n_out_ret) {
       fb_seen += (int64_t)c->n_fb;
       c64_seen += (int64_t)c->n_cert64;
       verts = 2 * n_ev + 64;
+      open = 2 * c->n_fb;
       IP_TRY(vt_grow<D>(s, pow2_at_least(std::max<uint64_t>(nv * 4, s.vt_cap * 2)), hi));
       // slots moved: pass 1 again, so that CSL points into the new table;
       // every vertex listed so far is evaluated and counted
