@@ -654,13 +654,39 @@ __global__ __launch_bounds__(256) void seed_kernel(FDev F, LatDev L, const doubl
   }
 }
 
-// Canonical polynomial f and gradient at x (the order of ip.h's ip_seed_search): per
+// The part of FDev that f_grad needs.
+struct FRec {
+  const double *rec;
+  int64_t S;
+  int32_t p, kernel;
+  double gamma, coef0, bias;
+};
+
+// Canonical f and gradient at x (the order of ip.h's ip_seed_search): per
 // support vector in index order, read as a wave-uniform record.
 template <int D>
-__device__ __forceinline__ double f_grad(const FDev &F, const double *x, double *g) {
+__device__ __forceinline__ double f_grad(const FRec &F, const double *x, double *g) {
   double acc = 0.0;
 #pragma unroll
   for (int j = 0; j < D; ++j) g[j] = 0.0;
+  if (F.kernel == IP_KERNEL_RBF) {
+    const double m2g = -2.0 * F.gamma;
+    for (int64_t i = 0; i < F.S; ++i) {
+      const double *rec = F.rec + i * 8;
+      double df[D], d2 = 0.0;
+#pragma unroll
+      for (int j = 0; j < D; ++j) {
+        df[j] = x[j] - rec[j];
+        d2 = fma(df[j], df[j], d2);
+      }
+      const double e = exp_own(-(F.gamma * d2));
+      acc = fma(rec[D], e, acc);
+      const double w = (rec[D] * e) * m2g;
+#pragma unroll
+      for (int j = 0; j < D; ++j) g[j] = fma(w, df[j], g[j]);
+    }
+    return acc + F.bias;
+  }
   const double pg = (double)F.p * F.gamma;
   for (int64_t i = 0; i < F.S; ++i) {
     const double *rec = F.rec + i * 8;
@@ -681,17 +707,28 @@ __device__ __forceinline__ double f_grad(const FDev &F, const double *x, double 
   return acc + F.bias;
 }
 
-// Very many starts of a polynomial, one lane per start: with three waves on
-// every SIMD a scalar load per record is hidden, and is cheaper than the
-// record's way through LDS and into vector registers (d = 6, S = 2000, 20
-// steps: 131 072 starts 6.87 ms, 2^20 27.6; through LDS 5.37 and 31.0; two
-// starts per lane 31.0 too; d = 5, S = 500, 10 steps: 131 072: 0.93 and 0.72,
-// 262 144: 1.15 and 1.33).  The Gaussian is faster through LDS at any count.
-constexpr int64_t kSeedMany = 196608;
+// Most starts whose records go through LDS; above, one lane per start reads
+// them by scalar loads.  These hit while the records (64 bytes each) fit the
+// scalar cache (16 KiB); else each is a miss, which three waves on a SIMD hide
+// (65 536 starts are one).  Scalar and LDS in us, 10 steps: d = 6, S = 100:
+// 65 536 starts 131 and 128, 131 072: 157 and 166, 196 608: 194 and 223; d = 6,
+// S = 300: 131 072: 449 and 465, 180 000: 540 and 593; d = 4, S = 300: 131 072:
+// 451 and 384, 196 608: 506 and 469; d = 5, S = 500: 131 072: 907 and 689, 180 000:
+// 960 and 919, 196 608: 831 and 884, 262 144: 1042 and 1087; Gaussian, d = 4, S =
+// 100: 65 536: 201 and 188, 131 072: 279 and 294, 196 608: 376 and 395; d = 6, S =
+// 300: 150 000: 1273 and 1169, 262 144: 1569 and 1672.  Of very few records
+// the way through their tile costs what it saves (S = 24, d = 6: 65 536: 45 and
+// 47; S = 8: 13 000: 23 and 24).
+int64_t seed_lds_max(int64_t S, bool rbf) {
+  if (S < 32) return 0;
+  if (S <= 256) return 65536;
+  return S <= 384 && !rbf ? 131072 : 184320;
+}
 
 template <int D>
-__global__ __launch_bounds__(256) void seed_many_kernel(FDev F, LatDev L, const double *__restrict__ q0,
-                                                        uint64_t n, int iters, double *__restrict__ q, double *__restrict__ fq) {
+__global__ __launch_bounds__(256) void seed_scalar_kernel(FRec F, LatDev L, const double *__restrict__ q0, uint64_t n,
+                                                          int iters, double *__restrict__ q,
+                                                          double *__restrict__ fq) {
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
     double x[D], g[D];
 #pragma unroll
@@ -727,10 +764,20 @@ __global__ __launch_bounds__(256) void seed_many_kernel(FDev F, LatDev L, const 
 // per start, 0.76 with single reads, 0.67 now).
 constexpr int kSeedG = 16, kSeedT = 48;
 // One lane per start takes the same time up to 65 536 starts (a wave per
-// SIMD); the split form grows from four blocks per CU on.  Both at d = 5,
-// S = 500, 10 steps: 3000 starts 125 us (split) and 527, 12 000: 292 and 527,
-// 16 000: 367 and 527; at d = 3, S = 50: 12 000: 59 and 56, 16 000: 70 and 56.
+// SIMD); the split form takes a step more with every 4096 (a block per CU)
+// and has a cost per step of its own, so it needs the more vectors the more
+// starts there are.  Split and one lane each in us, 10 steps, d = 3: S = 8:
+// 4096 starts 27 and 23; S = 24: 34 and 38, 8192: 55 and 38; S = 50: 8192: 50
+// and 61, 12 288: 68 and 61; S = 100: 12 288: 92 and 105; Gaussian S = 24: 4096: 38
+// and 53, 8192: 62 and 53; S = 50: 12 288: 83 and 90.  d = 5, S = 500: 12 000: 292
+// and 527, 16 000: 367 and 527.
 constexpr int64_t kSeedSplitMax = 12288;
+
+bool seed_split(int64_t n, int64_t S, bool rbf) {
+  if (n > kSeedSplitMax) return false;
+  const int step = (int)((n + 4095) / 4096) - 1;  // 0, 1, 2
+  return S >= ((rbf ? 16 : 24) << step);
+}
 
 template <int D, bool RBF>
 __global__ __launch_bounds__(512) void seed_split_kernel(FDev F, LatDev L, const double *__restrict__ q0, uint64_t n,
@@ -869,20 +916,22 @@ __global__ __launch_bounds__(512) void seed_split_kernel(FDev F, LatDev L, const
 
 int ip_seed_search_impl(ip_ctx *ctx, const ip_problem *p, const double *q0, int64_t n, int32_t iters, double *q,
                         double *fq) {
-  const bool split = n <= kSeedSplitMax, rbf = p->f.kernel == IP_KERNEL_RBF;
+  const bool rbf = p->f.kernel == IP_KERNEL_RBF;
+  const bool split = seed_split(n, p->f.S, rbf), lds = n <= seed_lds_max(p->f.S, rbf);
   const unsigned blocks = (unsigned)std::min<int64_t>(split ? (n + kSeedG - 1) / kSeedG : (n + 255) / 256, 16384);
-#define IP_SDK(KERNEL, THREADS)                                                                                  \
-  hipLaunchKernelGGL(KERNEL, dim3(blocks), dim3(THREADS), 0, ctx->stream, p->f, p->fine, q0, (uint64_t)n, (int)iters, \
-                     q, fq)
+  const FRec fr{p->f.rec, p->f.S, p->f.p, p->f.kernel, p->f.gamma, p->f.coef0, p->f.bias};
+#define IP_SDF(KERNEL, THREADS, F) \
+  hipLaunchKernelGGL(KERNEL, dim3(blocks), dim3(THREADS), 0, ctx->stream, F, p->fine, q0, (uint64_t)n, (int)iters, q, fq)
+#define IP_SDK(KERNEL, THREADS) IP_SDF(KERNEL, THREADS, p->f)
 #define IP_SD(DD)                                \
   if (split && rbf)                              \
     IP_SDK((seed_split_kernel<DD, true>), 512);  \
   else if (split)                                \
     IP_SDK((seed_split_kernel<DD, false>), 512); \
+  else if (!lds)                                 \
+    IP_SDF((seed_scalar_kernel<DD>), 256, fr);   \
   else if (rbf)                                  \
     IP_SDK((seed_kernel<DD, true>), 256);        \
-  else if (n > kSeedMany)                        \
-    IP_SDK((seed_many_kernel<DD>), 256);         \
   else                                           \
     IP_SDK((seed_kernel<DD, false>), 256)
   switch (p->d) {
@@ -896,6 +945,7 @@ int ip_seed_search_impl(ip_ctx *ctx, const ip_problem *p, const double *q0, int6
   }
 #undef IP_SD
 #undef IP_SDK
+#undef IP_SDF
   IP_TRY_HIP(ctx, hipGetLastError());
   return IP_OK;
 }
