@@ -720,17 +720,19 @@ int out_reserve(Run &s, uint64_t need, uint64_t n_used) {
   IP_TRY(ip_dalloc_again(ctx, &nb, cap * sizeof(OutRec), s.out ? 0 : s.tb->out_last, &got));
   if (n_used)
     IP_TRY_HIP(ctx, hipMemcpyAsync(nb, s.out, n_used * sizeof(OutRec), hipMemcpyDeviceToDevice, ctx->stream));
-  IP_TRY_HIP(ctx, hipStreamSynchronize(ctx->stream));
-  if (s.out) release(ctx, s.out);
+  if (s.out) {
+    IP_TRY_HIP(ctx, hipStreamSynchronize(ctx->stream));
+    release(ctx, s.out);
+  }
   s.out = (OutRec *)nb;
   s.out_cap = got / sizeof(OutRec);
   return IP_OK;
 }
 
-// The search's edges are no longer needed.
+// The search's edges are no longer needed (by work queued after this; what
+// takes the block next runs on the same stream).
 void out_release(Run &s) {
   if (!s.out) return;
-  (void)hipStreamSynchronize(s.ctx->stream);
   s.tb->out_last = s.out_cap * sizeof(OutRec);
   release(s.ctx, s.out);
   s.out = nullptr;
