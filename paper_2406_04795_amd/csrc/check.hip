@@ -229,11 +229,6 @@ __device__ __forceinline__ bool sphere_cyl(const double *c, double r, const doub
 // predicates, so skipping their tests leaves every verdict unchanged.  Boxes
 // and cylinders are first tested against a ball holding them (centre x,
 // radius rb): farther than R + rb, the ball cannot reach them.
-__device__ __forceinline__ bool ball_near_sphere(const double *c, double R, const double *o) {
-  const double rr = R + o[3];
-  return !(sq3(c[0] - o[0], c[1] - o[1], c[2] - o[2]) > rr * rr);
-}
-
 __device__ __forceinline__ bool ball_near_box(const double *c, double R, const double *B) {
   const double dx = c[0] - B[3], dy = c[1] - B[7], dz = c[2] - B[11];
   double s = 0.0;

@@ -124,19 +124,6 @@ __device__ __forceinline__ float exp32_own(float t) {
   return ldexpf(p, (int)k);
 }
 
-// One canonical RBF term: alpha exp(-(gamma d2)) with d2 the fma chain of
-// (x_j - s_j)^2 over j, added to acc with an fma.
-template <int D>
-__device__ __forceinline__ double rbf_term(const double *sv, double al, double gamma, const double *x, double acc) {
-  double d2 = 0.0;
-#pragma unroll
-  for (int j = 0; j < D; ++j) {
-    const double df = x[j] - sv[j];
-    d2 = fma(df, df, d2);
-  }
-  return fma(al, exp_own(-(gamma * d2)), acc);
-}
-
 // One term of the canonical sum at x: t^p (P > 0: the degree, 0: F.p) or, P
 // = -1, the Gaussian exp(-(gamma |x - s|^2)); acc = fma(alpha, term, acc)
 // follows in index order.
@@ -399,18 +386,6 @@ __device__ __forceinline__ int ht_insert(uint64_t *keys, uint64_t mask, uint64_t
   return -1;
 }
 
-// Lookup in a table that no thread modifies during the kernel.
-__device__ __forceinline__ int64_t ht_find(const uint64_t *keys, uint64_t mask, uint64_t key) {
-  uint64_t h = mix64(key) & mask;
-  for (uint64_t n = 0; n <= mask && n < IP_MAX_PROBE; ++n) {
-    uint64_t cur = keys[h];
-    if (cur == key) return (int64_t)h;
-    if (cur == IP_EMPTY_KEY) return -1;
-    h = (h + 1) & mask;
-  }
-  return -1;
-}
-
 // Vertex-table entry: packed vertex key, f at the vertex (NaN payload while
 // pending), and a bitmask of the visited edges (v, R) whose smaller endpoint
 // is this vertex, bit R of the 2^d-bit mask (the edge set of the search).
@@ -445,6 +420,7 @@ __device__ __forceinline__ int ht_insert_s(uint64_t *base, uint64_t mask, uint64
   return -1;
 }
 
+// Lookup in a table that no thread modifies during the kernel.
 template <int SW>
 __device__ __forceinline__ int64_t ht_find_s(const uint64_t *base, uint64_t mask, uint64_t key) {
   uint64_t h = mix64(key) & mask;

@@ -587,7 +587,6 @@ struct Run {
   bool cert = false;      // FP32 certified evaluation (else canonical FP64)
   float *vb = nullptr;    // per-slot bound of the stored f (cert only)
   uint32_t *fb = nullptr; // FP64 fallback list
-  uint64_t fb_cap = 0;
   int64_t n_fallback = 0;
   int64_t n_settled64 = 0;
 };
@@ -657,7 +656,6 @@ int vt_init(Run &s, uint64_t cap) {
     IP_TRY(ip_ensure(ctx, tb.fb, cap * 4));
     s.vb = (float *)tb.vals.p;
     s.fb = (uint32_t *)tb.fb.p;
-    s.fb_cap = tb.fb.bytes / 4;
   }
   return IP_OK;
 }
@@ -699,7 +697,6 @@ int vt_grow(Run &s, uint64_t new_cap, uint64_t n_out) {
     s.vb = (float *)nvb;
     IP_TRY(ip_ensure(ctx, tb.fb, new_cap * 4));
     s.fb = (uint32_t *)tb.fb.p;
-    s.fb_cap = tb.fb.bytes / 4;
   }
   IP_TRY(remap_out<D>(s, n_out));
   ++s.regrows;
@@ -936,20 +933,7 @@ __device__ __forceinline__ int nth_bit(uint32_t m, int n) {
   return __ffs((int)m) - 1;
 }
 
-// Lehmer code of a permutation w of {0..D-1} in the factorial number system.
-template <int D>
-__device__ __forceinline__ uint32_t lehmer_encode(const int32_t *w) {
-  uint32_t code = 0;
-#pragma unroll
-  for (int i = 0; i < D; ++i) {
-    uint32_t c = 0;
-#pragma unroll
-    for (int j = i + 1; j < D; ++j) c += (uint32_t)(w[j] < w[i]);
-    code = code * (uint32_t)(D - i) + c;
-  }
-  return code;
-}
-
+// The permutation w of {0..D-1} of a Lehmer code in the factorial number system.
 template <int D>
 __device__ __forceinline__ void lehmer_decode(uint32_t code, int32_t *w) {
   uint32_t c[D];
@@ -968,11 +952,6 @@ __device__ __forceinline__ void lehmer_decode(uint32_t code, int32_t *w) {
 
 // Coarse n-simplex key: coarse vertex in the high bits, Lehmer code of the
 // coordinate order w in the low LB bits.
-template <int D>
-__device__ __forceinline__ uint64_t sig_key(const LatDev &Lc, const int32_t *v, const int32_t *w, int LB) {
-  return (vpack<D>(Lc, v) << LB) | (uint64_t)lehmer_encode<D>(w);
-}
-
 template <int D>
 __device__ __forceinline__ void sig_unpack(const LatDev &Lc, uint64_t key, int LB, int32_t *v, int32_t *w) {
   lehmer_decode<D>((uint32_t)(key & ((1ull << LB) - 1ull)), w);
@@ -1138,17 +1117,10 @@ __global__ __launch_bounds__(kExpand) void sigma_kernel(LatDev Lc, int LB, const
   stage_flush_block(st[wib], sn, put, &ctr->n_aux);
 }
 
-// Template point p of coarse simplex (v, w) in fine lattice coordinates:
-// y_{w_i} = k v_{w_i} + u_i (Eq. 1 with the coarse edge directions e_{w_i}).
-template <int D>
-__device__ __forceinline__ void template_point(const int32_t *v, const int32_t *w, int k, uint64_t up, int32_t *y) {
-#pragma unroll
-  for (int i = 0; i < D; ++i) y[w[i]] = k * v[w[i]] + (int32_t)((up >> (8 * i)) & 0xffu);
-}
-
-// The same point from the inverse order: coordinate c carries template
-// coordinate winv[c] (w[winv[c]] = c); no register array is indexed at run
-// time.
+// Template point of coarse simplex (v, w) in fine lattice coordinates: y_{w_i}
+// = k v_{w_i} + u_i (Eq. 1 with the coarse edge directions e_{w_i}), from the
+// inverse order: coordinate c carries template coordinate winv[c] (w[winv[c]] =
+// c); no register array is indexed at run time.
 template <int D>
 __device__ __forceinline__ void template_point_inv(const int32_t *v, const int32_t *winv, int k, uint64_t up,
                                                    int32_t *y) {
@@ -2748,7 +2720,6 @@ int subdivide_table(ip_ctx *ctx, const ip_problem *p, const SubArgs &a, const ui
     IP_TRY(ip_ensure(ctx, ctx->vtf.fb, vcap * 4));
     f.vb = (float *)ctx->vtf.vals.p;
     f.fb = (uint32_t *)ctx->vtf.fb.p;
-    f.fb_cap = ctx->vtf.fb.bytes / 4;
     return IP_OK;
   };
   f.cert = cert;

@@ -178,12 +178,6 @@ def _d(keep, a):
     return a.ctypes.data_as(_dp)
 
 
-def _i(keep, a):
-    a = np.ascontiguousarray(a, dtype=np.int32)
-    keep.append(a)
-    return a.ctypes.data_as(_ip)
-
-
 def _stream_handle(stream):
     if stream is None:
         import torch
