@@ -384,7 +384,9 @@ constexpr int kSceneLds = 3072;
 // verdict.  Robots with capsules use the per-configuration kernel.
 // The scene (all of it up to the culling rows, and the integers) is staged
 // into LDS first: read from memory wave-uniformly, every joint and obstacle
-// is one more serial miss of the scalar cache.
+// is one more serial miss of the scalar cache.  From 8192 waves on others hide
+// that, and scalar operands are the cheaper (63 spheres, 48 obstacles, 1000
+// waves: 24 us with LDS and 30 without, 8000: 50 and 49, 16 000: 85 and 72).
 template <int NSP, bool LDS>
 __global__ __launch_bounds__(256) void check_sphere_kernel(SceneDev S, int n_lsph, const double *__restrict__ q,
                                                            int64_t n, int64_t ld, uint8_t *__restrict__ verdict) {
@@ -438,24 +440,38 @@ __global__ __launch_bounds__(256) void check_sphere_kernel(SceneDev S, int n_lsp
   }
 }
 
+// Most waves of the sphere-parallel layout: above, one lane per configuration.
+// That layout pays the kinematics once per sphere and does not cull, but has
+// no serial chain over links and obstacles; the other takes about the same
+// time up to 256 000 configurations, which grows with the spheres and, until
+// most configurations collide, with the obstacles.  Sphere-parallel and the
+// other in us, 16 obstacles: 18 spheres (32 lanes), 6000 configurations 19 and
+// 33, 16 000: 30 and 32, 64 000: 88 and 31 (unrelated configurations, few free:
+// 16 384: 44 and 69, 40 000: 72 and 69); 8 spheres: 64 000: 24 and 30, 128 000: 38
+// and 32; 63 spheres (64 lanes): 8192: 45 and 148, 20 000: 71 and 148, 40 000: 114
+// and 152, 65 536: 165 and 151; with one obstacle 16 384: 50 and 44; with 120
+// obstacles 16 384: 156 and 155 to 235.  So 8192 waves, or as many as take what
+// the other's chain is expected to, less a margin of 28 us: where nearly every
+// configuration collides early the chain is short (63 spheres, 32 obstacles
+// around the base: 35), which the scene's sizes do not say.
+int64_t check_sphere_waves(int n_lsph, int nobs) {
+  const double chain = n_lsph * std::min(150.0 * nobs, 2000.0 + 10.0 * nobs);  // ns
+  return std::max<int64_t>(8192, (int64_t)((chain - 28000.0) / (1.4 + 0.045 * nobs)));
+}
+
 // Launches the verdict kernel for n configurations: the sphere-parallel
-// layout when the robot is made of at most 64 spheres and its lanes start
-// fewer than 8192 waves, else the per-configuration kernel.  The first pays
-// the kinematics once per sphere and does not cull, but has no serial chain
-// over links and obstacles; the second takes about the same time up to
-// 256 000 configurations.  Both in us for 18 spheres (32 lanes) against 16
-// obstacles: 6000 configurations 19 and 33, 16 000: 30 and 32, 64 000: 88 and
-// 31, 500 000: 603 and 51; for 8 spheres: 64 000: 24 and 30, 128 000: 38 and
-// 32.
+// layout when the robot is made of at most 64 spheres and starts no more waves
+// than check_sphere_waves, else the per-configuration kernel.
 int launch_check(ip_ctx *ctx, const SceneDev &S, int n_lsph, int n_lcap, const double *q, int64_t n, int64_t ld,
                  uint8_t *verdict) {
   if (n == 0) return IP_OK;
   int nsp = 1;
   while (nsp < n_lsph && nsp < 64) nsp <<= 1;
-  if (n_lcap == 0 && n_lsph > 0 && n_lsph <= 64 && n < 8192 * 64 / nsp) {
+  if (n_lcap == 0 && n_lsph > 0 && n_lsph <= 64 &&
+      n < check_sphere_waves(n_lsph, S.n_osph + S.n_obox + S.n_ocyl) * 64 / nsp) {
     const int64_t per_block = 4 * (64 / nsp);
     const int64_t blocks = std::min<int64_t>((n + per_block - 1) / per_block, 65536);
-    const bool lds = S.ocyl + 16 * S.n_ocyl - S.joint_T <= kSceneLds;
+    const bool lds = S.ocyl + 16 * S.n_ocyl - S.joint_T <= kSceneLds && n * nsp <= 8192 * 64;
 #define IP_CSK(NN, LL)                                                                                            \
   hipLaunchKernelGGL((check_sphere_kernel<NN, LL>), dim3((unsigned)blocks), dim3(256), 0, ctx->stream, S, n_lsph, q, \
                      n, ld, verdict)
