@@ -194,17 +194,28 @@ __global__ __launch_bounds__(256, (P < 0 || R < 4) ? 4 : 2) void feval64_tile_ke
   }
 }
 
-// Which kernel, by the vertex count n (times in us at d = 6, p = 3,
-// S = 2000).  Up to 16384 vertices one lane each fills less than one wave per
-// CU, and the split form is the faster (4096: 23 against 90; 16384: 60
-// against 92), with as few vertices per forming wave as still give each CU a
-// block (1000: 21 with one, 24 with four).  Above, the least number of
-// vertices per lane that still fills the SIMDs once: 65 536 lanes are one wave
-// on each (65536: 1 per lane 101, 2 per lane 148; 200003: 1, 2 and 4 per lane
-// 264, 209, 232; 1048576: 1006, 772, 730).  The Gaussian term is 34 operations
-// long and needs no sharing of the records (d = 5, S = 300, 1048576 vertices:
-// 351 with one per lane, 438 with two).
+// Which kernel, by the vertex count n and the support vectors S (times in us,
+// d = 6, p = 3, S = 2000 unless given).  Up to 16384 vertices one lane each
+// fills less than one wave per CU, and the split form is the faster (4096: 23
+// against 90; 16384: 60 against 92), with as few vertices per forming wave as
+// still give each CU a block (1000: 21 with one, 24 with four).  It has a cost
+// of its own per block, so few support vectors need few vertices (split and
+// one lane each, S = 8: 61: 17 and 15; S = 50: 7000: 19 and 17, 16384: 28 and
+// 17; S = 200: 7000: 20 and 24, 16384: 28 and 24; S = 1000: 50 and 58).  Above,
+// the least number of vertices per lane that still fills the SIMDs once: 65 536
+// lanes are one wave on each (65536: 1 per lane 101, 2 per lane 148; 200003: 1,
+// 2 and 4 per lane 264, 209, 232; 600000, S = 1000: 309, 244 and 286; 700000:
+// 337, 286, 293; 1048576: 1006, 772, 730).  A degree without an instantiation
+// of its own (p = 5: the power is a loop) gains from sharing only where waves
+// abound, and never with four (S = 1000, 200000: 180, 246; 700000: 413, 493, 525;
+// 3000000: 1569, 1494, 1931).  The Gaussian term is 34 operations long and
+// needs no sharing (d = 5, S = 300, 1048576 vertices: 351 with one per lane, 438
+// with two), nor do very few support vectors (S = 8, 200000: 17 and 17).
 constexpr uint64_t kSplitMax = 16384;
+inline bool eval_split(uint64_t n, int64_t S) {
+  return n <= kSplitMax && S >= (n <= 3584 ? 32 : n <= 7168 ? 96 : 256);
+}
+
 // Threads that fill the chip (1024 on each CU).
 constexpr uint64_t kFill = 262144;
 
@@ -232,19 +243,20 @@ void launch64(const Eval64 &e, const FDev &F, const LatDev &L) {
 #define IP_L64(KERNEL, PER, BLOCK)                                                                              \
   hipLaunchKernelGGL(KERNEL, grid(PER, kFill / (BLOCK)), dim3(BLOCK), 0, e.st, F, L, e.list, e.n, e.n_dev, e.keys, \
                      e.vraw, e.out, e.stamp)
-  if (n <= 1792) {
-    IP_L64((feval64_split_kernel<D, P, MODE, 1>), 7, 512);
-  } else if (n <= 3584) {
-    IP_L64((feval64_split_kernel<D, P, MODE, 2>), 14, 512);
-  } else if (n <= kSplitMax) {
-    IP_L64((feval64_split_kernel<D, P, MODE, 4>), 28, 512);
-  } else if (P < 0) {
+  if (eval_split(n, F.S)) {
+    if (n <= 1792)
+      IP_L64((feval64_split_kernel<D, P, MODE, 1>), 7, 512);
+    else if (n <= 3584)
+      IP_L64((feval64_split_kernel<D, P, MODE, 2>), 14, 512);
+    else
+      IP_L64((feval64_split_kernel<D, P, MODE, 4>), 28, 512);
+  } else if constexpr (P < 0) {
     IP_L64((feval64_tile_kernel<D, P, 1, 2, MODE>), 256, 256);
-  } else if (n <= 98304) {
+  } else if (n <= 98304 || (P == 0 && n <= 786432) || (F.S < 32 && n <= 524288)) {
     IP_L64((feval64_tile_kernel<D, P, 1, 4, MODE>), 256, 256);
-  } else if (n <= 393216) {
+  } else if (P == 0 || n <= 655360) {
     IP_L64((feval64_tile_kernel<D, P, 2, 4, MODE>), 512, 256);
-  } else {
+  } else if constexpr (P > 0) {
     IP_L64((feval64_tile_kernel<D, P, 4, 4, MODE>), 1024, 256);
   }
 #undef IP_L64
