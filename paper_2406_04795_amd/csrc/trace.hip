@@ -830,7 +830,10 @@ int trace_direct(Run &s, ip_stats &st, uint64_t *n_out_ret) {
   uint32_t level = 0, chunk = 0;
   bool from_edges = false;            // the first level queued starts with pass 2
   auto queue = [&]() -> int {
-    for (uint32_t q = 0; q < kChain; ++q, ++level) {
+    // one level each at first: many a coarse search has no edges at all, and
+    // passes queued behind its end still cost 2 to 4 us each
+    const uint32_t len = chunk < 2 ? 1 : kChain;
+    for (uint32_t q = 0; q < len; ++q, ++level) {
       if (!from_edges) {
         IP_TRY((level_pass<D, false>(s, level, edges)));
         IP_TRY(eval_chain(s, &dev->n_ev[level & 1u], verts, open));
